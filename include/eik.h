@@ -66,15 +66,13 @@ extern "C" {
 #define EIK_FLAG_TRACK_CHANGE 8u  /* eik_opts.flags, ablation operators only: re-activate the
                                      neighbours when a value changes, not only when it decreases
                                      (the precision section's change tracking) */
-#define EIK_FLAG_PACKED 32u       /* eik_opts.flags, forward solves with EIK_OP_DBAR and
-                                     adjoints: each relaxation (adjoint: readiness) pass
-                                     first compacts the tile's dirty points into a dense
-                                     list (256-thread workgroups); without it every thread
-                                     handles its own point (one thread per point, up to
-                                     1024).  Same result either way; the packed form does
-                                     fewer evaluations per wave and can win when the device
-                                     is full of work (batches of shots), the default has
-                                     lower latency per pass (single solves). */
+#define EIK_FLAG_PACKED 32u       /* eik_opts.flags, with EIK_OP_DBAR: adjoints compact each
+                                     readiness pass's dirty points into a dense list
+                                     (256-thread workgroups) instead of one thread per point
+                                     (up to 1024).  Same result either way; the packed form
+                                     wins when the device is full of work (batches of
+                                     shots).  Accepted by forward solves, which have one
+                                     form (a wave per tile). */
 #define EIK_FLAG_WARM_START 16u   /* eik_opts.flags, forward solves with EIK_OP_DBAR: resume from
                                      the times already in t_out instead of +inf.  They must be
                                      an upper bound of the solution at every point (>= +0, not
@@ -112,7 +110,8 @@ typedef struct {
     int32_t tile[3];         /* tile shape (x, y, z); zeros => default for ndim (3D 16x8x8,
                                 2D 32x32).  Supported: 3D 32x8x4, 16x8x8, 8x8x8, 64x4x4,
                                 16x8x4, 8x8x4, 8x4x4; 2D 32x32, 64x16, 128x8, 16x16, 16x8 */
-    int32_t grid_blocks;     /* persistent workgroups; 0 => fill the device */
+    int32_t grid_blocks;     /* persistent workgroups at most; 0 => fill the device (a forward
+                                solve's workgroup has several waves, each with its own tile) */
     int64_t max_tile_visits; /* 0 => unlimited; else stop after this many tile visits (ELIMIT) */
     uint32_t flags;          /* EIK_FLAG_* bits.  EIK_FLAG_TIME_KERNELS: record HIP events
                                 around the persistent kernel (solve or adjoint) on `stream`;
@@ -145,18 +144,19 @@ typedef struct {
     int64_t tile_visits;     /* tiles claimed and processed by the persistent solve */
     int64_t point_updates;   /* points whose value decreased, summed over visits */
     int64_t ntiles;          /* tiles in the problem(s) */
-    int64_t relax_passes;    /* in-tile relaxation passes (adjoint: readiness passes), summed
-                                over visits */
+    int64_t relax_passes;    /* in-tile relaxation steps that had a dirty point (adjoint:
+                                readiness passes), summed over visits */
     uint32_t flags;          /* raw device flags (bit0 domain, bit1 limit, bit2 bad source, bit3 watchdog,
                                 bit4 invalid warm-start value) */
     int32_t status;          /* the EIK_* code these flags map to */
     double kernel_ms;        /* mean duration of the timed persistent kernels, or -1 */
     int64_t kernel_launches; /* how many launches kernel_ms averages */
-    double phase_us[4];      /* last solve or adjoint, summed over workgroups (microseconds of
+    double phase_us[4];      /* last solve or adjoint, summed over workers (microseconds of
                                 wall clock): [0] claiming / waiting for work, [1] staging a
                                 tile and its halo in LDS, [2] relaxing (adjoint: readiness
                                 passes), [3] write-back + publish */
-    int64_t workgroups;      /* persistent workgroups of the last launch */
+    int64_t workgroups;      /* persistent workers of the last launch: workgroups, or the waves
+                                of a forward solve, each running a tile at a time */
     int64_t bucket_advances; /* times the lowest open priority bucket moved on */
     int64_t handoffs;        /* runs that started on a neighbour handed on by the previous run */
     int64_t evaluations;     /* with eik_opts.work_ref: operator evaluations in the solve */

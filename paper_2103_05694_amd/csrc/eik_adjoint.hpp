@@ -82,7 +82,7 @@ __global__ void k_adj_push_all(int ntiles, const uint64_t* tile_tmax,
     if (blockIdx.x == 0 && threadIdx.x == 0) *s.poisoned = 0;  // rings were wiped by the reset
     for (int tile = blockIdx.x * blockDim.x + threadIdx.x; tile < ntiles; tile += gridDim.x * blockDim.x) {
         s.tstate[tile] = kQ;
-        __hip_atomic_fetch_add(s.pending, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        pend_add(s, 1, 0);
         push_tile(s, (uint32_t)tile, tref - as_f64(tile_tmax[tile]), 0);
     }
 }
@@ -137,7 +137,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT > 25
     __shared__ int s_cnt[2];
     __shared__ int s_more[3];  // direct form, per pass (mod 3): some point completed with an in-tile parent
     __shared__ int s_tile;
-    __shared__ int64_t s_bucket;
+    __shared__ int64_t s_slot;
     __shared__ uint32_t s_state;
     __shared__ uint32_t s_nb[6];
     __shared__ uint32_t s_nid[6];
@@ -162,7 +162,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT > 25
     constexpr int NAX = C::D3 ? 3 : 2;
     if (tid == 0) {
         s_next = -1;
-        s_bucket = 0;
+        s_slot = 0;
         for (int i = 0; i < 8; ++i) s_stat[i] = 0;
         s_stat[8] = wall_clock64();
     }
@@ -170,14 +170,14 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT > 25
     int32_t cur_hint = 0;  // wave 0: the window's lowest bucket as last seen
     for (;;) {
         if (tid < 64) {
-            int64_t bucket = s_bucket;
+            int64_t slot = s_slot;
             int tile = s_next;
-            if (tile < 0) tile = claim(S, &bucket, cur_hint);
+            if (tile < 0) tile = claim(S, &slot, cur_hint);
             else if (tid == 0) ++s_stat[7];
             if (tid == 0) {
                 s_next = -1;
                 s_tile = tile;
-                s_bucket = bucket;
+                s_slot = slot;
                 if (tile >= 0) {
                     ++s_stat[4];
                     uint32_t st = __hip_atomic_fetch_xor(S.tstate + tile, kQ | kR, __ATOMIC_RELAXED,
@@ -619,7 +619,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT > 25
         __syncthreads();
 
         if (tid < 64) {
-            const int nxt = publish(S, A.tkey, (uint32_t)tile, s_bucket, !visited, s_nb, s_nid, s_face, true);
+            const int nxt = publish(S, A.tkey, (uint32_t)tile, s_slot, !visited, s_nb, s_nid, s_face, true);
             if (tid == 0) s_next = nxt;
         }
         if (tid == 0) {

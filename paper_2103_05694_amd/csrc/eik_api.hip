@@ -18,6 +18,7 @@
 #define EIK_SOLVE_THREADS 1024
 #endif
 #include "eik_adjoint.hpp"
+#include "eik_sweep.hpp"
 
 using namespace eik;
 
@@ -48,14 +49,13 @@ constexpr int tile_threads() { return TX * TY * TZ < kThreads ? TX * TY * TZ : k
 constexpr int kSolveThreads = EIK_SOLVE_THREADS;
 template <int TX, int TY, int TZ>
 constexpr int solve_threads() { return TX * TY * TZ < kSolveThreads ? TX * TY * TZ : kSolveThreads; }
-constexpr int kRings = 32;
-// A push from a run claimed from bucket b lands at most nrings - 1 - lookahead
+// A push from a run claimed from bucket b lands at most kRings - 1 - lookahead
 // buckets above b; 16 leaves a push range of 15 buckets.
 constexpr int kMaxLookahead = 16;
 static_assert(kMaxLookahead < kRings && kMaxLookahead < 64, "the claim window is read by one wave");
 constexpr int kScalWords = 192;
 constexpr int kTimelineCap = 1 << 16;
-constexpr int kSCur = 0, kSPending = 64, kSFlags = 128, kSPoisoned = 129, kSSrcCount = 130;
+constexpr int kSCur = 0, kSFlags = 128, kSPoisoned = 129, kSSrcCount = 130;
 
 // One uploaded batch layout: the problem table (tile shape and offsets
 // included) and the source offsets, as on the host and on the device.
@@ -80,7 +80,7 @@ struct Workspace {
     uint64_t* tkey = nullptr;
     int64_t tiles_cap = 0;
     uint32_t ring_cap = 0;
-    // scalars, on separate 256-byte lines: cur, pending, then flags / poisoned /
+    // scalars, on separate 256-byte lines: cur, then flags / poisoned /
     // source-list count (see the kS* offsets)
     int32_t* scal = nullptr;
     unsigned long long* counters = nullptr;
@@ -164,7 +164,7 @@ int get_ws(hipStream_t st, Workspace** out) {
     w->stream = st;
     hipError_t e = hipMalloc((void**)&w->scal, kScalWords * sizeof(int32_t));
     if (e == hipSuccess) e = hipMalloc((void**)&w->counters, kCounters * sizeof(unsigned long long));
-    if (e == hipSuccess) e = hipMalloc((void**)&w->ctr, sizeof(uint32_t) * kRings * kCtrStride);
+    if (e == hipSuccess) e = hipMalloc((void**)&w->ctr, sizeof(uint32_t) * kCtrWords);
     if (e == hipSuccess) e = hipMalloc((void**)&w->timeline, sizeof(unsigned long long) * (2 + 2 * kTimelineCap));
     if (e != hipSuccess) {
         delete w;
@@ -173,7 +173,7 @@ int get_ws(hipStream_t st, Workspace** out) {
     int32_t init[kScalWords] = {0};
     init[kSPoisoned] = 1;  // the first reset initialises the rings
     HIP_TRY(hipMemcpy(w->scal, init, sizeof(init), hipMemcpyHostToDevice));
-    HIP_TRY(hipMemset(w->ctr, 0, sizeof(uint32_t) * kRings * kCtrStride));
+    HIP_TRY(hipMemset(w->ctr, 0, sizeof(uint32_t) * kCtrWords));
     HIP_TRY(hipMemset(w->counters, 0, kCounters * sizeof(unsigned long long)));
     HIP_TRY(hipMemset(w->timeline, 0, sizeof(unsigned long long) * (2 + 2 * kTimelineCap)));
     g_ws[key] = w;
@@ -191,7 +191,8 @@ int ensure_tiles(Workspace& w, int64_t ntiles) {
     if (ntiles > (int64_t)1 << 30) return fail(EIK_ENOTSUP, "more than 2^30 tiles");
     int rc;
     if ((rc = grow(&w.tstate, &w.tiles_cap, ntiles, w.stream))) return rc;
-    const uint32_t need_ring = next_pow2((uint64_t)std::max<int64_t>(w.tiles_cap, 2));
+    // each shard's ring holds its share of the tiles
+    const uint32_t need_ring = next_pow2((uint64_t)std::max<int64_t>((w.tiles_cap + kShards - 1) / kShards, 2));
     if (need_ring > w.ring_cap) {
         HIP_TRY(hipStreamSynchronize(w.stream));
         if (w.items) HIP_TRY(hipFree(w.items));
@@ -201,9 +202,10 @@ int ensure_tiles(Workspace& w, int64_t ntiles) {
         w.tkey = nullptr;
         w.tile_tmax = nullptr;
         w.ring_cap = 0;
-        hipError_t e = hipMalloc((void**)&w.items, sizeof(uint64_t) * (size_t)kRings * need_ring);
-        if (e == hipSuccess) e = hipMalloc((void**)&w.tkey, sizeof(uint64_t) * (size_t)need_ring);
-        if (e == hipSuccess) e = hipMalloc((void**)&w.tile_tmax, sizeof(uint64_t) * (size_t)need_ring);
+        const size_t slots = (size_t)kShards * need_ring;
+        hipError_t e = hipMalloc((void**)&w.items, sizeof(uint64_t) * kRings * slots);
+        if (e == hipSuccess) e = hipMalloc((void**)&w.tkey, sizeof(uint64_t) * slots);
+        if (e == hipSuccess) e = hipMalloc((void**)&w.tile_tmax, sizeof(uint64_t) * slots);
         if (e != hipSuccess) return fail(EIK_ENOMEM, std::string("hipMalloc failed: ") + hipGetErrorString(e));
         w.ring_cap = need_ring;
         // fresh ring memory: the next reset must initialise it
@@ -396,11 +398,9 @@ Sched make_sched(const Bufs& w, const eik_opts* o) {
     s.ctr = w.ctr;
     s.tstate = w.tstate;
     s.cur = w.scal + kSCur;
-    s.pending = w.scal + kSPending;
     s.flags = (uint32_t*)(w.scal + kSFlags);
     s.poisoned = w.scal + kSPoisoned;
     s.counters = w.counters;
-    s.nrings = kRings;
     s.cap_mask = w.ring_cap - 1;
     double d = o ? o->delta : 0.0;
     s.inv_delta = (d > 0.0 && std::isfinite(d)) ? 1.0 / d : 0.0;
@@ -464,9 +464,9 @@ int forward_seq(const Bufs& b, const ProbTable& T, int64_t nsrc, int64_t ntiles,
     if (OP != EIK_OP_DBAR && s.max_visits == 0) s.max_visits = 256 * (long long)ntiles;
     int32_t* srccnt = b.scal + kSSrcCount;
 
-    hipLaunchKernelGGL(k_reset, dim3(blocks_for(std::max<int64_t>(ntiles, (int64_t)kRings * b.ring_cap), kThreads, 4096)),
+    hipLaunchKernelGGL(k_reset, dim3(blocks_for(std::max<int64_t>(ntiles, (int64_t)kRings * kShards * b.ring_cap), kThreads, 4096)),
                        dim3(kThreads), 0, st, s, b.tkey, (int)ntiles, srccnt,
-                       (long long)kRings * b.ring_cap, b.force_wipe);
+                       (long long)kRings * kShards * b.ring_cap, b.force_wipe);
     hipLaunchKernelGGL((k_src_mark<TX, TY, TZ>), dim3(blocks_for(nsrc, kThreads)), dim3(kThreads), 0, st,
                        T, src_idx, src_t0, (long long)nsrc, s, b.srclist, srccnt);
     if (warm)
@@ -489,40 +489,29 @@ int forward_seq(const Bufs& b, const ProbTable& T, int64_t nsrc, int64_t ntiles,
     a.tkey = b.tkey;
     a.work_ref = o ? o->work_ref : nullptr;
     a.rw = rw;
+    a.warm = warm ? 1 : 0;
     a.s = s;
-    // the two pass structures of k_solve: one thread per point (default) or
-    // compacted pass lists on 256-thread blocks (EIK_FLAG_PACKED, d-bar only)
-    constexpr int nt = solve_threads<TX, TY, TZ>();
-    constexpr int ntp = tile_threads<TX, TY, TZ>();
-    const bool count = a.work_ref != nullptr;
-    const bool pack = o && (o->flags & EIK_FLAG_PACKED);
+    // the monotone operators run one wave per tile; the ablation operators, which
+    // are not causal, evaluate every marked point once per pass
     const void* kern = nullptr;
-    int threads = nt;
+    int threads = 64 * SweepCfg<TX, TY, TZ>::W;
     if constexpr (OP == EIK_OP_DBAR) {
-        if (pack) {
-            threads = ntp;
-            kern = count ? (const void*)k_solve<TX, TY, TZ, ntp, OP, true, true>
-                         : (const void*)k_solve<TX, TY, TZ, ntp, OP, false, true>;
-        } else {
-            kern = count ? (const void*)k_solve<TX, TY, TZ, nt, OP, true>
-                         : (const void*)k_solve<TX, TY, TZ, nt, OP>;
-        }
+        kern = a.work_ref ? (const void*)k_sweep<TX, TY, TZ, OP, true> : (const void*)k_sweep<TX, TY, TZ, OP>;
     } else if constexpr (OP == 4) {
-        // the rectilinear operator holds both neighbours and weights of each
-        // axis: in 3D it does not fit the 128 registers of a 1024-thread
-        // block, so 3D tiles run on blocks of at most 512 threads with the
-        // register budget of two waves per SIMD
-        constexpr int ntr = (TZ > 1 && nt > 512) ? 512 : nt;
-        threads = ntr;
-        kern = (const void*)k_solve<TX, TY, TZ, ntr, OP>;
+        kern = (const void*)k_sweep<TX, TY, TZ, OP>;
     } else {
-        kern = (const void*)k_solve<TX, TY, TZ, nt, OP>;
+        static_assert(TZ == 1, "the ablation operators are two-dimensional");
+        threads = TX * TY;
+        kern = (const void*)k_ablate<TX, TY, OP>;
     }
     int grid = 0;
     if ((rc = occupancy_grid(kern, threads, &grid, cached))) return rc;
     if (o && o->grid_blocks > 0) grid = std::min(grid, o->grid_blocks);
     if ((int64_t)grid > ntiles) grid = (int)ntiles;
     if (grid < 1) grid = 1;
+    // few tiles: fewer waves a block, so that they spread over the compute units
+    if (OP == EIK_OP_DBAR || OP == 4)
+        threads = (int)std::min<int64_t>(threads, 64 * ((ntiles + grid - 1) / grid));
     if (tw && (rc = timing_begin(*tw, o))) return rc;
     void* kargs[] = {(void*)&a};
     HIP_TRY(hipLaunchKernel(kern, dim3(grid), dim3(threads), kargs, 0, st));
@@ -607,9 +596,9 @@ int adjoint(Workspace& w, const std::vector<Prob>& probs, int64_t ntiles, int64_
     Sched s = make_sched(bufs_of(w), o);
     s.max_visits = 0;
     unsigned long long* tref = w.counters + 4;
-    hipLaunchKernelGGL(k_reset, dim3(blocks_for(std::max<int64_t>(ntiles, (int64_t)kRings * w.ring_cap), kThreads, 4096)),
+    hipLaunchKernelGGL(k_reset, dim3(blocks_for(std::max<int64_t>(ntiles, (int64_t)kRings * kShards * w.ring_cap), kThreads, 4096)),
                        dim3(kThreads), 0, st, s, w.tkey, (int)ntiles, w.scal + kSSrcCount,
-                       (long long)kRings * w.ring_cap, 0);
+                       (long long)kRings * kShards * w.ring_cap, 0);
     // mu := NaN (not done): a tile that has not run yet reads as not done
     hipLaunchKernelGGL(k_fill_nan, dim3(blocks_for(npts, kThreads, 8192)), dim3(kThreads), 0, st, (long long)npts, mu);
     hipLaunchKernelGGL((k_adj_prep<TX, TY, TZ>), dim3((unsigned)std::min<int64_t>(ntiles, 65536)), dim3(kThreads),
@@ -751,7 +740,7 @@ constexpr int64_t kNaMaxSrc = 1 << 16;
 constexpr size_t na_round(size_t x) { return (x + 255) / 256 * 256; }
 constexpr size_t kNaItems = 0;
 constexpr size_t kNaCtr = kNaItems + na_round(sizeof(uint64_t) * kRings * kNaMaxTiles);
-constexpr size_t kNaTstate = kNaCtr + na_round(sizeof(uint32_t) * kRings * kCtrStride);
+constexpr size_t kNaTstate = kNaCtr + na_round(sizeof(uint32_t) * kCtrWords);
 constexpr size_t kNaTkey = kNaTstate + na_round(sizeof(uint32_t) * kNaMaxTiles);
 constexpr size_t kNaTmin = kNaTkey + na_round(sizeof(uint64_t) * kNaMaxTiles);
 constexpr size_t kNaScal = kNaTmin + na_round(sizeof(uint64_t) * kNaMaxTiles);
@@ -811,7 +800,7 @@ Bufs na_bufs(const NaDevice& d, hipStream_t st) {
     b.counters = (unsigned long long*)(d.ptr + kNaCounters);
     b.srclist = (int32_t*)(d.ptr + kNaSrclist);
     b.timeline = nullptr;
-    b.ring_cap = (uint32_t)kNaMaxTiles;
+    b.ring_cap = (uint32_t)(kNaMaxTiles / kShards);
     // the first call on a device initialises the rings (their memory has
     // never been written by this library); later calls find them drained
     b.force_wipe = d.wiped ? 0 : 1;

@@ -1,16 +1,6 @@
-// Forward kernels: per-solve reset, source placement, the persistent
-// soft-priority tile solver, finalisation and the upwind-parent record.
-//
-// The persistent solver realises the paper's asynchronous marching method
-// (Algorithm "Asynchronous Marching Method") with a tile of the grid as the unit
-// of work: a workgroup claims the approximately earliest active tile, stages
-// its times, the 1-cell halo and the per-point constants in LDS, applies the
-// update operator (Algorithm "Eikonal Update Operator" with the exactly monotone
-// rounding) to dirty points until nothing in the tile changes, writes the
-// lowered points back and activates the face neighbours whose halo changed with
-// the priority floor(t / delta).  Theorem 1 (monotone + causal => one fixed
-// point for every order) is what makes the racing, out-of-order schedule
-// produce the same bits as sequential fast marching.
+// Forward kernels: per-solve reset, source placement, finalisation, the
+// upwind-parent record, the residual and the ablation solver; the solver itself
+// is in eik_sweep.hpp.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -50,6 +40,7 @@ struct SolveArgs {
     // rectilinear grids (OP 4): reciprocal spacings per axis and index, laid
     // out [wm_x (nx), wp_x (nx), wm_y (ny), wp_y (ny), wm_z (nz), wp_z (nz)]
     const double* rw;
+    int warm;                // t holds a caller's upper bound (warm start)
     Sched s;
 };
 
@@ -112,7 +103,7 @@ __global__ void k_reset(Sched s, uint64_t* tkey, int ntiles, int32_t* srclist_co
         const long long cap = (long long)s.cap_mask + 1;
         for (long long i = i0; i < ring_words; i += stride) s.items[i] = (uint64_t)(i % cap) << 32;
         // head = tail = 0; count word = bias (0 queued, 0 running)
-        for (long long i = i0; i < (long long)s.nrings * kCtrStride; i += stride)
+        for (long long i = i0; i < (long long)kPendWord; i += stride)
             s.ctr[i] = (i % kCtrStride) == kCrWord ? (uint32_t)kCountBias : 0u;
     }
     if (i0 == 0) {
@@ -121,7 +112,7 @@ __global__ void k_reset(Sched s, uint64_t* tkey, int ntiles, int32_t* srclist_co
             s.timeline[1] = 0ull;
         }
         *s.cur = 0;
-        *s.pending = 0;
+        for (int i = 0; i < kShards; ++i) *pend_word(s, i) = 0ull;
         *s.flags = 0u;
         for (int i = 0; i < kCounters; ++i) s.counters[i] = 0ull;
         *srclist_count = 0;
@@ -268,7 +259,7 @@ __global__ void k_warm_push(ProbTable T, int ntiles, const uint64_t* tile_min, S
 }
 
 // ---------------------------------------------------------------------------
-// the persistent solver
+// tiles in LDS, and the ablation solver
 // ---------------------------------------------------------------------------
 
 template <int TX, int TY, int TZ, int NT>
@@ -305,6 +296,23 @@ __device__ __forceinline__ double wave_min(double v) {
     return v;
 }
 
+// Adds a worker's statistics to the launch's: [0..3] phase times, [4] visits,
+// [5] point updates, [6] passes, [7] hand-offs.  Single lane.
+__device__ __forceinline__ void flush_stats(const Sched& S, const unsigned long long* st) {
+    auto add = [&](int i, unsigned long long v) {
+        __hip_atomic_fetch_add(S.counters + i, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    };
+    for (int i = 0; i < 4; ++i) add(5 + i, st[i]);
+    add(10, 1ull);
+    add(12, st[7]);
+    add(0, st[4]);
+    add(1, st[5]);
+    add(2, st[6]);
+    if (S.timeline)
+        __hip_atomic_fetch_max(S.timeline + 1, (unsigned long long)wall_clock64(), __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_AGENT);
+}
+
 // Dirty flags of the in-tile relaxation: one byte per point, stored so that
 // the NPT points of one thread (p = tid + j * NT) are adjacent and one LDS
 // access reads or clears all of them.
@@ -325,80 +333,55 @@ __device__ __forceinline__ void st_flags(uint8_t* f, uint32_t v) {
     else *f = (uint8_t)v;
 }
 
-// OP selects the operator: 0 the exact monotone d-bar (the solver), 1 d-hat,
-// 2 d-tilde (two-dimensional precision ablation only; see apply_op).
-// COUNT adds the work classification (A.work_ref must then be set).
-// Registers are capped for three waves per SIMD with blocks of up to 256
-// threads (three blocks per compute unit) and four with larger blocks (two
-// 512-thread blocks or one 1024-thread block per compute unit).  Compacted
-// passes on 3D tiles also take four (four 256-thread blocks per compute unit
-// keep more tiles in flight).  The rectilinear operator on 3D tiles takes four
-// with one point a thread and two with two points a thread on 512 threads
-// (16x8x8 and larger), where it would spill.  The per-workgroup statistics
-// sit in LDS, not in registers, so that these budgets hold without spills.
-template <int TX, int TY, int TZ, int NT, int OP = 0, bool COUNT = false, bool PACK = false>
-__global__ void __launch_bounds__(NT)
-    __attribute__((amdgpu_waves_per_eu(OP == 4 && TZ > 1 && NT == 512 && TX * TY * TZ > NT ? 2 : ((NT > 256 || (PACK && TZ > 1)) ? 4 : 3)))) k_solve(SolveArgs A) {
-    using C = TileCfg<TX, TY, TZ, NT>;
-    constexpr int NPT = C::NPT;
-    static_assert(NPT == 1 || NPT == 2 || NPT == 4, "1, 2 or 4 points per thread");
-    constexpr uint32_t kAllDirty = NPT == 4 ? 0x01010101u : (NPT == 2 ? 0x0101u : 0x01u);
+// The precision ablation (two-dimensional grids): the same schedule with the
+// explicit operators OP 1..3 of apply_op.  They assign their value, which may
+// rise, and are not causal, so every neighbour of a changed point is marked
+// (with A.s.track on any change, else on a drop) and evaluated once per pass,
+// all of them at once: one thread per point, one workgroup per tile.  The
+// marks of a pass go to the other of two flag buffers, so one barrier per pass
+// orders them before the next pass's reads.
+template <int TX, int TY, int OP>
+__global__ void __launch_bounds__(TX * TY) k_ablate(SolveArgs A) {
+    constexpr int NT = TX * TY;
+    using C = TileCfg<TX, TY, 1, NT>;
     __shared__ double sT[C::NLDS];
-    __shared__ double sQ[PACK ? C::NP : 1];        // constants (PACK: any thread may relax a point)
-    __shared__ double sTin[PACK ? C::NP : 1];      // PACK: the values staged (not held in registers
-                                                   // through the passes)
-    __shared__ uint16_t sList[PACK ? C::NP : 1];   // PACK: the pass's dirty points, compacted
-    __shared__ int s_cnt[2];                       // PACK: list lengths
-    // dirty flags, two buffers (read in one pass, marked for the next); the
-    // NT bytes past the NP flags are per-thread sinks that let the marking
-    // store without branching
-    __shared__ __align__(4) uint8_t sDirty[2][C::NP + NT];
+    __shared__ uint8_t sDirty[2][NT + 4];
     __shared__ int s_more[3];  // per pass (mod 3): some wave marked a point
-    // rectilinear grids: the tile's reciprocal spacings, [wm_x | wp_x | wm_y |
-    // wp_y | wm_z | wp_z] over its TX, TY, TZ coordinates
-    __shared__ double sW[OP == 4 ? 2 * (TX + TY + TZ) : 1];
-    __shared__ int s_tile;
-    __shared__ int64_t s_bucket;
-    __shared__ uint32_t s_state;
-    __shared__ uint32_t s_nb[6];
-    __shared__ uint32_t s_nid[6];
+    __shared__ int s_tile, s_next;
+    __shared__ int64_t s_slot;
+    __shared__ uint32_t s_state, s_nb[6], s_nid[6];
     __shared__ unsigned long long s_face[6];
     __shared__ unsigned int s_upd;
-    __shared__ unsigned long long s_pend;  // smallest value left beyond the bucket (bits)
-    __shared__ int s_next;  // tile handed on by the previous run's publish, or -1
-    // per-workgroup statistics, kept by thread 0 in LDS (not in registers
-    // through the passes) and flushed once at exit: [0..3] phase times on the
-    // 100 MHz wall clock (claim, stage, relax, write + publish), [4] visits,
-    // [5] point updates, [6] passes, [7] hand-offs, [8] the last phase mark
+    // per-workgroup statistics: [0..3] phase times on the 100 MHz wall clock
+    // (claim, stage, relax, write + publish), [4] visits, [5] point updates,
+    // [6] passes, [7] hand-offs, [8] the last phase mark
     __shared__ unsigned long long s_stat[9];
 
-    const int tid = threadIdx.x;
-    const int lane = tid & 63;
-    const unsigned long long lanes_below = (1ull << lane) - 1ull;
-    (void)lanes_below;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int lx = tid % TX, ly = tid / TX, L = C::lds(lx, ly, 0);
     const Sched& S = A.s;
-    // per-wave work classification (with A.work_ref): operator evaluations,
-    // those that lowered the value, those that set the final value
-    unsigned long long w_eval = 0, w_imp = 0, w_good = 0;
     if (tid == 0) {
         s_next = -1;
-        s_bucket = 0;
+        s_slot = 0;
         for (int i = 0; i < 8; ++i) s_stat[i] = 0;
         s_stat[8] = wall_clock64();
     }
-
+    auto phase = [&](int i) {
+        const unsigned long long now = wall_clock64();
+        s_stat[i] += now - s_stat[8];
+        s_stat[8] = now;
+    };
     int32_t cur_hint = 0;  // wave 0: the window's lowest bucket as last seen
     for (;;) {
-        // ---- claim (or take the tile handed on) ----------------------------
         if (tid < 64) {
-            int64_t bucket = s_bucket;
+            int64_t slot = s_slot;
             int tile = s_next;
-            if (tile < 0) tile = claim(S, &bucket, cur_hint);
+            if (tile < 0) tile = claim(S, &slot, cur_hint);
             else if (tid == 0) ++s_stat[7];
             if (tid == 0) {
                 s_next = -1;
                 s_tile = tile;
-                s_bucket = bucket;
+                s_slot = slot;
                 if (tile >= 0) {
                     // Q -> R; every load of this run is issued after it returned
                     uint32_t st = __hip_atomic_fetch_xor(S.tstate + tile, kQ | kR, __ATOMIC_RELAXED,
@@ -422,584 +405,142 @@ __global__ void __launch_bounds__(NT)
         const uint32_t st = s_state;
         const Prob P = prob_of_tile(A.pt, tile);
         const int tl = tile - P.tile_off;
-        const int tx = tl % P.ntx, ty = (tl / P.ntx) % P.nty, tz = tl / (P.ntx * P.nty);
-        const int x0 = tx * TX, y0 = ty * TY, z0 = tz * TZ;
+        const int tx = tl % P.ntx, ty = tl / P.ntx;
+        const int x0 = tx * TX, y0 = ty * TY;
         if (tid == 0) {
             ++s_stat[4];
-            const unsigned long long now = wall_clock64();
-            s_stat[0] += now - s_stat[8];
-            s_stat[8] = now;
+            phase(0);
         }
-
         if (st & 0x80000000u) {  // visit cap reached: drop the tile
-            if (tid == 0) drop_run(S, (uint32_t)tile, s_bucket);
+            if (tid == 0) drop_run(S, (uint32_t)tile, s_slot);
             __syncthreads();
             continue;
         }
         const bool visited = (st & kV) != 0;
-
-        // face neighbours x-, x+, y-, y+, z-, z+ (bit 30: the tile exists)
+        // face neighbours x-, x+, y-, y+ (bit 30: the tile exists)
         if (tid < 6) {
-            int d = tid >> 1, side = tid & 1;
-            int nt[3] = {tx, ty, tz};
-            int lim[3] = {P.ntx, P.nty, P.ntz};
-            nt[d] += side ? 1 : -1;
-            uint32_t w = 0, nid = 0;
-            if (nt[d] >= 0 && nt[d] < lim[d]) {
-                nid = (uint32_t)(P.tile_off + (nt[2] * P.nty + nt[1]) * P.ntx + nt[0]);
-                w = 0x40000000u;
-            }
-            s_nb[tid] = w;
-            s_nid[tid] = nid;
+            const int d = tid >> 1, step = (tid & 1) ? 1 : -1;
+            const int nx = tx + (d == 0 ? step : 0), ny = ty + (d == 1 ? step : 0);
+            const bool has = d < 2 && nx >= 0 && nx < P.ntx && ny >= 0 && ny < P.nty;
+            s_nb[tid] = has ? 0x40000000u : 0u;
+            s_nid[tid] = has ? (uint32_t)(P.tile_off + ny * P.ntx + nx) : 0u;
             s_face[tid] = kInfBits;
         }
         if (tid == 0) {
             s_upd = 0u;
-            s_pend = kInfBits;
             s_more[1] = 0;
             s_more[2] = 0;
-            s_cnt[0] = 0;
-            s_cnt[1] = 0;
         }
-        // Optional bucket horizon (k = S.horizon > 0): a run settles only
-        // values with floor(r / delta) < b + k, b its bucket (with k = 1 the
-        // bucket discipline of delta-stepping).  A lower value never depends on
-        // a higher one (the operator is causal), so nothing below the horizon
-        // is lost; larger candidates are left for a later run of this tile,
-        // keyed by the smallest of them, instead of being written and
-        // propagated now as provisional values.
-        const double hz = (double)(s_bucket + S.horizon);
-
-        // ---- stage the tile and its halo in LDS ----------------------------
-        // t starts at +inf everywhere, so every in-grid value read here is a
-        // valid upper bound.  Every load of the stage (field and t of the
-        // thread's points, its halo cells) is issued before any is used, so the
-        // stage costs one memory round trip rather than one per load.
-        double t_in[NPT];   // the values staged (what the run started from)
-        double t_own[NPT];  // the thread's points' current values
-        double q_own[NPT];  // and their constants (0: not relaxed)
-        if constexpr (OP == 4) {
-            // the weights of the tile's coordinates (clamped past the grid's
-            // end, where no point is relaxed); read-only, ordered for the
-            // relaxation by the barrier that ends the stage
-            constexpr int NW = 2 * (TX + TY + TZ);
-            for (int w = tid; w < NW; w += NT) {
-                int k = w, axis = 0;
-                if (k >= 2 * TX) {
-                    k -= 2 * TX;
-                    axis = 1;
-                    if (k >= 2 * TY) {
-                        k -= 2 * TY;
-                        axis = 2;
-                    }
-                }
-                const int n = axis == 0 ? TX : (axis == 1 ? TY : TZ);
-                const int side = k >= n ? 1 : 0;
-                const int i = k - side * n;
-                const int g0 = axis == 0 ? x0 : (axis == 1 ? y0 : z0);
-                const int gn = axis == 0 ? P.nx : (axis == 1 ? P.ny : P.nz);
-                const int base = axis == 0 ? 0 : (axis == 1 ? 2 * P.nx : 2 * (P.nx + P.ny));
-                sW[w] = A.rw[base + side * gn + min(g0 + i, gn - 1)];
-            }
+        // ---- stage the tile and its halo -----------------------------------
+        const int x = x0 + lx, y = y0 + ly;
+        const bool in = x < P.nx && y < P.ny;
+        const int64_t gi = P.pt_off + (int64_t)y * P.nx + x;
+        double q = 0.0, t_in = inf64();
+        if (in) {
+            bool ok;
+            q = field_q(A.field[gi], P.h, P.kind, ok);
+            t_in = as_f64(__hip_atomic_load((const uint64_t*)(A.t + gi), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+            if (!ok) set_flag(S, kFlagDomain);
+            if (!ok || signbit(t_in)) q = 0.0;  // a source is fixed
+            t_in = fabs(t_in);
         }
-        uint32_t live = 0;  // bit j: point j is in the grid and not a source
-        {
-            constexpr int NXF = 2 * TY * TZ, NYF = 2 * TX * TZ, NZF = C::D3 ? 2 * TX * TY : 0;
-            constexpr int NH = NXF + NYF + NZF;
-            constexpr int HPT = (NH + NT - 1) / NT;  // halo cells per thread
-            double fv[NPT], tv[NPT], hv[HPT];
-            int hl[HPT];
-            uint32_t inb = 0;
-#pragma unroll
-            for (int j = 0; j < NPT; ++j) {
-                const int p = tid + j * NT;
-                const int lx = p % TX, ly = (p / TX) % TY, lz = p / (TX * TY);
-                const int x = x0 + lx, y = y0 + ly, z = z0 + lz;
-                fv[j] = 0.0;
-                tv[j] = inf64();
-                if (x < P.nx && y < P.ny && z < P.nz) {
-                    const int64_t gi = P.pt_off + ((int64_t)z * P.ny + y) * P.nx + x;
-                    fv[j] = A.field[gi];
-                    tv[j] = as_f64(__hip_atomic_load((const uint64_t*)(A.t + gi), __ATOMIC_RELAXED,
-                                                     __HIP_MEMORY_SCOPE_AGENT));
-                    inb |= 1u << j;
-                }
-            }
-#pragma unroll
-            for (int k = 0; k < HPT; ++k) {
-                const int i = tid + k * NT;
-                hl[k] = -1;
-                hv[k] = inf64();
-                if (i < NH) {
-                    int lx, ly, lz;
-                    if (i < NXF) {
-                        int side = i / (TY * TZ), r = i % (TY * TZ);
-                        ly = r % TY; lz = r / TY; lx = side ? TX : -1;
-                    } else if (i < NXF + NYF) {
-                        int k2 = i - NXF, side = k2 / (TX * TZ), r = k2 % (TX * TZ);
-                        lx = r % TX; lz = r / TX; ly = side ? TY : -1;
-                    } else {
-                        int k2 = i - NXF - NYF, side = k2 / (TX * TY), r = k2 % (TX * TY);
-                        lx = r % TX; ly = r / TX; lz = side ? TZ : -1;
-                    }
-                    hl[k] = C::lds(lx, ly, lz);
-                    const int x = x0 + lx, y = y0 + ly, z = z0 + lz;
-                    // the sign (a source) is dropped after all loads are out:
-                    // an operation on the loaded value inside this branch
-                    // would wait for it here
-                    if (x >= 0 && x < P.nx && y >= 0 && y < P.ny && z >= 0 && z < P.nz)
-                        hv[k] = as_f64(__hip_atomic_load((const uint64_t*)(A.t + P.pt_off +
-                                                                           ((int64_t)z * P.ny + y) * P.nx + x),
-                                                         __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-                }
-            }
-#pragma unroll
-            for (int j = 0; j < NPT; ++j) {
-                const int p = tid + j * NT;
-                const int lx = p % TX, ly = (p / TX) % TY, lz = p / (TX * TY);
-                double tvj = tv[j], q = 0.0;
-                if ((inb >> j) & 1u) {
-                    bool ok;
-                    q = field_q(fv[j], P.h, P.kind, ok);
-                    if (!ok) {
-                        set_flag(S, kFlagDomain);
-                        q = 0.0;
-                    }
-                    if (signbit(tvj)) {  // a source: fixed
-                        tvj = fabs(tvj);
-                        q = 0.0;
-                    }
-                }
-                if (q > 0.0) live |= 1u << j;
-                sT[C::lds(lx, ly, lz)] = tvj;
-                q_own[j] = q;
-                if constexpr (PACK) {
-                    sQ[p] = q;
-                    sTin[p] = tvj;
-                }
-                t_in[j] = tvj;
-                t_own[j] = tvj;
-            }
-#pragma unroll
-            for (int k = 0; k < HPT; ++k)
-                if (hl[k] >= 0) sT[hl[k]] = fabs(hv[k]);
-        }
-        st_flags<NPT>(sDirty[1] + tid * NPT, 0u);
-        __syncthreads();
-        // First pass: every point on a first run, in a tile holding a source
-        // (placed before its first run, which already counts as visited) and
-        // with a horizon (points left beyond it last time); otherwise the
-        // interior is still at the fixed point its last run left given the old
-        // halo, so only boundary points next to a halo value below their own
-        // can improve.
-        {
-            uint32_t seed = 0;
-            if (!visited || (st & kS) || S.horizon > 0) {
-                seed = kAllDirty;
+        sT[L] = t_in;
+        for (int i = tid; i < 2 * (TX + TY); i += NT) {
+            int hx, hy;
+            if (i < 2 * TY) {
+                hx = i / TY ? TX : -1;
+                hy = i % TY;
             } else {
+                hx = (i - 2 * TY) % TX;
+                hy = (i - 2 * TY) / TX ? TY : -1;
+            }
+            const int X = x0 + hx, Y = y0 + hy;
+            const bool hin = X >= 0 && X < P.nx && Y >= 0 && Y < P.ny;
+            sT[C::lds(hx, hy, 0)] = hin ? hload(A.t + P.pt_off + (int64_t)Y * P.nx + X) : inf64();
+        }
+        sDirty[0][tid] = 0;
+        sDirty[1][tid] = 0;
+        __syncthreads();
+        // first pass: every point on a first run and in a tile holding a source;
+        // otherwise boundary points next to a halo value below their own
+        bool dirty = !visited || (st & kS) || S.horizon > 0;
+        if (!dirty)
+            dirty = (lx == 0 && sT[L - 1] < t_in) || (lx == TX - 1 && sT[L + 1] < t_in) ||
+                    (ly == 0 && sT[L - C::SY] < t_in) || (ly == TY - 1 && sT[L + C::SY] < t_in);
+        if (tid == 0) phase(1);
+        // ---- relax until the tile is quiet ---------------------------------
+        int cb = 0, passes = 0;
+        double v = t_in;
+        for (;;) {
+            if (tid == 0) s_more[(passes + 1) % 3] = 0;  // written next pass; last read two barriers ago
+            bool marked = false;
+            if (dirty && q > 0.0) {
+                const double ax = nmin(sT[L - 1], sT[L + 1]), ay = nmin(sT[L - C::SY], sT[L + C::SY]);
+                const double r = apply_op<OP>(ax, ay, inf64(), q);
+                const bool ch = r != v && r == r;
+                marked = S.track ? ch : (ch && r < v);
+                if (ch) {
+                    v = r;
+                    sT[L] = r;
+                }
+                if (marked) {
+                    uint8_t* nd = sDirty[cb ^ 1];
+                    if (lx > 0) nd[tid - 1] = 1;
+                    if (lx < TX - 1) nd[tid + 1] = 1;
+                    if (ly > 0) nd[tid - TX] = 1;
+                    if (ly < TY - 1) nd[tid + TX] = 1;
+                }
+            }
+            if (__ballot(marked) && lane == 0) s_more[passes % 3] = 1;
+            __syncthreads();
+            const int more = s_more[passes % 3];
+            ++passes;
+            if (!more) break;
+            cb ^= 1;
+            dirty = sDirty[cb][tid] != 0;
+            sDirty[cb][tid] = 0;
+            if (passes >= (1 << 16)) {  // these operators need not settle
+                if (tid == 0) set_flag(S, kFlagLimit);
+                break;
+            }
+        }
+        if (tid == 0) phase(2);
+        // ---- write back changed points, gather the faces' minima -----------
+        // every lowered face value counts (not causal), a raised one with tracking
+        const bool chg = in && v != t_in;
+        const bool act = chg && (v < t_in || S.track);
+        if (chg) tstore(A.t + gi, v);
+        const bool on[4] = {lx == 0, lx == TX - 1, ly == 0, ly == TY - 1};
 #pragma unroll
-                for (int j = 0; j < NPT; ++j) {
-                    const int p = tid + j * NT;
-                    const int lx = p % TX, ly = (p / TX) % TY, lz = p / (TX * TY);
-                    const int L = C::lds(lx, ly, lz);
-                    // the point and its six neighbours, read together
-                    const double c = sT[L];
-                    const double nxm = sT[L - 1], nxp = sT[L + 1], nym = sT[L - C::SY], nyp = sT[L + C::SY];
-                    const double nzm = C::D3 ? sT[L - C::SZ] : inf64(), nzp = C::D3 ? sT[L + C::SZ] : inf64();
-                    // smallest halo value next to the point (interior cells
-                    // do not count: they have not changed since the last run)
-                    double hm = inf64();
-                    if (lx == 0 && nxm < hm) hm = nxm;
-                    if (lx == TX - 1 && nxp < hm) hm = nxp;
-                    if (ly == 0 && nym < hm) hm = nym;
-                    if (ly == TY - 1 && nyp < hm) hm = nyp;
-                    if (C::D3) {
-                        if (lz == 0 && nzm < hm) hm = nzm;
-                        if (lz == TZ - 1 && nzp < hm) hm = nzp;
-                    }
-                    if (hm < c) seed |= 1u << (8 * j);
-                }
-            }
-            st_flags<NPT>(sDirty[0] + tid * NPT, seed);
-        }
-        if (tid == 0) {
-            const unsigned long long now = wall_clock64();
-            s_stat[1] += now - s_stat[8];
-            s_stat[8] = now;
-        }
-
-        // ---- relax until the tile is quiet --------------------------------
-        // Two pass structures, same result (any order of monotone updates
-        // reaches the same fixed point): PACK compacts each pass's dirty points
-        // into a dense list first (fewest operator evaluations per wave: more
-        // throughput when the device is full of work, as in a batch of shots);
-        // otherwise each thread relaxes its own point (one barrier per pass:
-        // lower latency when the front holds few tiles, as in a single solve).
-        int cb = 0;
-        int passes = 0;
-        double pend = inf64();
-        if constexpr (PACK) {
-            // Each pass first compacts the dirty points into a dense list (every
-            // thread reads its points' flags with one LDS access; per-point ballots
-            // give each point its place in the wave's segment, one LDS atomic per
-            // wave reserves the segment), then applies the operator to the list,
-            // so the waves run the operator only as many times as there are dirty
-            // points, not once per owned point.  A point whose value drops marks
-            // its in-tile neighbours above the new value dirty for the next pass;
-            // values read within a pass may already be newer (any order of
-            // monotone updates is valid).
-            for (;;) {
-                {
-                    uint8_t* df = sDirty[cb] + tid * NPT;
-                    const uint32_t fl = ld_flags<NPT>(df);
-                    if (fl) st_flags<NPT>(df, 0u);
-                    uint32_t m = 0;
-    #pragma unroll
-                    for (int j = 0; j < NPT; ++j) m |= ((fl >> (8 * j)) & 1u) << j;
-                    m &= live;
-                    unsigned long long B[NPT];
-                    int tot = 0;
-    #pragma unroll
-                    for (int j = 0; j < NPT; ++j) {
-                        B[j] = __ballot((m >> j) & 1u);
-                        tot += __popcll(B[j]);
-                    }
-                    if (tot) {
-                        int base = 0;
-                        if (lane == 0) base = atomicAdd(&s_cnt[cb], tot);
-                        base = __shfl(base, 0);
-    #pragma unroll
-                        for (int j = 0; j < NPT; ++j) {
-                            if ((m >> j) & 1u) sList[base + __popcll(B[j] & lanes_below)] = (uint16_t)(tid + j * NT);
-                            base += __popcll(B[j]);
-                        }
-                    }
-                }
-                __syncthreads();
-                const int n = s_cnt[cb];
-                if (n == 0) break;
-                // the other counter was last read before the previous barrier and is
-                // next filled after the coming one
-                if (tid == 0) s_cnt[cb ^ 1] = 0;
-                for (int i = tid; i < n; i += NT) {
-                    const int p = sList[i];
-                    const double q = sQ[p];
-                    const int lx = p % TX, ly = (p / TX) % TY, lz = p / (TX * TY);
-                    const int L = C::lds(lx, ly, lz);
-                    const double tc = sT[L];
-                    const double ax = nmin(sT[L - 1], sT[L + 1]);
-                    const double ay = nmin(sT[L - C::SY], sT[L + C::SY]);
-                    const double az = C::D3 ? nmin(sT[L - C::SZ], sT[L + C::SZ]) : inf64();
-                    bool ch, mark;
-                    double r;
-                    if constexpr (OP == 0) {
-                        r = update<C::D3>(ax, ay, az, q, q * q, tc, ch);
-                        // held back: its bucket lies at or beyond the horizon (a
-                        // value whose bucket index overflows the range is settled
-                        // at once, so the requeue can never repeat forever)
-                        const double rb = r * S.inv_delta;
-                        if (S.horizon > 0 && ch && rb >= hz && rb < 1.0e15) {
-                            pend = fmin(pend, r);
-                            ch = false;
-                        }
-                        mark = ch;
-                    } else {
-                        // the ablation operators assign (their value may rise) and
-                        // re-activate on a drop, or on any change when tracking
-                        r = apply_op<OP>(ax, ay, az, q);
-                        ch = r != tc && r == r;
-                        mark = S.track ? ch : (ch && r < tc);
-                    }
-                    if constexpr (COUNT) {
-                        bool good = false;
-                        if (ch) {
-                            const int gx = x0 + lx, gy = y0 + ly, gz = z0 + lz;
-                            good = r == A.work_ref[P.pt_off + ((int64_t)gz * P.ny + gy) * P.nx + gx];
-                        }
-                        w_eval += __popcll(__ballot(true));
-                        w_imp += __popcll(__ballot(ch));
-                        w_good += __popcll(__ballot(good));
-                    }
-                    if (ch) sT[L] = r;
-                    if (mark) {
-                        // with d-bar only neighbours above the new value can depend
-                        // on it (the operator is causal), so only they need another
-                        // look; the ablation operators mark every neighbour.  Six
-                        // unconditional stores, unwanted ones into this thread's
-                        // sink byte (no divergent branches).
-                        constexpr bool kAll = OP != 0;
-                        uint8_t* nd = sDirty[cb ^ 1];
-                        const int sink = C::NP + tid;
-                        nd[(lx > 0 && (kAll || sT[L - 1] > r)) ? didx<NT, NPT>(p - 1) : sink] = 1;
-                        nd[(lx < TX - 1 && (kAll || sT[L + 1] > r)) ? didx<NT, NPT>(p + 1) : sink] = 1;
-                        nd[(ly > 0 && (kAll || sT[L - C::SY] > r)) ? didx<NT, NPT>(p - TX) : sink] = 1;
-                        nd[(ly < TY - 1 && (kAll || sT[L + C::SY] > r)) ? didx<NT, NPT>(p + TX) : sink] = 1;
-                        if (C::D3) {
-                            nd[(lz > 0 && (kAll || sT[L - C::SZ] > r)) ? didx<NT, NPT>(p - TX * TY) : sink] = 1;
-                            nd[(lz < TZ - 1 && (kAll || sT[L + C::SZ] > r)) ? didx<NT, NPT>(p + TX * TY) : sink] = 1;
-                        }
-                    }
-                }
-                ++passes;
-                __syncthreads();
-                cb ^= 1;
-                if (OP != 0 && OP != 4 && passes >= (1 << 16)) {  // an ablation operator may not settle
-                    if (tid == 0) set_flag(S, kFlagLimit);
-                    break;
-                }
-                if (passes > (1 << 20)) {
-                    if (tid == 0) set_flag(S, kFlagWatchdog);
-                    break;
-                }
-            }
-        } else {
-            // Every thread relaxes its own points (p = tid + j * NT), whose time
-            // and constant it keeps in registers; only the neighbours come from
-            // LDS.  A pass evaluates each dirty point once and marks the in-tile
-            // neighbours that may now improve in the other flag buffer, so the
-            // pass's reads (buffer cb) and marks (buffer cb ^ 1) never touch the
-            // same bytes, and ONE barrier per pass suffices: it orders this pass's
-            // marks before the next pass's reads.  A flag byte of slot s_more says
-            // whether any wave marked anything; if none did, every flag is clear
-            // and the tile is quiet.  Values read within a pass may already be
-            // newer (any order of monotone updates is valid, Theorem 1).
-            uint32_t dirty = 0;  // bit j: point j is to be evaluated in this pass
-            {
-                const uint32_t fl = ld_flags<NPT>(sDirty[0] + tid * NPT);
-    #pragma unroll
-                for (int j = 0; j < NPT; ++j) dirty |= ((fl >> (8 * j)) & 1u) << j;
-                st_flags<NPT>(sDirty[0] + tid * NPT, 0u);
-                dirty &= live;
-            }
-            for (;;) {
-                if (tid == 0) s_more[(passes + 1) % 3] = 0;  // written next pass; last read two barriers ago
-                bool marked = false;
-                uint8_t* nd = sDirty[cb ^ 1];
-                const int sink = C::NP + tid;
-    #pragma unroll
-                for (int j = 0; j < NPT; ++j) {
-                    if (!__ballot((dirty >> j) & 1u)) continue;
-                    bool ch = false, good = false;  // for the work classification
-                    if ((dirty >> j) & 1u) {
-                        const int p = tid + j * NT;
-                        const int lx = p % TX, ly = (p / TX) % TY, lz = p / (TX * TY);
-                        const int L = C::lds(lx, ly, lz);
-                        const double q = q_own[j];
-                        const double tc = t_own[j];
-                        const double nxm = sT[L - 1], nxp = sT[L + 1], nym = sT[L - C::SY], nyp = sT[L + C::SY];
-                        const double nzm = C::D3 ? sT[L - C::SZ] : inf64(), nzp = C::D3 ? sT[L + C::SZ] : inf64();
-                        const double ax = nmin(nxm, nxp), ay = nmin(nym, nyp), az = nmin(nzm, nzp);
-                        bool mark;
-                        double r;
-                        if constexpr (OP == 0 || OP == 4) {
-                            if constexpr (OP == 0) {
-                                r = update<C::D3>(ax, ay, az, q, q * q, tc, ch);
-                            } else {
-                                const double nb6[6] = {nxm, nxp, nym, nyp, nzm, nzp};
-                                const double w6[6] = {sW[lx], sW[TX + lx], sW[2 * TX + ly], sW[2 * TX + TY + ly],
-                                                      C::D3 ? sW[2 * (TX + TY) + lz] : 1.0,
-                                                      C::D3 ? sW[2 * (TX + TY) + TZ + lz] : 1.0};
-                                r = update_rect<C::D3>(nb6, w6, q * q, tc, ch);
-                            }
-                            // held back: its bucket lies at or beyond the horizon (a
-                            // value whose bucket index overflows the range is settled
-                            // at once, so the requeue can never repeat forever)
-                            const double rb = r * S.inv_delta;
-                            if (S.horizon > 0 && ch && rb >= hz && rb < 1.0e15) {
-                                pend = fmin(pend, r);
-                                ch = false;
-                            }
-                            mark = ch;
-                        } else {
-                            // the ablation operators assign (their value may rise) and
-                            // re-activate on a drop, or on any change when tracking
-                            r = apply_op<OP>(ax, ay, az, q);
-                            ch = r != tc && r == r;
-                            mark = S.track ? ch : (ch && r < tc);
-                        }
-                        if constexpr (COUNT) {
-                            if (ch) {
-                                const int gx = x0 + lx, gy = y0 + ly, gz = z0 + lz;
-                                good = r == A.work_ref[P.pt_off + ((int64_t)gz * P.ny + gy) * P.nx + gx];
-                            }
-                        }
-                        if (ch) {
-                            t_own[j] = r;
-                            sT[L] = r;
-                        }
-                        if (mark) {
-                            // with d-bar only neighbours above the new value can depend
-                            // on it (the operator is causal); the values loaded above
-                            // can only have dropped since, so a neighbour loaded at or
-                            // below r needs no look.  The ablation operators mark every
-                            // neighbour.  Six unconditional stores, unwanted ones into
-                            // this thread's sink byte (no divergent branches).
-                            // (the targets fold the tile's edge into the sink, so a
-                            // mark is one compare and one select)
-                            constexpr bool kAll = OP != 0 && OP != 4;
-                            const int txm = lx > 0 ? didx<NT, NPT>(p - 1) : sink;
-                            const int txp = lx < TX - 1 ? didx<NT, NPT>(p + 1) : sink;
-                            const int tym = ly > 0 ? didx<NT, NPT>(p - TX) : sink;
-                            const int typ = ly < TY - 1 ? didx<NT, NPT>(p + TX) : sink;
-                            nd[(kAll || nxm > r) ? txm : sink] = 1;
-                            nd[(kAll || nxp > r) ? txp : sink] = 1;
-                            nd[(kAll || nym > r) ? tym : sink] = 1;
-                            nd[(kAll || nyp > r) ? typ : sink] = 1;
-                            if (C::D3) {
-                                const int tzm = lz > 0 ? didx<NT, NPT>(p - TX * TY) : sink;
-                                const int tzp = lz < TZ - 1 ? didx<NT, NPT>(p + TX * TY) : sink;
-                                nd[(kAll || nzm > r) ? tzm : sink] = 1;
-                                nd[(kAll || nzp > r) ? tzp : sink] = 1;
-                            }
-                            marked = true;
-                        }
-                    }
-                    if constexpr (COUNT) {
-                        // every lane of the wave takes part, so lane 0's totals are the wave's
-                        w_eval += __popcll(__ballot((dirty >> j) & 1u));
-                        w_imp += __popcll(__ballot(ch));
-                        w_good += __popcll(__ballot(good));
-                    }
-                }
-                if (__ballot(marked) && lane == 0) s_more[passes % 3] = 1;
-                __syncthreads();
-                // the pass flag and the thread's next flags are read together
-                // (one LDS round trip); when nothing was marked the flags are
-                // all clear and the read is simply unused
-                uint8_t* df = sDirty[cb ^ 1] + tid * NPT;
-                const int more = s_more[passes % 3];
-                const uint32_t fl = ld_flags<NPT>(df);
-                asm volatile("" ::"v"(fl));  // keeps the flag read ahead of the branch
-                ++passes;
-                if (!more) break;
-                cb ^= 1;
-                {
-                    dirty = 0;
-    #pragma unroll
-                    for (int j = 0; j < NPT; ++j) dirty |= ((fl >> (8 * j)) & 1u) << j;
-                    if (fl) st_flags<NPT>(df, 0u);
-                    dirty &= live;
-                }
-                if (OP != 0 && OP != 4 && passes >= (1 << 16)) {  // an ablation operator may not settle
-                    if (tid == 0) set_flag(S, kFlagLimit);
-                    break;
-                }
-                if (passes > (1 << 20)) {
-                    if (tid == 0) set_flag(S, kFlagWatchdog);
-                    break;
-                }
-            }
-        }
-
-        if (tid == 0) {
-            const unsigned long long now = wall_clock64();
-            s_stat[2] += now - s_stat[8];
-            s_stat[8] = now;
-        }
-        // ---- write back lowered points, gather lowered face minima ---------
-        uint32_t chg = 0;  // bit j: point j was stored
-        double fmin_[6] = {inf64(), inf64(), inf64(), inf64(), inf64(), inf64()};
-#pragma unroll
-        for (int j = 0; j < NPT; ++j) {
-            const int p = tid + j * NT;
-            const int lx = p % TX, ly = (p / TX) % TY, lz = p / (TX * TY);
-            const int x = x0 + lx, y = y0 + ly, z = z0 + lz;
-            // the point and the six cells next to it, read together
-            const int L = C::lds(lx, ly, lz);
-            const double v = sT[L];
-            const double nxm = sT[L - 1], nxp = sT[L + 1], nym = sT[L - C::SY], nyp = sT[L + C::SY];
-            const double nzm = C::D3 ? sT[L - C::SZ] : inf64(), nzp = C::D3 ? sT[L + C::SZ] : inf64();
-            const double tin = PACK ? sTin[p] : t_in[j];
-            if (x < P.nx && y < P.ny && z < P.nz) {
-                if (v < tin) {
-                    tstore(A.t + P.pt_off + ((int64_t)z * P.ny + y) * P.nx + x, v);
-                    chg |= 1u << j;
-                    // a lowered face value matters to the neighbour only where
-                    // it is below the neighbour's own value there (its halo
-                    // cell here, as staged; values only decrease): the
-                    // operator ignores a neighbour above the point it updates
-                    constexpr bool kAny = OP != 0 && OP != 4;  // not causal: every lowered face value
-                    if (lx == 0 && (kAny || v < nxm)) fmin_[0] = nmin(fmin_[0], v);
-                    if (lx == TX - 1 && (kAny || v < nxp)) fmin_[1] = nmin(fmin_[1], v);
-                    if (ly == 0 && (kAny || v < nym)) fmin_[2] = nmin(fmin_[2], v);
-                    if (ly == TY - 1 && (kAny || v < nyp)) fmin_[3] = nmin(fmin_[3], v);
-                    if (C::D3) {
-                        if (lz == 0 && (kAny || v < nzm)) fmin_[4] = nmin(fmin_[4], v);
-                        if (lz == TZ - 1 && (kAny || v < nzp)) fmin_[5] = nmin(fmin_[5], v);
-                    }
-                } else if (OP != 0 && OP != 4 && v != tin) {
-                    // an ablation operator raised the value: store it, and with
-                    // change tracking activate the neighbours across its faces
-                    tstore(A.t + P.pt_off + ((int64_t)z * P.ny + y) * P.nx + x, v);
-                    chg |= 1u << j;
-                    if (S.track) {
-                        if (lx == 0) fmin_[0] = nmin(fmin_[0], v);
-                        if (lx == TX - 1) fmin_[1] = nmin(fmin_[1], v);
-                        if (ly == 0) fmin_[2] = nmin(fmin_[2], v);
-                        if (ly == TY - 1) fmin_[3] = nmin(fmin_[3], v);
-                    }
-                }
-            }
-        }
-        // block-wide minima and counts: reduced within each wave first, then
-        // one LDS atomic per wave (per-lane atomics on one LDS word would be
-        // serialised lane by lane)
-#pragma unroll
-        for (int f = 0; f < 6; ++f) {
-            if (__ballot(fmin_[f] < inf64())) {
-                const double m = wave_min(fmin_[f]);
+        for (int f = 0; f < 4; ++f) {
+            if (__ballot(act && on[f])) {
+                const double m = wave_min(act && on[f] ? v : inf64());
                 if (lane == 0) atomicMin(&s_face[f], (unsigned long long)as_u64(m));
             }
         }
-        {
-            int cnt = 0;
-#pragma unroll
-            for (int j = 0; j < NPT; ++j) cnt += __popcll(__ballot((chg >> j) & 1u));
-            if (cnt && lane == 0) atomicAdd(&s_upd, (unsigned int)cnt);
-        }
-        if (__ballot(pend < inf64())) {
-            const double m = wave_min(pend);
-            if (lane == 0) atomicMin(&s_pend, (unsigned long long)as_u64(m));
-        }
+        const int cnt = __popcll(__ballot(chg));
+        if (cnt && lane == 0) atomicAdd(&s_upd, (unsigned int)cnt);
         // every wave's stores complete before the block hands the tile's faces
         // to the neighbours
         stores_done();
         __syncthreads();
-
-        // ---- publish: activate neighbours, end the run or hand on ----------
         if (tid < 64) {
-            // runs of this kernel read halos without looking at V (t starts at
-            // +inf), so V needs no ordering against the activations
-            const int nxt = publish(S, A.tkey, (uint32_t)tile, s_bucket, !visited, s_nb, s_nid, s_face, true,
-                                    s_pend, false);
+            // runs read halos without looking at V (t starts at +inf), so V
+            // needs no ordering against the activations
+            const int nxt = publish(S, A.tkey, (uint32_t)tile, s_slot, !visited, s_nb, s_nid, s_face, true, kInfBits,
+                                    false);
             if (tid == 0) s_next = nxt;
         }
         if (tid == 0) {
             s_stat[5] += s_upd;
             s_stat[6] += (unsigned long long)passes;
-            const unsigned long long now = wall_clock64();
-            s_stat[3] += now - s_stat[8];
-            s_stat[8] = now;
+            phase(3);
         }
         __syncthreads();
     }
-    if (COUNT && lane == 0) {
-        __hip_atomic_fetch_add(S.counters + 16, w_eval, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __hip_atomic_fetch_add(S.counters + 17, w_imp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __hip_atomic_fetch_add(S.counters + 18, w_good, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
     if (tid == 0) {
-        s_stat[0] += wall_clock64() - s_stat[8];
-        for (int i = 0; i < 4; ++i)
-            __hip_atomic_fetch_add(S.counters + 5 + i, s_stat[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __hip_atomic_fetch_add(S.counters + 10, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __hip_atomic_fetch_add(S.counters + 12, s_stat[7], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (S.timeline)
-            __hip_atomic_fetch_max(S.timeline + 1, (unsigned long long)wall_clock64(), __ATOMIC_RELAXED,
-                                   __HIP_MEMORY_SCOPE_AGENT);
-        __hip_atomic_fetch_add(S.counters + 0, s_stat[4], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __hip_atomic_fetch_add(S.counters + 1, s_stat[5], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __hip_atomic_fetch_add(S.counters + 2, s_stat[6], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        phase(0);
+        flush_stats(S, s_stat);
     }
 }
 

@@ -70,18 +70,25 @@ __device__ __forceinline__ void sort3(double& a0, double& a1, double& a2) {
     a1 = nmax(lo, m);
 }
 
-// Square root for the estimate below: the hardware reciprocal square root
-// refined by one coupled Newton step and one residual correction (about one
+// Square root for the estimate below: the hardware reciprocal square root y and
+// one third-order step, x y (1 + e / 2 + 3 e^2 / 8) with e = 1 - x y^2 (about one
 // ulp).  Not correctly rounded, and NaN for x == 0: the estimate only steers
 // the exact search, which handles any starting point.
 __device__ __forceinline__ double est_sqrt(double x) {
     const double y = __builtin_amdgcn_rsq(x);
-    double g = x * y, hh = 0.5 * y;
-    const double e = fma(-g, hh, 0.5);
-    g = fma(g, e, g);
-    hh = fma(hh, e, hh);
-    const double d = fma(-g, g, x);
-    return fma(d, hh, g);
+    const double t = x * y;
+    const double e = fma(-t, y, 1.0);
+    return fma(t * e, fma(e, 0.375, 0.5), t);
+}
+
+// Quotient for the estimates: the hardware reciprocal refined twice and one
+// residual correction (about one ulp; not correctly rounded).
+__device__ __forceinline__ double est_div(double n, double d) {
+    double y = __builtin_amdgcn_rcp(d);
+    y = fma(fma(-d, y, 1.0), y, y);
+    y = fma(fma(-d, y, 1.0), y, y);
+    const double u = n * y;
+    return fma(fma(-d, u, n), y, u);
 }
 
 // Closed-form Godunov estimate from sorted minima (u = r - a0 solves the one-,
@@ -212,6 +219,83 @@ __device__ __forceinline__ double update(double x, double y, double z, double q,
     return search_slow(a0, a1, a2, c, A0, G, tcb);
 }
 
+// Comparison of two doubles over the wave, as a lane mask.
+__device__ __forceinline__ unsigned long long mask_lt(double a, double b) { return __builtin_amdgcn_fcmp(a, b, 4); }
+__device__ __forceinline__ unsigned long long mask_ge(double a, double b) { return __builtin_amdgcn_fcmp(a, b, 3); }
+__device__ __forceinline__ bool in_mask(unsigned long long m) { return __builtin_amdgcn_inverse_ballot_w64(m); }
+
+// update() out of line, for the lanes its short form below cannot decide.
+template <bool D3>
+__device__ __noinline__ double update_rare(double x, double y, double z, double q, double tcur) {
+    bool changed;
+    return update<D3>(x, y, z, q, q * q, tcur, changed);
+}
+
+// update() for the wave-per-tile solver: called by whole waves, `act` the lanes
+// that count, `tc` their current values.  Returns the operator's value (an
+// improvement where it is below tc) for those lanes.
+//
+// It leaves out the clamps of the guess, the maximum with 0 of the smallest
+// minimum's term and the branches: within the window G - 1, G, G + 1, with
+// G - 1 above the smallest minimum, false..true outcomes still bracket the
+// answer, wherever tc is.  A lane whose window does not (also for a NaN guess,
+// or values so close that the window reaches the minimum) takes update()
+// itself; few solves have any.  The guess is the one of guess() with the square
+// roots of negative numbers that its regimes exclude left unguarded and fused
+// multiply-adds: it only has to be within an ulp of the answer.
+template <bool D3 = true>
+__device__ __forceinline__ double update_short(double x, double y, double z, double q, double tc,
+                                               unsigned long long act) {
+    double a0, a1, a2;
+    if constexpr (D3) {
+        a0 = x;
+        a1 = y;
+        a2 = z;
+        sort3(a0, a1, a2);
+    } else {
+        a0 = nmin(x, y);
+        a1 = nmax(x, y);
+        a2 = inf64();
+    }
+    const double c = q * q;
+    const double b1 = a1 - a0, r1 = a0 + q;
+    double rad = fma(-b1, b1, c + c), sum = b1, third = 0.5;
+    if constexpr (D3) {
+        const double b2 = a2 - a0, e2 = a2 - a1, sb = b1 + b2;
+        // three terms where those of a0 and a1 at a2 stay below c (never for a2 = +inf)
+        const bool three = fma(e2, e2, b2 * b2) < c;
+        const double d3 = fma(sb, sb, 3.0 * (c - fma(b2, b2, b1 * b1)));
+        rad = three ? d3 : rad;
+        sum = three ? sb : sum;
+        third = three ? 1.0 / 3.0 : third;
+    }
+    double g = fma(sum + est_sqrt(rad), third, a0);
+    g = r1 <= a1 ? r1 : g;
+    const uint64_t G = as_u64(g);
+    double r[3], s[3];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) r[k] = as_f64(G - 1 + (uint64_t)k);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        const double m0 = r[k] - a0, m1 = fmax(r[k] - a1, 0.0);
+        s[k] = m0 * m0 + m1 * m1;
+    }
+    if constexpr (D3) {
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            const double m2 = fmax(r[k] - a2, 0.0);
+            s[k] = s[k] + m2 * m2;
+        }
+    }
+    double res = s[1] >= c ? r[1] : r[2];
+    // decided where r[0] fails and r[2] reaches c
+    const unsigned long long sure = mask_lt(a0, r[0]) & mask_lt(s[0], c) & mask_ge(s[2], c);
+    if (act & ~sure) {
+        if (in_mask(act & ~sure)) res = update_rare<D3>(x, y, z, q, tc);
+    }
+    return res;
+}
+
 // ---------------------------------------------------------------------------
 // rectilinear grids: spacing varying per axis and index
 // ---------------------------------------------------------------------------
@@ -328,25 +412,29 @@ __device__ __forceinline__ double update_rect(const double* n, const double* w, 
     }
     const double a0 = s0;
     const uint64_t tcb = as_u64(tcur);
-    // guess: add axes while the root lies above the next minimum
-    double A = 0.0, B = 0.0, C = -c, u = inf64();
-    bool go = true;
-#pragma unroll
-    for (int j = 0; j < (D3 ? 3 : 2); ++j) {
-        const double ak = j == 0 ? s0 : (j == 1 ? s1 : s2);
-        const double wk = j == 0 ? v0 : (j == 1 ? v1 : v2);
-        const double nxt = (j == 0 ? s1 : (j == 1 ? s2 : inf64())) - a0;
-        if (go && ak < inf64()) {
-            const double b = ak - a0;
-            const double w2 = wk * wk;
+    // guess: the axes whose minimum lies below the root, i.e. at whose minimum
+    // the terms of the smaller ones do not reach c yet; one square root and one
+    // division for the quadratic they give
+    const double b1 = s1 - a0, b2 = s2 - a0;
+    const double w0 = v0 * v0, w1 = v1 * v1;
+    const bool use1 = w0 * b1 * b1 < c;   // false for b1 = +inf
+    double A = w0, B = 0.0, C = -c;
+    if (use1) {
+        const double wb = w1 * b1;
+        A = A + w1;
+        B = wb;
+        C = C + wb * b1;
+    }
+    if constexpr (D3) {
+        const double w2 = v2 * v2, e2 = b2 - b1;
+        if (use1 && w0 * b2 * b2 + w1 * e2 * e2 < c) {
+            const double wb = w2 * b2;
             A = A + w2;
-            B = B + w2 * b;
-            C = C + (w2 * b) * b;
-            const double disc = B * B - A * C;
-            u = (B + __builtin_sqrt(fmax(disc, 0.0))) / A;
-            go = u > nxt;
+            B = B + wb;
+            C = C + wb * b2;
         }
     }
+    const double u = est_div(B + est_sqrt(fmax(B * B - A * C, 0.0)), A);
     const double g = a0 + u;
     const uint64_t A0 = as_u64(a0);
     uint64_t G = as_u64(g);

@@ -19,6 +19,16 @@
 //  * delta = 0 puts everything in one bucket (a plain FIFO worklist);
 //  * the operator is monotone and causal, so none of this changes results.
 //
+// Shards.  A bucket's ring is split into kShards rings, and a tile always
+// goes to the one its id names (neighbouring tiles to different ones, one of
+// every aligned group of 8 to each).  A workgroup claims from its own shard
+// first and from the others when that one shows nothing.  The reason: the
+// device completes a read-modify-write of one 64-byte line about every 12 ns
+// whoever issues it (83 per us measured with 64 to 4096 waves, against 545 per
+// us over 8 lines), and while such requests queue, the loads behind them in the
+// compute unit wait too (staging a tile took 33 us instead of 3.2 us with 2816
+// waves on unsharded rings).
+//
 // Each ring is a bounded MPMC array of 64-bit cells (sequence << 32 | tile),
 // positions taken with fetch-add.  Its queued count and the number of runs
 // claimed from it share one 64-bit word (running << 32 | count + 2^31), so a
@@ -28,8 +38,8 @@
 // (sequence p + cap) by the consumer after reading: a producer never overwrites
 // a cell whose item has been claimed but not yet read.  A tile is queued at most
 // once at a time (tile state machine below), so a ring never holds more than
-// `ntiles` items and capacity = next_pow2(max(ntiles, 2)) means no producer waits
-// on an unclaimed item.  Positions and counters are never reset between solves
+// its share of the tiles, ceil(ntiles / 8), and capacity = next_pow2(max(that, 2))
+// means no producer waits on an unclaimed item.  Positions and counters are never reset between solves
 // (a solve ends with every ring drained), only re-initialised after a watchdog
 // expiry.
 //
@@ -73,12 +83,16 @@ constexpr uint32_t kQ = 1u, kR = 2u, kV = 4u, kS = 8u;
 // [12] hand-offs [13..15] residual accumulators [16] operator evaluations
 // [17] improving evaluations [18] evaluations that set the final value
 constexpr int kCounters = 24;
-constexpr int kMaxRings = 64;
+constexpr int kRings = 32;    // buckets of the window
+constexpr int kShards = 8;    // rings per bucket
 // Each ring counter (head, tail, count + running) lives in its own 256-byte
 // line, so polling one does not slow the atomics on the others.
 constexpr int kCtrPad = 64;                 // uint32 words per counter line
 constexpr int kCtrStride = 4 * kCtrPad;     // uint32 words per ring
 constexpr int kCrWord = 2 * kCtrPad;        // offset of the count + running word
+// words of all ring counters and, after them, the live-work counters
+constexpr int kPendWord = kRings * kShards * kCtrStride;
+constexpr int kCtrWords = kPendWord + kShards * kCtrPad;
 constexpr uint64_t kCountBias = 1ull << 31; // count is stored biased, so it may dip below 0
 constexpr uint64_t kRunOne = 1ull << 32;
 
@@ -86,15 +100,13 @@ constexpr uint64_t kRunOne = 1ull << 32;
 constexpr uint32_t kFlagDomain = 1u, kFlagLimit = 2u, kFlagBadSrc = 4u, kFlagWatchdog = 8u, kFlagBadStart = 16u;
 
 struct Sched {
-    uint64_t* items;     // [nrings][cap]
+    uint64_t* items;     // [kRings * kShards][cap]
     uint32_t* ctr;       // ring counters, see ring_head / ring_tail / ring_cr
     uint32_t* tstate;    // [ntiles]
     int32_t* cur;        // lowest bucket of the window
-    int32_t* pending;    // tiles queued or running
     unsigned long long* counters;  // statistics: [0] visits [1] point updates [2] relax passes ...
     uint32_t* flags;     // device status flags
     int32_t* poisoned;   // set on a watchdog expiry: the next reset re-initialises the rings
-    int nrings;
     uint32_t cap_mask;
     double inv_delta;    // 1/delta, 0 => single bucket
     long long max_visits;  // 0 => unlimited
@@ -113,6 +125,47 @@ __device__ __forceinline__ unsigned long long* ring_cr(const Sched& s, int r) {
 __device__ __forceinline__ int32_t cr_count(uint64_t w) { return (int32_t)((int64_t)(w & 0xffffffffull) - (int64_t)kCountBias); }
 __device__ __forceinline__ unsigned long long ld_cr(const Sched& s, int r) {
     return __hip_atomic_load(ring_cr(s, r), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// Ring of a bucket in a shard; shard of a tile and of this workgroup.
+__device__ __forceinline__ int ring_of(int64_t bucket, int shard) {
+    return (int)(bucket & (kRings - 1)) * kShards + shard;
+}
+__device__ __forceinline__ int shard_of(uint32_t tile) {
+    return (int)((tile ^ (((tile >> 3) * 0x9E3779B1u) >> 29)) & (kShards - 1));
+}
+// A run is counted as running in the ring it was claimed from, named by its
+// slot = bucket * kShards + shard; a run handed on keeps the slot.
+__device__ __forceinline__ int64_t slot_bucket(int64_t slot) { return slot / kShards; }
+__device__ __forceinline__ int slot_ring(int64_t slot) { return ring_of(slot / kShards, (int)(slot & (kShards - 1))); }
+__device__ __forceinline__ int my_shard() { return (int)(blockIdx.x & (kShards - 1)); }
+
+// Live work: per shard of the counting workgroup, the tiles ever queued (high
+// half) and the runs ever ended (low half).  Both only grow, so "ended" summed
+// first and "queued" summed afterwards can only be equal when nothing was
+// queued or running in between.
+__device__ __forceinline__ unsigned long long* pend_word(const Sched& s, int shard) {
+    return (unsigned long long*)(s.ctr + kPendWord + shard * kCtrPad);
+}
+__device__ __forceinline__ void pend_add(const Sched& s, uint32_t queued, uint32_t ended) {
+    __hip_atomic_fetch_add(pend_word(s, my_shard()), ((unsigned long long)queued << 32) + ended, __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_AGENT);
+}
+// True when no work is left anywhere.  All 64 lanes.
+__device__ __forceinline__ bool all_done(const Sched& s) {
+    const int lane = threadIdx.x & 63;
+    uint32_t sum[2];
+#pragma unroll
+    for (int pass = 0; pass < 2; ++pass) {
+        unsigned long long w = 0;
+        if (lane < kShards)
+            w = __hip_atomic_load(pend_word(s, lane), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        stores_done();  // the first pass's loads return before the second's go out
+        uint32_t v = pass == 0 ? (uint32_t)w : (uint32_t)(w >> 32);
+#pragma unroll
+        for (int off = 1; off < kShards; off <<= 1) v += __shfl_xor(v, off);
+        sum[pass] = (uint32_t)__builtin_amdgcn_readfirstlane((int)v);
+    }
+    return sum[0] == sum[1];
 }
 __device__ __forceinline__ void cr_add(const Sched& s, int r, uint64_t v) {
     __hip_atomic_fetch_add(ring_cr(s, r), (unsigned long long)v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -141,10 +194,10 @@ __device__ __forceinline__ int64_t bucket_of(const Sched& s, double t) {
     return (int64_t)k;
 }
 
-// Enqueue `tile` with time key `t`.  The caller has already counted it in
-// `pending`.  `base` is the bucket the pushing run was claimed from (0 before
+// Enqueue `tile` with time key `t`.  The caller has already counted it as live
+// work.  `base` is the bucket the pushing run was claimed from (0 before
 // the solve starts): `cur` cannot pass it while that run is live and is at least
-// base - lookahead, so buckets in [base, base + nrings - 1 - lookahead] never
+// base - lookahead, so buckets in [base, base + kRings - 1 - lookahead] never
 // alias a bucket behind `cur`.  With count = false the ring's queued count is
 // left to the caller, which must add it after its stores are done and before
 // it ends the run (publish folds it into the end-of-run RMW).  Single lane.
@@ -152,8 +205,8 @@ __device__ __forceinline__ void push_tile(const Sched& s, uint32_t tile, double 
                                           bool count = true) {
     int64_t k = bucket_of(s, t);
     if (k < base) k = base;
-    if (k > base + s.nrings - 1 - s.lookahead) k = base + s.nrings - 1 - s.lookahead;
-    int r = (int)(k % s.nrings);
+    if (k > base + kRings - 1 - s.lookahead) k = base + kRings - 1 - s.lookahead;
+    const int r = ring_of(k, shard_of(tile));
     uint32_t pos = __hip_atomic_fetch_add(ring_tail(s, r), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     uint64_t* cell = s.items + (size_t)r * (s.cap_mask + 1) + (pos & s.cap_mask);
     // wait until the previous lap's consumer has read this cell (bounded: that
@@ -179,21 +232,20 @@ __device__ __forceinline__ void push_tile(const Sched& s, uint32_t tile, double 
 __device__ __forceinline__ int64_t push_bucket(const Sched& s, double t, int64_t base) {
     int64_t k = bucket_of(s, t);
     if (k < base) k = base;
-    if (k > base + s.nrings - 1 - s.lookahead) k = base + s.nrings - 1 - s.lookahead;
+    if (k > base + kRings - 1 - s.lookahead) k = base + kRings - 1 - s.lookahead;
     return k;
 }
 
-// End of the runs claimed from `bucket` by this workgroup: its pushes were
-// counted first (push_tile waits for that), so the bucket never looks drained
-// while work it produced is in flight.  Single lane.
-__device__ __forceinline__ void end_run(const Sched& s, int64_t bucket) {
+// End of a run: its pushes were counted first (push_tile waits for that), so the
+// bucket does not look drained while work it produced is in flight.  Single lane.
+__device__ __forceinline__ void end_run(const Sched& s, int64_t slot) {
     stores_done();
-    cr_add(s, (int)(bucket % s.nrings), 0ull - kRunOne);
+    cr_add(s, slot_ring(slot), 0ull - kRunOne);
 }
 
 // Count a newly activated tile and enqueue it.  Single lane.
 __device__ __forceinline__ void activate_push(const Sched& s, uint32_t tile, double t, int64_t base) {
-    __hip_atomic_fetch_add(s.pending, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    pend_add(s, 1, 0);
     push_tile(s, tile, t, base);
 }
 
@@ -226,134 +278,329 @@ __device__ __forceinline__ int try_claim(const Sched& s, int r) {
     }
 }
 
+// Try to take up to `want` items from ring r with one RMW, which counts as many
+// runs as started.  All 64 lanes of a wave; lane i < the returned number gets an
+// item in `item`.  Returns -2 on a watchdog expiry.
+__device__ __forceinline__ int try_claim_many(const Sched& s, int r, int want, int& item) {
+    const int lane = threadIdx.x & 63;
+    int got = 0;
+    uint32_t pos = 0;
+    if (lane == 0) {
+        const uint64_t step = (kRunOne - 1) * (uint64_t)want;
+        const uint64_t old = __hip_atomic_fetch_add(ring_cr(s, r), (unsigned long long)step, __ATOMIC_RELAXED,
+                                                    __HIP_MEMORY_SCOPE_AGENT);
+        const int32_t have = cr_count(old);
+        got = have <= 0 ? 0 : (have < want ? have : want);
+        if (got < want) cr_add(s, r, 0ull - (kRunOne - 1) * (uint64_t)(want - got));
+        if (got)
+            pos = __hip_atomic_fetch_add(ring_head(s, r), (uint32_t)got, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    got = __builtin_amdgcn_readfirstlane(got);
+    pos = (uint32_t)__builtin_amdgcn_readfirstlane((int)pos) + (uint32_t)lane;
+    bool bad = false;
+    if (lane < got) {
+        uint64_t* cell = s.items + (size_t)r * (s.cap_mask + 1) + (pos & s.cap_mask);
+        // the producer that reserved this position is about to fill the cell
+        for (long long spin = 0;; ++spin) {
+            const uint64_t it = __hip_atomic_load(cell, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if ((uint32_t)(it >> 32) == pos + 1u) {
+                __hip_atomic_store(cell, (uint64_t)(pos + s.cap_mask + 1u) << 32, __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_AGENT);
+                item = (int)(uint32_t)it;
+                break;
+            }
+            if (spin > (1ll << 24)) {
+                set_flag(s, kFlagWatchdog);
+                bad = true;
+                break;
+            }
+            __builtin_amdgcn_s_sleep(1);
+        }
+    }
+    return __ballot(bad) ? -2 : got;
+}
+
 // Idle back-off: s_sleep takes an immediate, so sleep in units of 127.
 __device__ __forceinline__ void idle_sleep(int units) {
     for (int i = 0; i < units; ++i) __builtin_amdgcn_s_sleep(127);
 }
 
-// Called by all 64 lanes of one wave.  Returns a tile and the bucket it came
-// from (*bucket), counted as running there, or -1 when no work is left anywhere
-// (pending == 0), or -2 on a watchdog expiry.
+// Called by all 64 lanes of one wave.  `take(ring, count)` takes items from a
+// ring that showed `count` queued ones and returns > 0 (taken), 0 (none left) or
+// -2.  Returns what `take` returned and the slot (*slot: bucket and shard, counted
+// as running there), or -1 when no work is left anywhere, or -2 on a watchdog expiry.
 //
-// The watchdog counts consecutive polls that saw no progress anywhere: the
-// window's first count word (it changes with every claim, push and end of a
-// run in the current bucket), the current bucket and the live-work count are
-// compared with the previous poll's, and any change restarts the count.  So it
-// fires only when nothing has moved for 2^19 polls (about 14 s with the
-// back-off below), however long a valid solve takes.
+// A poll reads the count words of 8 buckets x 8 shards, one per lane, and `cur`
+// in one round trip (`cur_hint` is the window's lowest bucket as this workgroup
+// last saw it; the words are used only when `cur` still equals it), and the
+// words of all other buckets, in one more, only when those show nothing.  It
+// takes from the lowest bucket of its own shard, else from the lowest of the
+// others.  A claim that comes too late costs two read-modify-writes on the very
+// line the work comes through, so where few items face many claimers only some
+// of them try: about as many as there are items.
 //
-// `cur_hint` is the window's lowest bucket as this workgroup last saw it (0
-// before its first claim; `cur` never decreases).  A poll reads the window's
-// count words at the hint and `cur` itself together, one round trip, and uses
-// them only when `cur` still equals the hint; otherwise it reads again from the
-// new value (the cost of the former sequential read).
-__device__ __forceinline__ int claim(const Sched& s, int64_t* bucket, int32_t& cur_hint) {
+// The watchdog counts consecutive polls that saw no progress anywhere (no count
+// word, `cur` or live-work change); it fires after 2^kStallBits of them (about
+// 14 s with the back-off below), however long a valid solve takes.  kMaxSleep
+// caps the back-off (units of s_sleep(127), about 3.4 us); with few workgroups
+// polling (64 or fewer) the cap is a quarter of one, as they cannot flood the
+// counters and the front's next tile waits for the poll.
+template <int kMaxSleep, int kStallBits, class Take>
+__device__ __forceinline__ int claim_with(const Sched& s, int64_t* slot, int32_t& cur_hint, Take take) {
     const int lane = threadIdx.x & 63;
     const int win = s.lookahead + 1;
+    const int own = my_shard();
+    const int lj = lane / kShards, lsh = lane % kShards;
+    constexpr int kCols = 64 / kShards;  // buckets read at once
+    const unsigned long long own_lanes = 0x0101010101010101ull << own;
+    static_assert(kShards == 8, "the lane masks below");
+    constexpr int kParts = kRings / kCols;
     long long idle = 0;   // polls so far (sets the back-off)
     long long stall = 0;  // polls since anything last moved (the watchdog)
-    unsigned long long seen_w = ~0ull;
-    long long seen_cp = -1;
+    unsigned long long seen = ~0ull;
+    uint32_t rnd = (uint32_t)wall_clock64() * 0x9E3779B1u + blockIdx.x * 0x85EBCA6Bu;
     for (;;) {
         const int32_t c = cur_hint;
-        const int r = (int)(((int64_t)c + lane) % s.nrings);
-        unsigned long long w = kCountBias;  // nothing queued, nothing running
-        if (lane < win) w = ld_cr(s, r);
         const int32_t cnow = ld_rlx(s.cur);
+        unsigned long long w[kParts];
+        w[0] = ld_cr(s, ring_of((int64_t)c + lj, lsh));
         if (cnow != c) {
             cur_hint = cnow;
             continue;
         }
-        const unsigned long long mask = __ballot(cr_count(w) > 0);
-        if (mask) {
-            // lowest bucket of the window with queued work
-            const int j = __ffsll((long long)mask) - 1;
-            int got = -1;
-            if (lane == 0) got = try_claim(s, (int)(((int64_t)c + j) % s.nrings));
-            got = __shfl(got, 0);
-            if (got >= 0) {
-                *bucket = (int64_t)c + j;
-                return got;
-            }
-            if (got == -2) return -2;
-            continue;
-        }
-        const unsigned long long w0 = __shfl(w, 0);
-        int32_t pend_now = -1;
-        if (w0 == kCountBias) {
-            // bucket `cur` drained: move to the next bucket that has work
-            // queued or still running (full scan).  A bucket whose runs (taken
-            // through the lookahead window) are still live is not skipped:
-            // their pushes may land in it, and its ring must not be reused
-            // for a later bucket meanwhile.
-            unsigned long long wf = kCountBias;
-            if (lane < s.nrings) wf = ld_cr(s, r);
-            const unsigned long long m2 = __ballot(wf != kCountBias) & ~1ull;
-            if (m2) {
-                const int j = __ffsll((long long)m2) - 1;
-                if (lane == 0) {
+        int first = 0;  // bucket (from c) of w[at]'s lane 0
+        unsigned long long at = w[0];
+        unsigned long long mask = __ballot(lj < win && cr_count(at) > 0);
+        bool moved = false;
+        if (!mask) {
+#pragma unroll
+            for (int p = 1; p < kParts; ++p) w[p] = ld_cr(s, ring_of((int64_t)c + p * kCols + lj, lsh));
+            int from = 0;
+            if (!__ballot(lane < kShards && w[0] != kCountBias)) {
+                // bucket `cur` drained: move to the next bucket that has work
+                // queued or still running.  A bucket whose runs (taken through
+                // the lookahead window) are still live is not skipped: their
+                // pushes may land in it, and its rings must not be reused for a
+                // later bucket meanwhile.  (The words are not read at one
+                // instant, so a push may be missed that goes to a word read
+                // before it from a run whose end is seen: the bucket then counts
+                // as kRings later, which only delays it.)
+                int next = 0;
+#pragma unroll
+                for (int p = kParts - 1; p >= 0; --p) {
+                    unsigned long long m2 = __ballot(w[p] != kCountBias);
+                    if (p == 0) m2 &= ~0xFFull;
+                    if (m2) next = p * kCols + (__ffsll((long long)m2) - 1) / kShards;
+                }
+                if (next) {
                     int32_t expect = c;
-                    if (__hip_atomic_compare_exchange_strong(s.cur, &expect, c + j, __ATOMIC_RELAXED,
-                                                             __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) {
-                        const unsigned long long i = __hip_atomic_fetch_add(s.counters + 11, 1ull, __ATOMIC_RELAXED,
-                                                                            __HIP_MEMORY_SCOPE_AGENT);
-                        if (s.timeline && i < (unsigned long long)s.timeline_cap) {
-                            __hip_atomic_store(s.timeline + 2 + 2 * i, (unsigned long long)wall_clock64(),
-                                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                            __hip_atomic_store(s.timeline + 3 + 2 * i, (unsigned long long)(c + j),
-                                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    if (lane == 0) {
+                        if (__hip_atomic_compare_exchange_strong(s.cur, &expect, c + next, __ATOMIC_RELAXED,
+                                                                 __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) {
+                            expect = c + next;
+                            const unsigned long long i = __hip_atomic_fetch_add(s.counters + 11, 1ull, __ATOMIC_RELAXED,
+                                                                                __HIP_MEMORY_SCOPE_AGENT);
+                            if (s.timeline && i < (unsigned long long)s.timeline_cap) {
+                                __hip_atomic_store(s.timeline + 2 + 2 * i, (unsigned long long)wall_clock64(),
+                                                   __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                                __hip_atomic_store(s.timeline + 3 + 2 * i, (unsigned long long)(c + next),
+                                                   __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                            }
                         }
                     }
+                    cur_hint = __builtin_amdgcn_readfirstlane(expect);
+                    if (cur_hint != c + next) continue;  // another workgroup moved it
+                    from = next;                         // the window now starts there
+                    moved = true;
+                } else {
+                    if (all_done(s)) return -1;
                 }
-                continue;
             }
-            pend_now = ld_rlx(s.pending);
-            if (pend_now <= 0) return -1;
+            // lowest bucket of the window with work
+#pragma unroll
+            for (int p = kParts - 1; p >= 0; --p) {
+                const int j = p * kCols + lj;
+                const unsigned long long m = __ballot(j >= from && j < from + win && cr_count(w[p]) > 0);
+                if (m) {
+                    mask = m;
+                    at = w[p];
+                    first = p * kCols;
+                }
+            }
         }
-        const long long cp = ((long long)c << 32) ^ (long long)(uint32_t)pend_now;
-        if (w0 != seen_w || cp != seen_cp) {
-            stall = 0;  // something moved since the last poll
-            seen_w = w0;
-            seen_cp = cp;
+        if (mask) {
+            const unsigned long long mine = mask & own_lanes;
+            int l;
+            if (mine) {
+                l = __ffsll((long long)mine) - 1;
+            } else {
+                // lowest bucket with work; of its shards the next after this one's
+                const int jl = (__ffsll((long long)mask) - 1) & ~(kShards - 1);
+                const uint32_t sh = (uint32_t)(mask >> jl) & 0xFFu;
+                const uint32_t rot = ((sh | (sh << 8)) >> own) & 0xFFu;
+                l = jl + ((__ffs((int)rot) - 1 + own) & (kShards - 1));
+            }
+            const int32_t count = cr_count(__shfl(at, l));
+            // claimers this ring may have: this shard's workgroups, or all
+            const uint32_t rivals = mine ? (gridDim.x + kShards - 1) / kShards : gridDim.x;
+            rnd = (uint32_t)__builtin_amdgcn_readfirstlane((int)(rnd * 1664525u + 1013904223u));
+            if ((uint32_t)count * 2u >= rivals || (rnd >> 16) * (uint64_t)rivals < (uint64_t)count * 2u * 65536u) {
+                const int64_t bucket = (int64_t)c + first + l / kShards;
+                const int got = take(ring_of(bucket, l % kShards), count);
+                if (got > 0) {
+                    *slot = bucket * kShards + l % kShards;
+                    return got;
+                }
+                if (got == -2) return -2;
+            }
+            __builtin_amdgcn_s_sleep(8);
+            stall = 0;
+            continue;
         }
+        if (moved) continue;
+        if (__ballot(w[0] != seen)) stall = 0;  // something moved since the last poll
+        seen = w[0];
         ++idle;
-        if (++stall > (1ll << 19)) {
+        if (++stall > (1ll << kStallBits)) {
             if (lane == 0) set_flag(s, kFlagWatchdog);
             return -2;
         }
-        // exponential back-off, ~0.1 us doubling up to ~25 us, keeps idle
-        // workgroups from flooding the counters the busy ones need
+        // exponential back-off from about 0.1 us keeps idle workgroups from
+        // flooding the counters the busy ones need
         if (idle < 2) __builtin_amdgcn_s_sleep(4);
         else if (idle < 3) __builtin_amdgcn_s_sleep(16);
         else if (idle < 4) __builtin_amdgcn_s_sleep(64);
-        else idle_sleep(idle < 5 ? 1 : (idle < 6 ? 2 : (idle < 7 ? 4 : 8)));
+        else if (kMaxSleep == 1 && gridDim.x <= 64) __builtin_amdgcn_s_sleep(32);
+        else idle_sleep(min(kMaxSleep, idle < 5 ? 1 : (idle < 6 ? 2 : (idle < 7 ? 4 : 8))));
+    }
+}
+
+// One tile for a block of its own (the block-per-tile kernels).
+__device__ __forceinline__ int claim(const Sched& s, int64_t* slot, int32_t& cur_hint) {
+    int tile = -1;
+    const int rc = claim_with<8, 19>(s, slot, cur_hint, [&](int r, int32_t) {
+        int got = -1;
+        if ((threadIdx.x & 63) == 0) got = try_claim(s, r);
+        got = __shfl(got, 0);
+        tile = got;
+        return got >= 0 ? 1 : (got == -2 ? -2 : 0);
+    });
+    return rc > 0 ? tile : rc;
+}
+
+// Work for the waves of one block that each run tiles of their own.  A wave
+// without work registers as idle; one idle wave at a time polls the rings for
+// all of them and takes several items with one RMW, so the shared counters see
+// one poller per block (a read-modify-write of one address completes about
+// every 12 ns on this device whoever issues it, so thousands of polling waves
+// would slow every push and claim).
+struct GroupMail {
+    int lock;
+    unsigned int idle;       // waves waiting for work
+    int tile[16];            // per wave: kNoMail, or the tile handed to it
+    int64_t slot[16];
+};
+constexpr int kNoMail = -3;
+
+__device__ __forceinline__ int lds_ld(const int* p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
+// As claim(), for wave `w` of the block.
+__device__ __forceinline__ int claim_group(const Sched& s, GroupMail& g, int w, int64_t* slot, int32_t& cur_hint) {
+    const int lane = threadIdx.x & 63;
+    if (lane == 0) {
+        __hip_atomic_store(&g.tile[w], kNoMail, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        __hip_atomic_fetch_or(&g.idle, 1u << w, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
+    }
+    for (;;) {
+        int tile = kNoMail;
+        int locked = 0;
+        if (lane == 0) {
+            tile = __hip_atomic_load(&g.tile[w], __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP);
+            if (tile == kNoMail) {
+                locked = __hip_atomic_exchange(&g.lock, 1, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP) == 0;
+                // work may have been handed over before the lock was free
+                if (locked) tile = __hip_atomic_load(&g.tile[w], __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP);
+            }
+        }
+        tile = __builtin_amdgcn_readfirstlane(tile);
+        locked = __builtin_amdgcn_readfirstlane(locked);
+        if (tile != kNoMail) {
+            if (locked && lane == 0)
+                __hip_atomic_store(&g.lock, 0, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
+            *slot = g.slot[w];
+            return tile;
+        }
+        if (!locked) {
+            __builtin_amdgcn_s_sleep(4);
+            continue;
+        }
+        int item = -1;
+        int64_t b = 0;
+        unsigned int who = 0;
+        const int got = claim_with<1, 22>(s, &b, cur_hint, [&](int r, int32_t count) {
+            who = (unsigned int)__builtin_amdgcn_readfirstlane(
+                (int)__hip_atomic_load(&g.idle, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP));
+            // a share of what is queued, so that the blocks' waves fill evenly
+            const int want = max(1, min(__popc(who), count >> 6));
+            return try_claim_many(s, r, want, item);
+        });
+        int mine = got;
+        if (got > 0) {
+            // this wave takes item 0, the next idle waves the others
+            mine = __builtin_amdgcn_readfirstlane(item);
+            unsigned int rest = who & ~(1u << w), gone = 1u << w;
+            for (int i = 1; i < got; ++i) {
+                const int o = __ffs(rest) - 1;
+                rest &= rest - 1;
+                gone |= 1u << o;
+            }
+            if (lane == 0) __hip_atomic_fetch_and(&g.idle, ~gone, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            rest = who & ~(1u << w);
+            for (int i = 1; i < got; ++i) {
+                const int o = __ffs(rest) - 1;
+                rest &= rest - 1;
+                const int t = __shfl(item, i);
+                if (lane == 0) {
+                    g.slot[o] = b;
+                    __hip_atomic_store(&g.tile[o], t, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
+                }
+            }
+            *slot = b;
+        } else if (lane == 0) {
+            __hip_atomic_fetch_and(&g.idle, ~(1u << w), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        }
+        if (lane == 0) __hip_atomic_store(&g.lock, 0, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
+        return mine;
     }
 }
 
 // End of a run of `tile`, executed by the 64 lanes of wave 0 after every wave
 // of the block has written its results and waited for them (stores_done).
-//   nb[f]   neighbour f's state word with bit 30 set when it exists,
-//   nid[f]  its tile id, face[f] the priority key bits of the lowered values on
-//           face f (kInfBits: nothing lowered there),
+// Lane f < 6 holds, for face f,
+//   nb      bit 30 set when the neighbour across it exists,
+//   nid     its tile id, face the priority key bits of the lowered values on
+//           the face (kInfBits: nothing lowered there);
 //   first   the run wrote this tile's interior for the first time (sets V).
 // The tile's own state word drops R (and gains V); the RMW's return also says
 // whether the tile was activated during the run.  Lanes 0..5 activate the
 // neighbours in parallel, after that RMW when neighbours read V (order_v).
-// The live-work count changes once, by (#newly queued neighbours + requeue -
-// 1), before any push makes new items claimable, so it never under-counts.
+// The live work counts the newly queued neighbours, a requeue and this run's end
+// at once, before any push makes new items claimable, so it never under-counts.
 // `self_key` (bits of a time, kInfBits for none) requeues the tile itself with
 // at most that key: the run left points whose new values lie beyond its
 // bucket.
 // With `cont`, the lowest-key newly activated neighbour that falls in this
 // run's own bucket is not pushed: it is returned (state Q, counted live and
-// counted running in `bucket`) for this workgroup to run next, which saves a
+// counted running in this run's slot) for this workgroup to run next, which saves a
 // push, a poll and a claim on the front's critical path.  Returns that tile or
 // -1 (the run has then ended), uniform across the wave.
-__device__ __forceinline__ int publish(const Sched& s, uint64_t* tkey, uint32_t tile, int64_t bucket, bool first,
-                                       const uint32_t* nb, const uint32_t* nid,
-                                       const unsigned long long* face, bool cont = false,
-                                       unsigned long long self_key = kInfBits, bool order_v = true) {
+__device__ __forceinline__ int publish_wave(const Sched& s, uint64_t* tkey, uint32_t tile, int64_t slot, bool first,
+                                            uint32_t nb, uint32_t nid, unsigned long long face, bool cont,
+                                            unsigned long long self_key, bool order_v) {
     const int lane = threadIdx.x & 63;
+    const int64_t bucket = slot_bucket(slot);
     // lane 0 updates the tile's own word before the activations when readers
     // of the neighbours rely on V (order_v); otherwise lane 6 does it
     // alongside them
@@ -374,9 +621,9 @@ __device__ __forceinline__ int publish(const Sched& s, uint64_t* tkey, uint32_t 
     uint32_t n = 0;
     unsigned long long fk = kInfBits;
     if (lane < 6) {
-        fk = face[lane];
-        if ((nb[lane] & 0x40000000u) && fk != kInfBits) {
-            n = nid[lane];
+        fk = face;
+        if ((nb & 0x40000000u) && fk != kInfBits) {
+            n = nid;
             uint32_t old = __hip_atomic_fetch_or(s.tstate + n, kQ, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             if ((old & (kQ | kR)) == 0) {
                 want = true;
@@ -404,18 +651,15 @@ __device__ __forceinline__ int publish(const Sched& s, uint64_t* tkey, uint32_t 
         const unsigned long long cm = __ballot(cand && fk == key);
         if (cm) cl = __ffsll((long long)cm) - 1;
     }
-    if (lane == 0) {
-        const int delta = k + (requeue ? 1 : 0) - 1;
-        if (delta != 0)
-            __hip_atomic_fetch_add(s.pending, delta, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-    // Pushes into this run's own bucket leave their queued count to the one
-    // RMW below, which also ends the run (or, for a hand-on, just adds them):
-    // their cells are stored first, and the run stays counted until that RMW,
-    // so the bucket never looks drained with work of it uncounted.  Pushes to
-    // other buckets count themselves, and that completes before the RMW too.
+    if (lane == 0) pend_add(s, (uint32_t)k + (requeue ? 1u : 0u), 1u);
+    // Pushes into this run's own ring leave their queued count to the one
+    // RMW below, which also ends the run: their cells are stored first, and the
+    // run stays counted until that RMW, so the bucket never looks drained with
+    // work of it uncounted.  Pushes to other rings count themselves, and that
+    // completes before the RMW too.
+    const int ring = slot_ring(slot);
     const bool pushme = want && lane != cl;
-    const bool same = pushme && push_bucket(s, as_f64(fk), bucket) == bucket;
+    const bool same = pushme && ring_of(push_bucket(s, as_f64(fk), bucket), shard_of(n)) == ring;
     if (pushme) push_tile(s, n, as_f64(fk), bucket, !same);
     bool rq_same = false;
     if (lane == 0 && requeue) {
@@ -423,11 +667,10 @@ __device__ __forceinline__ int publish(const Sched& s, uint64_t* tkey, uint32_t 
                                             __HIP_MEMORY_SCOPE_AGENT);
         if (self_key < kb) kb = self_key;
         const double key = kb == kInfBits ? 0.0 : as_f64(kb);
-        rq_same = push_bucket(s, key, bucket) == bucket;
+        rq_same = ring_of(push_bucket(s, key, bucket), shard_of(tile)) == ring;
         push_tile(s, tile, key, bucket, !rq_same);
     }
     const uint64_t nsame = (uint64_t)__popcll(__ballot(same)) + (uint64_t)__popcll(__ballot(rq_same));
-    const int ring = (int)(bucket % s.nrings);
     if (cl >= 0) {
         if (lane == 0 && nsame) {
             stores_done();
@@ -443,12 +686,23 @@ __device__ __forceinline__ int publish(const Sched& s, uint64_t* tkey, uint32_t 
     return -1;
 }
 
+// The same with the six faces' values in memory shared by the block.
+__device__ __forceinline__ int publish(const Sched& s, uint64_t* tkey, uint32_t tile, int64_t slot, bool first,
+                                       const uint32_t* nb, const uint32_t* nid,
+                                       const unsigned long long* face, bool cont = false,
+                                       unsigned long long self_key = kInfBits, bool order_v = true) {
+    const int lane = threadIdx.x & 63;
+    const bool in = lane < 6;
+    return publish_wave(s, tkey, tile, slot, first, in ? nb[lane] : 0u, in ? nid[lane] : 0u,
+                        in ? face[lane] : kInfBits, cont, self_key, order_v);
+}
+
 // Drop a claimed tile without running it (visit cap reached).  Lane 0.
-__device__ __forceinline__ void drop_run(const Sched& s, uint32_t tile, int64_t bucket) {
+__device__ __forceinline__ void drop_run(const Sched& s, uint32_t tile, int64_t slot) {
     const uint32_t old = __hip_atomic_fetch_xor(s.tstate + tile, kR, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (old & kQ) push_tile(s, tile, 0.0, bucket);
-    else __hip_atomic_fetch_sub(s.pending, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    end_run(s, bucket);
+    pend_add(s, (old & kQ) ? 1u : 0u, 1u);
+    if (old & kQ) push_tile(s, tile, 0.0, slot_bucket(slot));
+    end_run(s, slot);
 }
 
 }  // namespace eik
