@@ -175,8 +175,7 @@ __global__ void k_src_place(ProbTable T, const int64_t* src_idx, const double* s
     long long* ti = (long long*)(t + P.pt_off + idx);
     __hip_atomic_fetch_min(ti, (long long)as_u64(-t0), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     uint32_t tile = tile_of_point<TX, TY, TZ>(P, idx);
-    uint32_t old = __hip_atomic_fetch_or(s.tstate + tile, kQ | kV, __ATOMIC_RELAXED,
-                                         __HIP_MEMORY_SCOPE_AGENT);
+    uint32_t old = __hip_atomic_fetch_or(s.tstate + tile, kQ, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (!(old & kQ)) activate_push(s, tile, t0, 0);
 }
 
@@ -436,12 +435,14 @@ __global__ void __launch_bounds__(TX * TY) k_ablate(SolveArgs A) {
         const bool in = x < P.nx && y < P.ny;
         const int64_t gi = P.pt_off + (int64_t)y * P.nx + x;
         double q = 0.0, t_in = inf64();
+        bool src = false;
         if (in) {
             bool ok;
             q = field_q(A.field[gi], P.h, P.kind, ok);
             t_in = as_f64(__hip_atomic_load((const uint64_t*)(A.t + gi), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
             if (!ok) set_flag(S, kFlagDomain);
-            if (!ok || signbit(t_in)) q = 0.0;  // a source is fixed
+            src = signbit(t_in);
+            if (!ok || src) q = 0.0;  // a source is fixed
             t_in = fabs(t_in);
         }
         sT[L] = t_in;
@@ -507,8 +508,9 @@ __global__ void __launch_bounds__(TX * TY) k_ablate(SolveArgs A) {
         if (tid == 0) phase(2);
         // ---- write back changed points, gather the faces' minima -----------
         // every lowered face value counts (not causal), a raised one with tracking
+        // and on the first run a source, which no operator lowers
         const bool chg = in && v != t_in;
-        const bool act = chg && (v < t_in || S.track);
+        const bool act = (chg && (v < t_in || S.track)) || (src && !visited);
         if (chg) tstore(A.t + gi, v);
         const bool on[4] = {lx == 0, lx == TX - 1, ly == 0, ly == TY - 1};
 #pragma unroll

@@ -149,7 +149,7 @@ struct SweepTile {
     double wx[OP == 4 ? 2 * (TX + TY + TZ) : 1];
     unsigned long long stat[9];       // as in k_ablate
     uint8_t dirty[C::NP];             // marks carried into the next sweep
-    uint8_t low[C::NP];               // lowered by this run, at C::mine()
+    uint8_t low[C::NP];               // 1: lowered by this run, at C::mine(); 2: a source on its first run
 };
 
 template <int TX, int TY, int TZ, int OP = 0, bool COUNT = false>
@@ -391,6 +391,10 @@ __global__ void __launch_bounds__((64 * SweepCfg<TX, TY, TZ>::W))
                 double m = nmin(nmin(sT[L - 1], sT[L + 1]), nmin(sT[L - C::SY], sT[L + C::SY]));
                 if (C::D3) m = nmin(m, nmin(sT[L - C::SZ], sT[L + C::SZ]));
                 if (m < sT[L]) sF[p] = 1;
+                // The first run hands a source's value to the neighbours across
+                // the faces (2: its own value is not stored): it is not lowered,
+                // and in a tile of one point nothing else is.
+                if ((st & kS) && !visited && !(sQ[p] > 0.0) && sT[L] < inf64()) sC[C::mine(p)] = 2;
             }
         }
         // The octant to sweep first: per axis, the side where more of the
@@ -567,7 +571,7 @@ __global__ void __launch_bounds__((64 * SweepCfg<TX, TY, TZ>::W))
         int upd = 0;
 #pragma unroll
         for (int j = 0; j < NPT; ++j) {
-            const bool c = sC[lane * NPT + j] != 0;  // only points in the grid are ever lowered
+            const bool c = sC[lane * NPT + j] == 1;  // only points in the grid are ever lowered
             const unsigned long long m = __ballot(c);
             if (m) {
                 const int64_t step = g0 + C::jz(j) * plane + (int64_t)C::jy(j) * P.nx + C::jx(j);

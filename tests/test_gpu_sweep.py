@@ -1,0 +1,85 @@
+"""The wave-per-tile solver and the sharded bucket rings at the sizes where they
+can go wrong: grids one point short of, at and one past a tile's edges, grids
+thinner than a tile, single tiles, a few tiles (fewer than the shards, not a
+multiple of 8), fronts from every octant and from several sides at once,
+sources on tile corners, and batches of more problems than a wave has lanes.
+Every result is bitwise the oracle's."""
+import numpy as np
+import pytest
+import torch
+
+import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+TILES = [(32, 8, 4), (16, 8, 8), (8, 8, 8), (64, 4, 4), (16, 8, 4), (8, 8, 4), (8, 4, 4),
+         (32, 32, 1), (64, 16, 1), (128, 8, 1), (16, 16, 1), (16, 8, 1)]
+
+
+@pytest.fixture(scope="module")
+def O(oracle_lib):
+    return oracle_lib
+
+
+def check(eik, O, field, src, t0=None, **kw):
+    ref = O.fmm(field, 1.0, src, t0=t0)
+    f = torch.from_numpy(field if field.shape[0] > 1 else field[0]).cuda()
+    got = eik.solve(f, 1.0, torch.from_numpy(src), t0=None if t0 is None else torch.from_numpy(t0), **kw)
+    got = got.cpu().numpy().reshape(field.shape)
+    assert np.array_equal(got.view(np.uint64), ref.reshape(field.shape).view(np.uint64)), (field.shape, kw)
+
+
+@pytest.mark.parametrize("tile", TILES)
+def test_tile_edges(gpu, O, tile):
+    rng = np.random.default_rng(sum(tile))
+    tx, ty, tz = tile
+    for d in (-1, 0, 1):
+        for e in (-1, 1):
+            nz = 1 if tz == 1 else max(tz + d, 2)
+            shape = (nz, max(2 * ty + e, 2), max(tx + d, 2))
+            f = W.random_field(shape, rng, 0.5, 5.0, block=3)
+            n = f.size
+            # the corners of the grid and of the tiles, all octants at once
+            src = np.unique(np.array([0, n - 1, shape[2] - 1, min(tx, shape[2]) - 1, rng.integers(0, n)],
+                                     dtype=np.int64))
+            for s in (src, src[-1:], src[:1]):
+                check(gpu, O, f, s, tile=tile if tz > 1 else tile[:2], delta=1.5, lookahead=3)
+
+
+@pytest.mark.parametrize("shape", [(1, 1, 1), (1, 1, 300), (1, 300, 1), (2, 2, 2), (3, 1, 200), (200, 3, 1), (9, 65, 17),
+                                   (17, 9, 130)])
+def test_thin_and_few_tiles(gpu, O, shape):
+    rng = np.random.default_rng(sum(shape))
+    f = W.random_field(shape, rng, 0.2, 3.0)
+    src = np.array([rng.integers(0, f.size)], dtype=np.int64)
+    tiles = [(16, 8, 8), (8, 4, 4)] if shape[0] > 1 else [(32, 32), (16, 8)]
+    for tile in tiles:
+        for kw in (dict(), dict(delta=0.7, lookahead=16), dict(delta=2.0, horizon=1)):
+            check(gpu, O, f, src, np.array([0.25]), tile=tile, **kw)
+
+
+def test_batch_beyond_a_wave(gpu, O):
+    """130 problems: the wave finds a tile's problem in steps of 64."""
+    rng = np.random.default_rng(8)
+    fields, srcs = [], []
+    for i in range(130):
+        f = W.random_field(tuple(int(v) for v in rng.integers(3, 19, 3)), rng, 0.5, 4.0)
+        fields.append(f)
+        srcs.append(np.array([rng.integers(0, f.size)], dtype=np.int64))
+    ts = gpu.solve_batched([torch.from_numpy(f).cuda() for f in fields], 1.0, [torch.from_numpy(s) for s in srcs],
+                           delta=0.5, tile=(8, 8, 8), lookahead=8)
+    for f, s, t in zip(fields, srcs, ts):
+        ref = O.fmm(f, 1.0, s)
+        assert np.array_equal(t.cpu().numpy().view(np.uint64), ref.reshape(f.shape).view(np.uint64)), f.shape
+
+
+def test_values_that_miss_the_window(gpu, O):
+    """Constants far below an ulp of the times, and equal minima: the short form
+    of the operator must hand these to the exact search."""
+    rng = np.random.default_rng(4)
+    f = W.random_field((9, 17, 19), rng, 1.0, 2.0)
+    f[:, 4:12, 5:14] *= 1e13
+    src = np.array([0, f.size // 2], dtype=np.int64)
+    check(gpu, O, f, src, np.array([1000.0, 1000.0]), tile=(8, 8, 8), delta=0.5, lookahead=4)
+    g = np.full((1, 40, 40), 3.0)
+    check(gpu, O, g, np.array([0, 39, 1599], dtype=np.int64), tile=(16, 16), delta=1.0)
