@@ -66,13 +66,9 @@ extern "C" {
 #define EIK_FLAG_TRACK_CHANGE 8u  /* eik_opts.flags, ablation operators only: re-activate the
                                      neighbours when a value changes, not only when it decreases
                                      (the precision section's change tracking) */
-#define EIK_FLAG_PACKED 32u       /* eik_opts.flags, with EIK_OP_DBAR: adjoints compact each
-                                     readiness pass's dirty points into a dense list
-                                     (256-thread workgroups) instead of one thread per point
-                                     (up to 1024).  Same result either way; the packed form
-                                     wins when the device is full of work (batches of
-                                     shots).  Accepted by forward solves, which have one
-                                     form (a wave per tile). */
+#define EIK_FLAG_PACKED 32u       /* eik_opts.flags, with EIK_OP_DBAR: formerly chose between two
+                                     pass structures.  Solves and adjoints now have one form (a
+                                     wave per tile), so the flag changes nothing. */
 #define EIK_FLAG_WARM_START 16u   /* eik_opts.flags, forward solves with EIK_OP_DBAR: resume from
                                      the times already in t_out instead of +inf.  They must be
                                      an upper bound of the solution at every point (>= +0, not
@@ -110,8 +106,8 @@ typedef struct {
     int32_t tile[3];         /* tile shape (x, y, z); zeros => default for ndim (3D 16x8x8,
                                 2D 32x32).  Supported: 3D 32x8x4, 16x8x8, 8x8x8, 64x4x4,
                                 16x8x4, 8x8x4, 8x4x4; 2D 32x32, 64x16, 128x8, 16x16, 16x8 */
-    int32_t grid_blocks;     /* persistent workgroups at most; 0 => fill the device (a forward
-                                solve's workgroup has several waves, each with its own tile) */
+    int32_t grid_blocks;     /* persistent workgroups at most; 0 => fill the device (a workgroup
+                                has several waves, each with its own tile) */
     int64_t max_tile_visits; /* 0 => unlimited; else stop after this many tile visits (ELIMIT) */
     uint32_t flags;          /* EIK_FLAG_* bits.  EIK_FLAG_TIME_KERNELS: record HIP events
                                 around the persistent kernel (solve or adjoint) on `stream`;
@@ -155,8 +151,8 @@ typedef struct {
                                 wall clock): [0] claiming / waiting for work, [1] staging a
                                 tile and its halo in LDS, [2] relaxing (adjoint: readiness
                                 passes), [3] write-back + publish */
-    int64_t workgroups;      /* persistent workers of the last launch: workgroups, or the waves
-                                of a forward solve, each running a tile at a time */
+    int64_t workgroups;      /* persistent workers of the last launch: waves, each running a
+                                tile at a time (ablation operators: workgroups) */
     int64_t bucket_advances; /* times the lowest open priority bucket moved on */
     int64_t handoffs;        /* runs that started on a neighbour handed on by the previous run */
     int64_t evaluations;     /* with eik_opts.work_ref: operator evaluations in the solve */

@@ -28,7 +28,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
-#include "eik_kernels.hpp"
+#include "eik_sweep.hpp"
 
 namespace eik {
 
@@ -75,15 +75,40 @@ __global__ void k_adj_prep(ProbTable T, int ntiles, const double* t, uint64_t* t
     }
 }
 
-// Queue every tile, latest first.
+// Queue every tile, latest first.  Lanes that push into the same ring do so
+// with one read-modify-write per counter for all of them (a counter's line
+// takes one about every 12 ns, and there are as many tiles as points / 1024).
 __global__ void k_adj_push_all(int ntiles, const uint64_t* tile_tmax,
                                const unsigned long long* tref_bits, Sched s) {
     const double tref = as_f64(*tref_bits);
+    const int lane = threadIdx.x & 63;
     if (blockIdx.x == 0 && threadIdx.x == 0) *s.poisoned = 0;  // rings were wiped by the reset
-    for (int tile = blockIdx.x * blockDim.x + threadIdx.x; tile < ntiles; tile += gridDim.x * blockDim.x) {
-        s.tstate[tile] = kQ;
-        pend_add(s, 1, 0);
-        push_tile(s, (uint32_t)tile, tref - as_f64(tile_tmax[tile]), 0);
+    for (int first = blockIdx.x * blockDim.x + (threadIdx.x & ~63); first < ntiles; first += gridDim.x * blockDim.x) {
+        const int tile = first + lane;
+        const bool in = tile < ntiles;
+        if (in) s.tstate[tile] = kQ;
+        const int64_t k = in ? push_bucket(s, tref - as_f64(tile_tmax[tile]), 0) : 0;
+        const int r = ring_of(k, shard_of((uint32_t)tile));
+        unsigned long long todo = __ballot(in);
+        if (lane == 0) pend_add(s, (uint32_t)__popcll(todo), 0);
+        while (todo) {
+            const int lead = __ffsll((long long)todo) - 1;
+            const int ring = __shfl(r, lead);
+            const unsigned long long same = __ballot(r == ring) & todo;
+            todo &= ~same;
+            uint32_t pos = 0;
+            if (lane == lead)
+                pos = __hip_atomic_fetch_add(ring_tail(s, ring), (uint32_t)__popcll(same), __ATOMIC_RELAXED,
+                                             __HIP_MEMORY_SCOPE_AGENT);
+            pos = __shfl(pos, lead) + (uint32_t)__popcll(same & ((1ull << lane) - 1ull));
+            if ((same >> lane) & 1ull) {
+                // nothing runs yet: every cell of an empty ring is free
+                uint64_t* cell = s.items + (size_t)ring * (s.cap_mask + 1) + (pos & s.cap_mask);
+                __hip_atomic_store(cell, ((uint64_t)(pos + 1u) << 32) | (uint32_t)tile, __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_AGENT);
+            }
+            if (lane == lead) cr_add(s, ring, (uint64_t)__popcll(same));
+        }
     }
 }
 
@@ -120,525 +145,450 @@ struct AdjArgs {
     Sched s;
 };
 
-// Registers are capped for three waves per SIMD with blocks of up to 256
-// threads (with the staging loads all in flight at once the largest tiles would
-// otherwise drop to two) and four with larger blocks (the direct form: one
-// thread per point).
-template <int TX, int TY, int TZ, int NT, bool PACK = false>
-__global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT > 256 ? 4 : 3))) k_adjoint(AdjArgs A) {
-    using C = TileCfg<TX, TY, TZ, NT>;
-    constexpr int NPT = C::NPT;
-    __shared__ double sT[C::NLDS];
-    __shared__ double sM[C::NLDS];
-    __shared__ uint8_t sP[C::NLDS];
-    __shared__ double sG[C::NP];               // dL/dt of the tile's points
-    __shared__ uint16_t sList[PACK ? C::NP : 1];  // PACK: the pass's dirty points, compacted
-    __shared__ __align__(4) uint8_t sDirty[2][C::NP];  // layout of didx()
-    __shared__ int s_cnt[2];
-    __shared__ int s_more[3];  // direct form, per pass (mod 3): some point completed with an in-tile parent
-    __shared__ int s_tile;
-    __shared__ int64_t s_slot;
-    __shared__ uint32_t s_state;
-    __shared__ uint32_t s_nb[6];
-    __shared__ uint32_t s_nid[6];
-    __shared__ unsigned long long s_face[6];
-    __shared__ unsigned int s_done;
-    __shared__ int s_next;  // tile handed on by the previous run's publish, or -1
-    // per-workgroup statistics, kept by thread 0 in LDS (not in registers) and
-    // flushed once at exit: [0..3] phase times on the 100 MHz wall clock, as in
-    // the forward solver (claim, stage, readiness passes, write + publish),
-    // [4] visits, [5] points done, [6] passes, [7] hand-offs, [8] the last
-    // phase mark
-    __shared__ unsigned long long s_stat[9];
+// One wave's tile of the adjoint in LDS.
+template <int TX, int TY, int TZ>
+struct AdjTile {
+    using C = SweepCfg<TX, TY, TZ>;
+    double t[C::NLDS];
+    double m[C::NLDS];            // mu of a finished point, dL/dt of one that is not (halo: mu)
+    unsigned long long stat[9];   // as in k_ablate
+    uint8_t par[C::NLDS];         // parent codes (bits 0-5), kDone, 0x80 a source or outside the grid
+    uint8_t dirty[C::NP];         // marks carried into the next sweep
+};
+constexpr uint32_t kDone = 0x40u;
 
-    const int tid = threadIdx.x;
-    const int lane = tid & 63;
-    const unsigned long long lanes_below = (1ull << lane) - 1ull;
-    (void)lanes_below;
+// Waves (tiles in flight) per workgroup: as many as a compute unit's LDS holds.
+template <int TX, int TY, int TZ>
+constexpr int adj_waves() {
+    return (160 * 1024 - 1024) / (int)sizeof(AdjTile<TX, TY, TZ>) < 16
+               ? (160 * 1024 - 1024) / (int)sizeof(AdjTile<TX, TY, TZ>)
+               : 16;
+}
+
+// The reverse sweep, one wave per tile in the order of the forward solver
+// (eik_sweep.hpp) turned round: the octant is the one the parents lie in, so a
+// point is mostly visited after its children, and a point that finishes marks
+// its parents, which are then mostly the next points visited.
+template <int TX, int TY, int TZ>
+__global__ void __launch_bounds__((64 * adj_waves<TX, TY, TZ>()))
+    __attribute__((amdgpu_waves_per_eu(((adj_waves<TX, TY, TZ>() + 3) / 4)))) k_adjoint(AdjArgs A) {
+    using C = SweepCfg<TX, TY, TZ>;
+    using F = Face<TX, TY, TZ>;
+    constexpr int NPT = C::NPT;
+    __shared__ AdjTile<TX, TY, TZ> s_tiles[adj_waves<TX, TY, TZ>()];
+    __shared__ GroupMail s_mail;
+    if (threadIdx.x == 0) {
+        s_mail.lock = 0;
+        s_mail.idle = 0;
+    }
+    __syncthreads();  // the waves part here; none meets another one again
+
+    const int w = uni((int)(threadIdx.x >> 6));
+    const int lane = threadIdx.x & 63;
+    double* const sT = s_tiles[w].t;
+    double* const sM = s_tiles[w].m;
+    uint8_t* const sP = s_tiles[w].par;
+    uint8_t* const sF = s_tiles[w].dirty;
+    unsigned long long* const s_stat = s_tiles[w].stat;
     const Sched& S = A.s;
     const double tref = as_f64(*A.tref_bits);
-    constexpr int PSTEP[3] = {1, TX, TX * TY};
-    constexpr int LSTEP[3] = {1, C::SY, C::SZ};
-    constexpr int NAX = C::D3 ? 3 : 2;
-    if (tid == 0) {
-        s_next = -1;
-        s_slot = 0;
+    // this lane's column in sweep order (y and z counted from the side the sweep starts at)
+    const int yy = lane % TY, zz = (lane / TY) % TZ;
+    const int xs0 = ((lane / C::NCOL) * NPT - yy - zz) & (TX - 1);  // its first point of a sweep
+    constexpr unsigned long long aheadY = C::inner(1, 1), behindY = C::inner(1, 0);
+    constexpr unsigned long long aheadZ = C::inner(2, 1), behindZ = C::inner(2, 0);
+    if (lane == 0) {
         for (int i = 0; i < 8; ++i) s_stat[i] = 0;
         s_stat[8] = wall_clock64();
     }
-
-    int32_t cur_hint = 0;  // wave 0: the window's lowest bucket as last seen
-    for (;;) {
-        if (tid < 64) {
-            int64_t slot = s_slot;
-            int tile = s_next;
-            if (tile < 0) tile = claim(S, &slot, cur_hint);
-            else if (tid == 0) ++s_stat[7];
-            if (tid == 0) {
-                s_next = -1;
-                s_tile = tile;
-                s_slot = slot;
-                if (tile >= 0) {
-                    ++s_stat[4];
-                    uint32_t st = __hip_atomic_fetch_xor(S.tstate + tile, kQ | kR, __ATOMIC_RELAXED,
-                                                         __HIP_MEMORY_SCOPE_AGENT);
-                    if ((st & (kQ | kR)) != kQ) set_flag(S, kFlagWatchdog);
-                    s_state = st;
-                }
-            }
-        }
-        __syncthreads();
-        const int tile = s_tile;
-        if (tile < 0) break;
-        const uint32_t st = s_state;
-        const bool visited = (st & kV) != 0;
-        const Prob P = prob_of_tile(A.pt, tile);
-        if (tid == 0) {
+    auto phase = [&](int i) {
+        if (lane == 0) {
             const unsigned long long now = wall_clock64();
-            s_stat[0] += now - s_stat[8];
+            s_stat[i] += now - s_stat[8];
             s_stat[8] = now;
         }
+    };
+    int32_t cur_hint = 0;
+    int64_t slot = 0;
+    int next = -1;
+    for (;;) {
+        // ---- claim (or take the tile handed on) ----------------------------
+        int tile = next;
+        if (tile < 0) tile = claim_group(S, s_mail, w, &slot, cur_hint);
+        else if (lane == 0) ++s_stat[7];
+        tile = uni(tile);
+        if (tile < 0) break;
+        uint32_t st = 0;
+        if (lane == 0) {
+            st = __hip_atomic_fetch_xor(S.tstate + tile, kQ | kR, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if ((st & (kQ | kR)) != kQ) set_flag(S, kFlagWatchdog);
+            ++s_stat[4];
+        }
+        st = (uint32_t)uni((int)st);
+        phase(0);
+        stores_done();  // the RMW has returned: every load of this run comes after it
+        next = -1;
+        const bool visited = (st & kV) != 0;
+        const Prob P = wave_prob_of_tile(A.pt, tile);
         const int tl = tile - P.tile_off;
         const int tx = tl % P.ntx, ty = (tl / P.ntx) % P.nty, tz = tl / (P.ntx * P.nty);
         const int x0 = tx * TX, y0 = ty * TY, z0 = tz * TZ;
 
-        if (tid < 6) {
-            int d = tid >> 1, side = tid & 1;
-            int nt[3] = {tx, ty, tz};
-            int lim[3] = {P.ntx, P.nty, P.ntz};
-            nt[d] += side ? 1 : -1;
-            uint32_t w = 0, nid = 0;
-            if (nt[d] >= 0 && nt[d] < lim[d]) {
-                nid = (uint32_t)(P.tile_off + (nt[2] * P.nty + nt[1]) * P.ntx + nt[0]);
-                w = ld_rlx(S.tstate + nid) | 0x40000000u;
-            }
-            s_nb[tid] = w;
-            s_nid[tid] = nid;
-            s_face[tid] = kInfBits;
-        }
-        if (tid == 0) {
-            s_done = 0u;
-            s_cnt[0] = 0;
-            s_cnt[1] = 0;
-            s_more[1] = 0;
-            s_more[2] = 0;
-        }
-
-        // stage own points and the halo: every load goes out before any is used
-        constexpr int NXF = 2 * TY * TZ, NYF = 2 * TX * TZ, NZF = C::D3 ? 2 * TX * TY : 0;
-        constexpr int NH = NXF + NYF + NZF;
-        constexpr int HPT = (NH + NT - 1) / NT;  // halo cells per thread
-        // halo cell i: its LDS index, face and global index (-1 outside the grid)
-        auto halo_cell = [&](int i, int& L, int& f) -> int64_t {
-            int lx, ly, lz;
-            if (i < NXF) {
-                int side = i / (TY * TZ), r = i % (TY * TZ);
-                ly = r % TY; lz = r / TY; lx = side ? TX : -1; f = side;
-            } else if (i < NXF + NYF) {
-                int k2 = i - NXF, side = k2 / (TX * TZ), r = k2 % (TX * TZ);
-                lx = r % TX; lz = r / TX; ly = side ? TY : -1; f = 2 + side;
-            } else {
-                int k2 = i - NXF - NYF, side = k2 / (TX * TY), r = k2 % (TX * TY);
-                lx = r % TX; ly = r / TX; lz = side ? TZ : -1; f = 4 + side;
-            }
-            L = C::lds(lx, ly, lz);
-            const int x = x0 + lx, y = y0 + ly, z = z0 + lz;
-            if (x >= 0 && x < P.nx && y >= 0 && y < P.ny && z >= 0 && z < P.nz)
-                return P.pt_off + ((int64_t)z * P.ny + y) * P.nx + x;
-            return -1;
-        };
-        bool was_done[NPT];
-        uint32_t live = 0;  // bit j: point j is in the grid, not a source, not yet done
+        // ---- stage the tile and its halo: every load goes out before any is used
+        constexpr int HB[6] = {(F::cells(0) + 63) / 64, (F::cells(1) + 63) / 64, (F::cells(2) + 63) / 64,
+                               (F::cells(3) + 63) / 64, (F::cells(4) + 63) / 64, (F::cells(5) + 63) / 64};
+        constexpr int HPT = 2 * (HB[0] + HB[2] + (C::D3 ? HB[4] : 0));  // halo cells per lane
+        const int64_t plane = (int64_t)P.ny * P.nx;
+        const int64_t g0 = P.pt_off + z0 * plane + (int64_t)y0 * P.nx + x0;  // the tile's first point
+        const int has = (tx > 0 ? 1 : 0) | (tx < P.ntx - 1 ? 2 : 0) | (ty > 0 ? 4 : 0) | (ty < P.nty - 1 ? 8 : 0) |
+                        (tz > 0 ? 16 : 0) | (tz < P.ntz - 1 ? 32 : 0);
+        const int lx0 = lane % TX, ly0 = (lane / TX) % TY, lz0 = lane / (TX * TY);
+        const int nx = P.nx - x0, ny = P.ny - y0, nz = P.nz - z0;  // points from the tile's first on
+        const bool whole = nx >= TX && ny >= TY && nz >= TZ;
+        // whether a tile and its halo span less than 4 GiB of an array
+        const bool narrow = C::D3 ? plane < (1ll << 29) / (TZ + 2) : P.nx < (1 << 29) / (TY + 2);
+        const int64_t lane_off = lz0 * plane + (int64_t)ly0 * P.nx + lx0;
+        uint32_t was = 0;  // bit j: point lane + 64 j was finished (or is outside) when the run began
         {
-            double tv[NPT], gv[NPT], mv[NPT];
-            uint8_t pv[NPT];
-            double htv[HPT], hmv[HPT];
-            uint8_t hpv[HPT];
-            uint32_t inb = 0, seed = 0;
+            double tv[NPT], gv[NPT], mv[NPT], ht[HPT], hm[HPT];
+            uint8_t pv[NPT], hp[HPT];
+            if (whole && narrow) {
+                // no bounds checks, 32-bit offsets from the corner of the halo
+                const int64_t corner = g0 - (C::D3 ? plane : 0) - P.nx - 1;
+                const double* const tb = A.t + corner;
+                const double* const gb = A.g + corner;
+                const double* const mb = A.mu + corner;
+                const uint8_t* const pb = A.par + corner;
+                const uint32_t row = (uint32_t)P.nx, pln = (uint32_t)plane;
+                auto off = [&](int lx, int ly, int lz) {
+                    return (C::D3 ? (uint32_t)(lz + 1) * pln : 0u) + (uint32_t)(ly + 1) * row + (uint32_t)(lx + 1);
+                };
+                auto ld = [&](const double* b, uint32_t o) { return *(const double*)((const char*)b + 8u * o); };
+                auto ldm = [&](uint32_t o) {
+                    return as_f64(__hip_atomic_load((const uint64_t*)((const char*)mb + 8u * o), __ATOMIC_RELAXED,
+                                                    __HIP_MEMORY_SCOPE_AGENT));
+                };
+                const uint32_t o0 = off(lx0, ly0, lz0);
 #pragma unroll
-            for (int j = 0; j < NPT; ++j) {
-                const int p = tid + j * NT;
-                const int lx = p % TX, ly = (p / TX) % TY, lz = p / (TX * TY);
-                const int x = x0 + lx, y = y0 + ly, z = z0 + lz;
-                tv[j] = inf64();
-                gv[j] = 0.0;
-                mv[j] = qnan64();
-                pv[j] = 0x80;  // outside points act as done sources
-                if (x < P.nx && y < P.ny && z < P.nz) {
-                    const int64_t gi = P.pt_off + ((int64_t)z * P.ny + y) * P.nx + x;
-                    tv[j] = A.t[gi];
-                    pv[j] = A.par[gi];
-                    gv[j] = A.g[gi];
-                    mv[j] = as_f64(__hip_atomic_load((const uint64_t*)(A.mu + gi), __ATOMIC_RELAXED,
-                                                     __HIP_MEMORY_SCOPE_AGENT));
-                    inb |= 1u << j;
+                for (int j = 0; j < NPT; ++j) {
+                    const uint32_t o = o0 + ((uint32_t)C::jz(j) * pln + (uint32_t)C::jy(j) * row + (uint32_t)C::jx(j));
+                    pv[j] = pb[o];
+                    tv[j] = ld(tb, o);
+                    gv[j] = ld(gb, o);
+                    mv[j] = ldm(o);
                 }
-            }
+                int hk = 0;
 #pragma unroll
-            for (int k = 0; k < HPT; ++k) {
-                const int i = tid + k * NT;
-                htv[k] = inf64();
-                hmv[k] = 0.0;
-                hpv[k] = 0x80;  // outside cells act as done sources
-                if (i < NH) {
-                    int L, f;
-                    const int64_t gi = halo_cell(i, L, f);
-                    if (gi >= 0) {
-                        htv[k] = A.t[gi];
-                        hpv[k] = A.par[gi];
-                        hmv[k] = as_f64(__hip_atomic_load((const uint64_t*)(A.mu + gi), __ATOMIC_RELAXED,
+                for (int f = 0; f < C::NF; ++f) {
+#pragma unroll
+                    for (int b = 0; b < HB[f]; ++b, ++hk) {
+                        const int c = lane + b * 64;
+                        ht[hk] = inf64();
+                        hm[hk] = 0.0;
+                        hp[hk] = 0x80;  // outside cells act as finished sources
+                        if (((has >> f) & 1) == 0) continue;
+                        if (F::cells(f) % 64 != 0 && c >= F::cells(f)) continue;
+                        const F e(f, c);
+                        const int s = (f & 1) ? 1 : -1;
+                        const uint32_t o = off(e.lx + (f < 2 ? s : 0), e.ly + (f >> 1 == 1 ? s : 0), e.lz + (f >= 4 ? s : 0));
+                        hp[hk] = pb[o];
+                        ht[hk] = ld(tb, o);
+                        hm[hk] = ldm(o);
+                    }
+                }
+            } else {
+#pragma unroll
+                for (int j = 0; j < NPT; ++j) {
+                    const int64_t gi = g0 + C::jz(j) * plane + (int64_t)C::jy(j) * P.nx + C::jx(j) + lane_off;
+                    pv[j] = 0x80;  // outside points act as finished sources
+                    tv[j] = inf64();
+                    gv[j] = 0.0;
+                    mv[j] = 0.0;
+                    if (!(lx0 + C::jx(j) < nx && ly0 + C::jy(j) < ny && lz0 + C::jz(j) < nz)) continue;
+                    pv[j] = A.par[gi];
+                    tv[j] = A.t[gi];
+                    gv[j] = A.g[gi];
+                    mv[j] = as_f64(__hip_atomic_load((const uint64_t*)A.mu + gi, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+                }
+                int hk = 0;
+#pragma unroll
+                for (int f = 0; f < C::NF; ++f) {
+#pragma unroll
+                    for (int b = 0; b < HB[f]; ++b, ++hk) {
+                        const int c = lane + b * 64;
+                        ht[hk] = inf64();
+                        hm[hk] = 0.0;
+                        hp[hk] = 0x80;
+                        if (((has >> f) & 1) == 0) continue;
+                        if (F::cells(f) % 64 != 0 && c >= F::cells(f)) continue;
+                        const F e(f, c);
+                        if (!(e.lx < nx && e.ly < ny && e.lz < nz)) continue;
+                        const int64_t step = f < 2 ? 1 : (f < 4 ? (int64_t)P.nx : plane);
+                        const int64_t gi = g0 + e.lz * plane + (int64_t)e.ly * P.nx + e.lx + ((f & 1) ? step : -step);
+                        hp[hk] = A.par[gi];
+                        ht[hk] = A.t[gi];
+                        hm[hk] = as_f64(__hip_atomic_load((const uint64_t*)A.mu + gi, __ATOMIC_RELAXED,
                                                           __HIP_MEMORY_SCOPE_AGENT));
                     }
                 }
             }
+            for (int i = lane; i < C::NP / 8; i += 64) ((uint64_t*)sF)[i] = 0;
 #pragma unroll
             for (int j = 0; j < NPT; ++j) {
-                const int p = tid + j * NT;
-                const int lx = p % TX, ly = (p / TX) % TY, lz = p / (TX * TY);
-                const int L = C::lds(lx, ly, lz);
-                double m = 0.0;
-                if ((inb >> j) & 1u) m = (pv[j] & 0x80) ? 0.0 : mv[j];
+                const int L = C::lds(lx0 + C::jx(j), ly0 + C::jy(j), lz0 + C::jz(j));
+                const bool src = (pv[j] & 0x80) != 0;
+                const bool done = src || !(mv[j] != mv[j]);
+                was |= (done ? 1u : 0u) << j;
                 sT[L] = tv[j];
-                sP[L] = pv[j];
-                sM[L] = m;
-                sG[p] = (inb >> j) & 1u ? gv[j] : 0.0;
-                was_done[j] = !(m != m);
-                if (((inb >> j) & 1u) && !(pv[j] & 0x80) && !was_done[j]) live |= 1u << j;
-                // first run: every point (leaves can sit anywhere); later runs:
-                // only boundary points, since nothing inside changed since the
-                // last run and readiness can only come from children across a face
-                const bool edge = lx == 0 || lx == TX - 1 || ly == 0 || ly == TY - 1 ||
-                                  (C::D3 && (lz == 0 || lz == TZ - 1));
-                if (!visited || edge) seed |= 1u << (8 * j);
+                sM[L] = src ? 0.0 : (done ? mv[j] : gv[j]);
+                sP[L] = src ? 0x80u | kDone : (pv[j] & 0x3Fu) | (done ? kDone : 0u);
             }
-            st_flags<NPT>(sDirty[0] + tid * NPT, seed);
-            st_flags<NPT>(sDirty[1] + tid * NPT, 0u);
+            wave_order();
+            // First marks of a later run: a point next to a finished child
+            // across a face (nothing inside has changed since the last run).  A
+            // first run looks at every point (leaves can sit anywhere).
+            int hk = 0;
 #pragma unroll
-            for (int k = 0; k < HPT; ++k) {
-                const int i = tid + k * NT;
-                if (i < NH) {
-                    int L, f;
-                    (void)halo_cell(i, L, f);
-                    sT[L] = htv[k];
-                    sP[L] = hpv[k];
-                    sM[L] = (hpv[k] & 0x80) ? 0.0 : hmv[k];
+            for (int f = 0; f < C::NF; ++f) {
+#pragma unroll
+                for (int b = 0; b < HB[f]; ++b, ++hk) {
+                    const int c = lane + b * 64;
+                    if (F::cells(f) % 64 == 0 || c < F::cells(f)) {
+                        const F e(f, c);
+                        const int L = e.lds();
+                        const bool src = (hp[hk] & 0x80) != 0;
+                        const bool done = src || !(hm[hk] != hm[hk]);
+                        const uint32_t p = src ? 0x80u | kDone : (hp[hk] & 0x3Fu) | (done ? kDone : 0u);
+                        sT[L + F::out(f)] = ht[hk];
+                        sM[L + F::out(f)] = src ? 0.0 : hm[hk];
+                        sP[L + F::out(f)] = p;
+                        // the minus-side neighbour is a child if its plus-side parent is the point
+                        const uint32_t want = (f & 1) ? 1u : 2u;
+                        if (done && ((p >> (2 * (f >> 1))) & 3u) == want && !(sP[L] & kDone)) sF[e.point()] = 1;
+                    }
                 }
             }
+            wave_order();
         }
-        __syncthreads();
-        if (tid == 0) {
-            const unsigned long long now = wall_clock64();
-            s_stat[1] += now - s_stat[8];
-            s_stat[8] = now;
+        // The octant: per axis, the side most parents of a sample are on.
+        int mx, my, mz = 0;
+        {
+            const uint32_t p = sP[C::lds((lane / C::NCOL) * NPT + NPT / 2, yy, zz)];
+            auto minus = [&](int k) {
+                return __popcll(__ballot(((p >> (2 * k)) & 3u) == 1u)) > __popcll(__ballot(((p >> (2 * k)) & 3u) == 2u));
+            };
+            mx = minus(0) ? TX - 1 : 0;
+            my = minus(1) ? TY - 1 : 0;
+            if (C::D3) mz = minus(2) ? TZ - 1 : 0;
         }
+        phase(1);
 
-        // Evaluate points whose children are all done, until no point is left
-        // to look at (two pass structures with the same result, as in the
-        // forward solver: PACK compacts the dirty points first).
-        int cb = 0;
-        int passes = 0;
-        if constexpr (PACK) {
-            // Evaluate points whose children are all done, until no point is left
-            // to look at.  As in the forward solver, each pass first compacts the
-            // points marked dirty into a list (per-point ballots place them, one
-            // LDS atomic per wave reserves the wave's segment), so a lane evaluates
-            // at most one point per round instead of walking all its own points.
-            // A point that becomes done marks its in-tile parents for the next
-            // pass; a point that is not ready yet is marked again by the child
-            // that completes it.
+        // ---- evaluate points whose children are all done, until none is left to look at
+        int passes = 0;  // levels with work
+        {
+            int sweeps = 0;
+            bool turn = true, all = !visited;
+            uint32_t D = 0;
+            int xs = 0, base = 0, pc = 0;
             for (;;) {
-                {
-                    uint8_t* df = sDirty[cb] + tid * NPT;
-                    const uint32_t fl = ld_flags<NPT>(df);
-                    if (fl) st_flags<NPT>(df, 0u);
-                    uint32_t m = 0;
-    #pragma unroll
-                    for (int j = 0; j < NPT; ++j) m |= ((fl >> (8 * j)) & 1u) << j;
-                    m &= live;
-                    unsigned long long B[NPT];
-                    int tot = 0;
-    #pragma unroll
-                    for (int j = 0; j < NPT; ++j) {
-                        B[j] = __ballot((m >> j) & 1u);
-                        tot += __popcll(B[j]);
+                if (turn) {
+                    const int cy = yy ^ my, cz = zz ^ mz;
+                    base = C::lds(0, cy, cz);
+                    pc = (cz * TY + cy) * TX;
+                    xs = xs0;
+                    D = 0;
+                    wave_order();
+                    if (all) {
+                        D = (1u << NPT) - 1u;
+                    } else {
+#pragma unroll
+                        for (int j = 0; j < NPT; ++j) D |= (uint32_t)sF[pc + (((xs0 + j) & (TX - 1)) ^ mx)] << j;
                     }
-                    if (tot) {
-                        int base = 0;
-                        if (lane == 0) base = atomicAdd(&s_cnt[cb], tot);
-                        base = __shfl(base, 0);
-    #pragma unroll
-                        for (int j = 0; j < NPT; ++j) {
-                            if ((m >> j) & 1u) sList[base + __popcll(B[j] & lanes_below)] = (uint16_t)(tid + j * NT);
-                            base += __popcll(B[j]);
-                        }
-                    }
+                    all = false;
+                    wave_order();
+                    for (int i = lane; i < C::NP / 8; i += 64) ((uint64_t*)sF)[i] = 0;
                 }
-                __syncthreads();
-                const int n = s_cnt[cb];
-                if (n == 0) break;
-                // the other counter was last read before the previous barrier and is
-                // next filled after the coming one
-                if (tid == 0) s_cnt[cb ^ 1] = 0;
-                for (int i = tid; i < n; i += NT) {
-                    const int p = sList[i];
-                    const int lx = p % TX, ly = (p / TX) % TY, lz = p / (TX * TY);
-                    const int L = C::lds(lx, ly, lz);
-                    // every LDS read of the point and its neighbours goes out at once
-                    const uint8_t pn = sP[L];
-                    const double mself = sM[L];
-                    const double tn = sT[L];
-                    uint8_t pm[2 * NAX];
-                    double mm[2 * NAX], tm[2 * NAX];
-    #pragma unroll
-                    for (int k = 0; k < NAX; ++k) {
-    #pragma unroll
-                        for (int side = 0; side < 2; ++side) {
-                            const int Lm = side ? L + LSTEP[k] : L - LSTEP[k];
-                            pm[2 * k + side] = sP[Lm];
-                            mm[2 * k + side] = sM[Lm];
-                            tm[2 * k + side] = sT[Lm];
+                bool quiet = false;
+                for (int k = 0; k < C::SWEEP; ++k) {
+                    unsigned long long act = __ballot(D & 1u);
+                    if (!act) {
+                        quiet = !__ballot(D != 0u);
+                        if (quiet) break;
+                        do {  // levels without a dirty point
+                            D >>= 1;
+                            ++xs;
+                            ++k;
+                            act = __ballot(D & 1u);
+                        } while (!act);
+                        xs &= TX - 1;
+                    }
+                    wave_order();
+                    ++passes;
+                    const int L = base + (xs ^ mx);
+                    constexpr int NB = C::D3 ? 6 : 4;
+                    constexpr int step[6] = {-1, 1, -C::SY, C::SY, -C::SZ, C::SZ};
+                    const uint32_t pn = sP[L];
+                    uint32_t pm[NB];
+#pragma unroll
+                    for (int i = 0; i < NB; ++i) pm[i] = sP[L + step[i]];
+                    // ready: not done, and no child (a neighbour whose parent on the
+                    // side towards the point it is) that is not
+                    unsigned long long wait = mask_eq(pn & kDone, kDone);
+#pragma unroll
+                    for (int i = 0; i < NB; ++i) {
+                        const uint32_t want = ((i & 1) ? 1u : 2u) << (2 * (i >> 1)), bits = 3u << (2 * (i >> 1));
+                        wait |= mask_eq(pm[i] & (bits | kDone), want);
+                    }
+                    unsigned long long fin = act & ~wait;
+                    unsigned long long a = 0, b = 0;
+                    if (fin) {
+                        const double tn = sT[L];
+                        double lam = sM[L], tm[NB], mm[NB];
+#pragma unroll
+                        for (int i = 0; i < NB; ++i) {
+                            tm[i] = sT[L + step[i]];
+                            mm[i] = sM[L + step[i]];
+                        }
+                        // children in neighbour order x-, x+, y-, y+, z-, z+
+#pragma unroll
+                        for (int i = 0; i < NB; ++i) {
+                            const uint32_t want = ((i & 1) ? 1u : 2u) << (2 * (i >> 1)), bits = 3u << (2 * (i >> 1));
+                            const double sum = lam + mm[i] * (tm[i] - tn);
+                            lam = in_mask(mask_eq(pm[i] & bits, want)) ? sum : lam;
+                        }
+                        unsigned long long m1[3] = {0, 0, 0}, m2[3] = {0, 0, 0};  // parent on the minus, plus side
+                        double wk[3] = {0.0, 0.0, 0.0};
+#pragma unroll
+                        for (int i = 0; i < NB / 2; ++i) {
+                            m1[i] = mask_eq(pn & (3u << (2 * i)), 1u << (2 * i));
+                            m2[i] = mask_eq(pn & (3u << (2 * i)), 2u << (2 * i));
+                            const double d = tn - (in_mask(m1[i]) ? tm[2 * i] : tm[2 * i + 1]);
+                            wk[i] = in_mask(m1[i] | m2[i]) ? d : 0.0;
+                        }
+                        double W = wk[0] + wk[1];
+                        W = W + wk[2];
+                        const double mun = lam / W;
+                        fin &= mask_ordered(mun);  // a NaN stays "not done"
+                        if (in_mask(fin)) {
+                            sM[L] = mun;
+                            sP[L] = (uint8_t)(pn | kDone);
+                        }
+                        // parents inside the tile may now be ready
+                        a = (mx ? m1[0] : m2[0]) & fin & __ballot(xs < TX - 1);
+                        b = (mx ? m2[0] : m1[0]) & fin & __ballot(xs > 0);
+                        a |= ((my ? m1[1] : m2[1]) & fin & aheadY) << 1;
+                        b |= ((my ? m2[1] : m1[1]) & fin & behindY) >> 1;
+                        if (C::D3) {
+                            a |= ((mz ? m1[2] : m2[2]) & fin & (C::NCOL < 64 ? aheadZ : ~0ull)) << TY;
+                            b |= ((mz ? m2[2] : m1[2]) & fin & (C::NCOL < 64 ? behindZ : ~0ull)) >> TY;
                         }
                     }
-                    if (!(mself != mself)) continue;  // already done
-                    bool ready = true;
-                    double lam = sG[p];
-                    // children in neighbour order x-, x+, y-, y+, z-, z+
-    #pragma unroll
-                    for (int k = 0; k < NAX; ++k) {
-    #pragma unroll
-                        for (int side = 0; side < 2; ++side) {
-                            const uint8_t pmk = pm[2 * k + side];
-                            // the minus-side neighbour is a child if its plus-side parent is n
-                            const uint32_t want = side ? 1u : 2u;
-                            if (!(pmk & 0x80) && ((pmk >> (2 * k)) & 3u) == want) {
-                                const double mmk = mm[2 * k + side];
-                                if (mmk != mmk) {
-                                    ready = false;
-                                } else {
-                                    double w = tm[2 * k + side] - tn;
-                                    lam = lam + mmk * w;
-                                }
-                            }
-                        }
-                    }
-                    if (!ready) continue;
-                    double wk[3] = {0.0, 0.0, 0.0};
-    #pragma unroll
-                    for (int k = 0; k < NAX; ++k) {
-                        const uint32_t code = (pn >> (2 * k)) & 3u;
-                        if (code == 1u) wk[k] = tn - tm[2 * k];
-                        else if (code == 2u) wk[k] = tn - tm[2 * k + 1];
-                    }
-                    double W = wk[0] + wk[1];
-                    W = W + wk[2];
-                    const double mun = lam / W;
-                    sM[L] = mun;
-                    // parents inside the tile may now be ready
-                    uint8_t* nd = sDirty[cb ^ 1];
-    #pragma unroll
-                    for (int k = 0; k < NAX; ++k) {
-                        const uint32_t code = (pn >> (2 * k)) & 3u;
-                        const int c = k == 0 ? lx : (k == 1 ? ly : lz);
-                        const int lim = k == 0 ? TX : (k == 1 ? TY : TZ);
-                        if (code == 1u && c > 0) nd[didx<NT, NPT>(p - PSTEP[k])] = 1;
-                        if (code == 2u && c < lim - 1) nd[didx<NT, NPT>(p + PSTEP[k])] = 1;
-                    }
+                    // a point behind is next visited by the lane one place back along its column
+                    if constexpr (C::NCOL < 64) b = (b >> C::NCOL) | (b << (64 - C::NCOL));
+                    D = (D >> 1) | (in_mask(a) ? 1u : 0u) | (in_mask(b) ? 1u << (NPT - 2) : 0u);
+                    xs = (xs + 1) & (TX - 1);
                 }
-                ++passes;
-                __syncthreads();
-                cb ^= 1;
-                if (passes > (1 << 20)) {
-                    if (tid == 0) set_flag(S, kFlagWatchdog);
+                if (quiet) break;
+                if (++sweeps > (1 << 20)) {
+                    if (lane == 0) set_flag(S, kFlagWatchdog);
                     break;
                 }
-            }
-        } else {
-            static_assert(PACK || NPT == 1, "the direct form has one point per thread");
-            // Direct form: each thread owns one point (NT == NP) and keeps its
-            // state in registers; only the neighbours come from LDS.  A pass
-            // evaluates each dirty point once and marks the in-tile parents of
-            // the points it completed in the other flag buffer, so one barrier
-            // per pass orders the marks before the next pass's reads.
-            {
-                const int p = tid;
-                const int lx = p % TX, ly = (p / TX) % TY, lz = p / (TX * TY);
-                const int L = C::lds(lx, ly, lz);
-                const uint8_t pn = sP[L];
-                const double tn = sT[L];
-                const double gn = sG[p];
-                bool done = was_done[0];
-                uint32_t dirty = 0;
+                // The next sweep turns round along the axes where most lanes' next
+                // dirty point has its parent behind.
+                int tx2 = 0, ty2 = 0, tz2 = 0;
                 {
-                    const uint32_t fl = ld_flags<NPT>(sDirty[0] + tid * NPT);
-                    dirty = fl & 1u & live;
-                    st_flags<NPT>(sDirty[0] + tid * NPT, 0u);
+                    wave_order();
+                    const bool any = D != 0u;
+                    const uint32_t p = sP[base + (((xs + (any ? __ffs((int)D) - 1 : 0)) & (TX - 1)) ^ mx)];
+                    auto turned = [&](int k, int m) {
+                        const int n1 = __popcll(__ballot(any && ((p >> (2 * k)) & 3u) == 1u));
+                        const int n2 = __popcll(__ballot(any && ((p >> (2 * k)) & 3u) == 2u));
+                        return m ? n2 > n1 : n1 > n2;
+                    };
+                    if (turned(0, mx)) tx2 = TX - 1;
+                    if (turned(1, my)) ty2 = TY - 1;
+                    if (C::D3 && turned(2, mz)) tz2 = TZ - 1;
                 }
-                for (;;) {
-                    if (tid == 0) s_more[(passes + 1) % 3] = 0;  // written next pass; last read two barriers ago
-                    bool marked = false;
-                    uint8_t* nd = sDirty[cb ^ 1];
-                    if (dirty && !done) {
-                        uint8_t pm[2 * NAX];
-                        double mm[2 * NAX], tm[2 * NAX];
-    #pragma unroll
-                        for (int k = 0; k < NAX; ++k) {
-    #pragma unroll
-                            for (int side = 0; side < 2; ++side) {
-                                const int Lm = side ? L + LSTEP[k] : L - LSTEP[k];
-                                pm[2 * k + side] = sP[Lm];
-                                mm[2 * k + side] = sM[Lm];
-                                tm[2 * k + side] = sT[Lm];
-                            }
-                        }
-                        bool ready = true;
-                        double lam = gn;
-                        // children in neighbour order x-, x+, y-, y+, z-, z+
-    #pragma unroll
-                        for (int k = 0; k < NAX; ++k) {
-    #pragma unroll
-                            for (int side = 0; side < 2; ++side) {
-                                const uint8_t pmk = pm[2 * k + side];
-                                // the minus-side neighbour is a child if its plus-side parent is n
-                                const uint32_t want = side ? 1u : 2u;
-                                if (!(pmk & 0x80) && ((pmk >> (2 * k)) & 3u) == want) {
-                                    const double mmk = mm[2 * k + side];
-                                    if (mmk != mmk) {
-                                        ready = false;
-                                    } else {
-                                        double w = tm[2 * k + side] - tn;
-                                        lam = lam + mmk * w;
-                                    }
-                                }
-                            }
-                        }
-                        if (ready) {
-                            double wk[3] = {0.0, 0.0, 0.0};
-    #pragma unroll
-                            for (int k = 0; k < NAX; ++k) {
-                                const uint32_t code = (pn >> (2 * k)) & 3u;
-                                if (code == 1u) wk[k] = tn - tm[2 * k];
-                                else if (code == 2u) wk[k] = tn - tm[2 * k + 1];
-                            }
-                            double W = wk[0] + wk[1];
-                            W = W + wk[2];
-                            const double mun = lam / W;
-                            sM[L] = mun;
-                            done = true;
-                            // parents inside the tile may now be ready
-    #pragma unroll
-                            for (int k = 0; k < NAX; ++k) {
-                                const uint32_t code = (pn >> (2 * k)) & 3u;
-                                const int c = k == 0 ? lx : (k == 1 ? ly : lz);
-                                const int lim = k == 0 ? TX : (k == 1 ? TY : TZ);
-                                if (code == 1u && c > 0) {
-                                    nd[didx<NT, NPT>(p - PSTEP[k])] = 1;
-                                    marked = true;
-                                }
-                                if (code == 2u && c < lim - 1) {
-                                    nd[didx<NT, NPT>(p + PSTEP[k])] = 1;
-                                    marked = true;
-                                }
-                            }
-                        }
-                    }
-                    if (__ballot(marked) && lane == 0) s_more[passes % 3] = 1;
-                    __syncthreads();
-                    const bool more = s_more[passes % 3] != 0;
-                    ++passes;
-                    if (!more) break;
-                    cb ^= 1;
-                    {
-                        uint8_t* df = sDirty[cb] + tid * NPT;
-                        const uint32_t fl = ld_flags<NPT>(df);
-                        dirty = fl & 1u & live;
-                        if (fl) st_flags<NPT>(df, 0u);
-                    }
-                    if (passes > (1 << 20)) {
-                        if (tid == 0) set_flag(S, kFlagWatchdog);
-                        break;
-                    }
+                turn = (tx2 | ty2 | tz2) != 0;
+                if (turn) {
+                    wave_order();
+#pragma unroll
+                    for (int j = 0; j < NPT; ++j)
+                        if ((D >> j) & 1u) sF[pc + (((xs + j) & (TX - 1)) ^ mx)] = 1;
+                    mx ^= tx2;
+                    my ^= ty2;
+                    mz ^= tz2;
                 }
             }
         }
+        wave_order();
+        if (lane == 0) s_stat[6] += (unsigned long long)passes;
+        phase(2);
 
-        if (tid == 0) {
-            s_stat[6] += (unsigned long long)passes;
-            const unsigned long long now = wall_clock64();
-            s_stat[2] += now - s_stat[8];
-            s_stat[8] = now;
-        }
-        // write back newly done points (first visit: every point, NaN = not done)
-        unsigned int ndone = 0;
-        double fkey[6] = {inf64(), inf64(), inf64(), inf64(), inf64(), inf64()};
-#pragma unroll
+        // ---- write back newly done points (first run: sources too), gather the faces' keys
+        int ndone = 0;
+    #pragma unroll
         for (int j = 0; j < NPT; ++j) {
-            const int p = tid + j * NT;
-            const int lx = p % TX, ly = (p / TX) % TY, lz = p / (TX * TY);
-            const int x = x0 + lx, y = y0 + ly, z = z0 + lz;
-            if (!(x < P.nx && y < P.ny && z < P.nz)) continue;
-            const int L = C::lds(lx, ly, lz);
-            const int64_t gi = P.pt_off + ((int64_t)z * P.ny + y) * P.nx + x;
-            const double mv = sM[L];
-            const bool done_now = !(mv != mv) && !was_done[j];
-            const uint8_t pn = sP[L];
-            if (done_now || !visited) {
-                __hip_atomic_store((uint64_t*)(A.mu + gi), as_u64(mv), __ATOMIC_RELAXED,
-                                   __HIP_MEMORY_SCOPE_AGENT);
+            const int L = C::lds(lx0 + C::jx(j), ly0 + C::jy(j), lz0 + C::jz(j));
+            const uint32_t p = sP[L];
+            const bool fin = (p & kDone) && !((was >> j) & 1u);
+            const bool in = whole || (lx0 + C::jx(j) < nx && ly0 + C::jy(j) < ny && lz0 + C::jz(j) < nz);
+            const bool put = fin || (!visited && (p & 0x80u) && in);
+            ndone += __popcll(__ballot(fin));
+            if (__ballot(put)) {
+                const int64_t at = g0 + C::jz(j) * plane + (int64_t)C::jy(j) * P.nx + C::jx(j);
+                if (put)
+                    __hip_atomic_store((uint64_t*)(A.mu + at) + lane_off, as_u64(sM[L]), __ATOMIC_RELAXED,
+                                       __HIP_MEMORY_SCOPE_AGENT);
             }
-            if (done_now && !(pn & 0x80)) {
-                ++ndone;
-                // a face point whose parent lies across that face unblocks the
-                // neighbour; the neighbour is keyed by the parent's own time, the
-                // earliest bucket in which that parent can be taken (its other
-                // children, later in time, are then mostly done as well)
-                if (lx == 0 && ((pn >> 0) & 3u) == 1u) fkey[0] = fmin(fkey[0], tref - sT[L - 1]);
-                if (lx == TX - 1 && ((pn >> 0) & 3u) == 2u) fkey[1] = fmin(fkey[1], tref - sT[L + 1]);
-                if (ly == 0 && ((pn >> 2) & 3u) == 1u) fkey[2] = fmin(fkey[2], tref - sT[L - C::SY]);
-                if (ly == TY - 1 && ((pn >> 2) & 3u) == 2u) fkey[3] = fmin(fkey[3], tref - sT[L + C::SY]);
-                if (C::D3) {
-                    if (lz == 0 && ((pn >> 4) & 3u) == 1u) fkey[4] = fmin(fkey[4], tref - sT[L - C::SZ]);
-                    if (lz == TZ - 1 && ((pn >> 4) & 3u) == 2u) fkey[5] = fmin(fkey[5], tref - sT[L + C::SZ]);
-                }
+            sF[lane + j * 64] = fin ? 1 : 0;
+        }
+        wave_order();
+        // A face point whose parent lies across that face unblocks the neighbour,
+        // keyed by the parent's own time, the earliest bucket in which that
+        // parent can be taken (its other children, later in time, are then mostly
+        // done as well).  The keys only order the work: floats rounded down.
+        unsigned long long face = kInfBits;
+#pragma unroll
+        for (int f = 0; f < C::NF; ++f) {
+            if (!((has >> f) & 1)) continue;
+            float fk = __uint_as_float(0x7F800000u);
+            unsigned long long any = 0;
+#pragma unroll
+            for (int b = 0; b < HB[f]; ++b) {
+                const int c = lane + b * 64;
+                const bool in = F::cells(f) % 64 == 0 || c < F::cells(f);
+                const F e(f, in ? c : 0);
+                const int L = e.lds();
+                const uint32_t want = (f & 1) ? 2u : 1u;
+                const bool on = in && sF[e.point()] != 0 && ((sP[L] >> (2 * (f >> 1))) & 3u) == want;
+                const double key = fmax(tref - sT[L + F::out(f)], 0.0);
+                fk = on ? fminf(fk, __double2float_rd(key)) : fk;
+                any |= __ballot(on);
+            }
+            if (any) {
+                const float m = __uint_as_float(wave_min_u32(__float_as_uint(fk)));
+                if (lane == f) face = as_u64((double)m);
             }
         }
-        // reduced within each wave, then one LDS atomic per wave
-#pragma unroll
-        for (int f = 0; f < 6; ++f) {
-            if (__ballot(fkey[f] < inf64())) {
-                const double m = wave_min(fkey[f]);
-                if (lane == 0) atomicMin(&s_face[f], (unsigned long long)as_u64(fmax(m, 0.0)));
+        // face neighbours x-, x+, y-, y+, z-, z+ (bit 30: the tile exists)
+        uint32_t nb = 0, nid = 0;
+        if (lane < 6) {
+            const int d = lane >> 1;
+            const int step = d == 0 ? 1 : (d == 1 ? P.ntx : P.ntx * P.nty);
+            if ((has >> lane) & 1) {
+                nid = (uint32_t)(tile + ((lane & 1) ? step : -step));
+                nb = 0x40000000u;
             }
-        }
-        {
-            unsigned int cnt = ndone;
-#pragma unroll
-            for (int off = 32; off > 0; off >>= 1) cnt += __shfl_xor(cnt, off);
-            if (cnt && lane == 0) atomicAdd(&s_done, cnt);
         }
         stores_done();
-        __syncthreads();
-
-        if (tid < 64) {
-            const int nxt = publish(S, A.tkey, (uint32_t)tile, s_slot, !visited, s_nb, s_nid, s_face, true);
-            if (tid == 0) s_next = nxt;
-        }
-        if (tid == 0) {
-            s_stat[5] += s_done;
-            const unsigned long long now = wall_clock64();
-            s_stat[3] += now - s_stat[8];
-            s_stat[8] = now;
-        }
-        __syncthreads();
+        next = uni(publish_wave(S, A.tkey, (uint32_t)tile, slot, !visited, nb, nid, face, true, kInfBits, false));
+        if (lane == 0) s_stat[5] += (unsigned long long)ndone;
+        phase(3);
     }
-    if (tid == 0) {
-        s_stat[0] += wall_clock64() - s_stat[8];
-        for (int i = 0; i < 4; ++i)
-            __hip_atomic_fetch_add(S.counters + 5 + i, s_stat[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __hip_atomic_fetch_add(S.counters + 2, s_stat[6], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __hip_atomic_fetch_add(S.counters + 10, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __hip_atomic_fetch_add(S.counters + 0, s_stat[4], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __hip_atomic_fetch_add(S.counters + 1, s_stat[5], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __hip_atomic_fetch_add(S.counters + 12, s_stat[7], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (lane == 0) {
+        phase(0);
+        flush_stats(S, s_stat);
     }
 }
 

@@ -18,7 +18,6 @@
 #define EIK_SOLVE_THREADS 1024
 #endif
 #include "eik_adjoint.hpp"
-#include "eik_sweep.hpp"
 
 using namespace eik;
 
@@ -615,18 +614,14 @@ int adjoint(Workspace& w, const std::vector<Prob>& probs, int64_t ntiles, int64_
     a.tkey = w.tkey;
     a.tref_bits = tref;
     a.s = s;
-    // two pass structures as in the forward solver: one thread per point
-    // (default) or compacted pass lists on 256-thread blocks (EIK_FLAG_PACKED)
-    constexpr int nt = solve_threads<TX, TY, TZ>();
-    constexpr int ntp = tile_threads<TX, TY, TZ>();
-    const bool pack = o && (o->flags & EIK_FLAG_PACKED);
-    const void* kern = pack ? (const void*)k_adjoint<TX, TY, TZ, ntp, true> : (const void*)k_adjoint<TX, TY, TZ, nt>;
-    const int threads = pack ? ntp : nt;
+    const void* kern = (const void*)k_adjoint<TX, TY, TZ>;
+    int threads = 64 * adj_waves<TX, TY, TZ>();
     int grid = 0;
     if ((rc = occupancy_grid(kern, threads, &grid))) return rc;
     if (o && o->grid_blocks > 0) grid = std::min(grid, o->grid_blocks);
     if ((int64_t)grid > ntiles) grid = (int)ntiles;
     if (grid < 1) grid = 1;
+    threads = (int)std::min<int64_t>(threads, 64 * ((ntiles + grid - 1) / grid));
     if ((rc = timing_begin(w, o))) return rc;
     void* kargs[] = {(void*)&a};
     HIP_TRY(hipLaunchKernel(kern, dim3(grid), dim3(threads), kargs, 0, st));

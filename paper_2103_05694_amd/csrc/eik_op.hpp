@@ -222,6 +222,8 @@ __device__ __forceinline__ double update(double x, double y, double z, double q,
 // Comparison of two doubles over the wave, as a lane mask.
 __device__ __forceinline__ unsigned long long mask_lt(double a, double b) { return __builtin_amdgcn_fcmp(a, b, 4); }
 __device__ __forceinline__ unsigned long long mask_ge(double a, double b) { return __builtin_amdgcn_fcmp(a, b, 3); }
+__device__ __forceinline__ unsigned long long mask_ordered(double a) { return __builtin_amdgcn_fcmp(a, a, 7); }
+__device__ __forceinline__ unsigned long long mask_eq(uint32_t a, uint32_t b) { return __builtin_amdgcn_uicmp(a, b, 32); }
 __device__ __forceinline__ bool in_mask(unsigned long long m) { return __builtin_amdgcn_inverse_ballot_w64(m); }
 
 // update() out of line, for the lanes its short form below cannot decide.
