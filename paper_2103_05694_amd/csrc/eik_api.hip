@@ -517,7 +517,7 @@ int forward_seq(const Bufs& b, const ProbTable& T, int64_t nsrc, int64_t ntiles,
     if (tw && (rc = timing_end(*tw, o))) return rc;
 
     if (par)
-        hipLaunchKernelGGL(k_parents, dim3(blocks_for(npts_total, kThreads, 1 << 16)), dim3(kThreads), 0,
+        hipLaunchKernelGGL(k_parents, dim3(blocks_for(npts_total, kParChunk, 1 << 16)), dim3(kParThreads), 0,
                            st, T, (long long)npts_total, (const double*)t, par);
     hipLaunchKernelGGL(k_src_unsign, dim3(blocks_for(nsrc, kThreads)), dim3(kThreads), 0, st, T, src_idx,
                        src_t0, (long long)nsrc, t);
@@ -598,10 +598,8 @@ int adjoint(Workspace& w, const std::vector<Prob>& probs, int64_t ntiles, int64_
     hipLaunchKernelGGL(k_reset, dim3(blocks_for(std::max<int64_t>(ntiles, (int64_t)kRings * kShards * w.ring_cap), kThreads, 4096)),
                        dim3(kThreads), 0, st, s, w.tkey, (int)ntiles, w.scal + kSSrcCount,
                        (long long)kRings * kShards * w.ring_cap, 0);
-    // mu := NaN (not done): a tile that has not run yet reads as not done
-    hipLaunchKernelGGL(k_fill_nan, dim3(blocks_for(npts, kThreads, 8192)), dim3(kThreads), 0, st, (long long)npts, mu);
-    hipLaunchKernelGGL((k_adj_prep<TX, TY, TZ>), dim3((unsigned)std::min<int64_t>(ntiles, 65536)), dim3(kThreads),
-                       0, st, T, (int)ntiles, t, w.tile_tmax, tref);
+    hipLaunchKernelGGL((k_adj_prep<TX, TY, TZ>), dim3(blocks_for(ntiles, 4, 2048)), dim3(kThreads), 0, st, T,
+                       (int)ntiles, t, mu, w.tile_tmax, tref);
     hipLaunchKernelGGL(k_adj_push_all, dim3(blocks_for(ntiles, kThreads, 4096)), dim3(kThreads), 0, st,
                        (int)ntiles, (const uint64_t*)w.tile_tmax, (const unsigned long long*)tref, s);
     HIP_TRY(hipGetLastError());
@@ -986,7 +984,7 @@ int eik_parents(const eik_grid* g, const double* t, int64_t nsrc, const int64_t*
     if ((rc = make_table(*w, probs, &soff, &T))) return rc;
     int64_t n = (int64_t)g->nx * g->ny * g->nz;
     hipStream_t st = (hipStream_t)stream;
-    hipLaunchKernelGGL(k_parents, dim3(blocks_for(n, kThreads, 1 << 16)), dim3(kThreads), 0, st, T,
+    hipLaunchKernelGGL(k_parents, dim3(blocks_for(n, kParChunk, 1 << 16)), dim3(kParThreads), 0, st, T,
                        (long long)n, t, parents_out);
     if (nsrc > 0)
         hipLaunchKernelGGL(k_parents_mark_src, dim3(blocks_for(nsrc, kThreads)), dim3(kThreads), 0, st,

@@ -614,38 +614,66 @@ __global__ void k_residual(Prob P, const double* field, const double* t, const u
 // upwind-parent record
 // ---------------------------------------------------------------------------
 
-// One thread per point over all problems.  Reads |t| (a set sign bit marks a
-// source while the solve's encoding is still in place: then bit 7 is written).
-__global__ void k_parents(ProbTable T, long long npts_total, const double* t, uint8_t* par) {
-    const long long stride = (long long)gridDim.x * blockDim.x;
-    for (long long g = (long long)blockIdx.x * blockDim.x + threadIdx.x; g < npts_total; g += stride) {
-        const Prob P = prob_of_point(T, g);
-        const int64_t i = g - P.pt_off;
-        const double* tp = t + P.pt_off;
-        const double ti = tp[i];
-        if (signbit(ti)) {
-            par[g] = 0x80;
-            continue;
+// The parent byte of a point with value t from its neighbours.  Reads |t|: a set
+// sign bit marks a source while the solve's encoding is still in place (then
+// bit 7 is written).  A neighbour off the grid is given as the point itself: it
+// is then no parent, and not the smaller of two of which the other is.
+__device__ __forceinline__ uint32_t parent_byte(double t, double xm, double xp, double ym, double yp, double zm,
+                                                double zp) {
+    auto code = [&](double l, double r) { return fmin(fabs(l), fabs(r)) < t ? (fabs(l) <= fabs(r) ? 1u : 2u) : 0u; };
+    const uint32_t b = code(xm, xp) | code(ym, yp) << 2 | code(zm, zp) << 4;
+    return signbit(t) ? 0x80u : b;
+}
+
+// Parents of all points of the launch, four consecutive points a thread.  Bound
+// by memory (9 B per point once the neighbours hit the caches) only if the
+// index arithmetic stays small: a block takes kParChunk consecutive points and
+// finds their problem once, and a thread divides once for four points, whose
+// rows it reads as vectors (512x512x256: 498 us with a search and three 64-bit
+// divisions per point, 345 us point by point without them).
+constexpr int kParThreads = 256, kParSteps = 4, kParChunk = 4 * kParThreads * kParSteps;
+__global__ void __launch_bounds__(kParThreads) k_parents(ProbTable T, long long npts_total, const double* t,
+                                                         uint8_t* par) {
+    // one point by the general route
+    auto single = [&](long long g) {
+        const Prob Q = prob_of_point(T, g);
+        const int64_t i = g - Q.pt_off, row = i / Q.nx, sy = Q.nx, sz = (int64_t)Q.nx * Q.ny;
+        const int x = (int)(i - row * Q.nx), y = (int)(row % Q.ny), z = (int)(row / Q.ny);
+        const double* at = t + g;
+        par[g] = (uint8_t)parent_byte(at[0], at[x > 0 ? -1 : 0], at[x < Q.nx - 1 ? 1 : 0], at[y > 0 ? -sy : 0],
+                                      at[y < Q.ny - 1 ? sy : 0], at[z > 0 ? -sz : 0], at[z < Q.nz - 1 ? sz : 0]);
+    };
+    for (long long c0 = (long long)blockIdx.x * kParChunk; c0 < npts_total; c0 += (long long)gridDim.x * kParChunk) {
+        const long long c1 = c0 + kParChunk < npts_total ? c0 + kParChunk : npts_total;
+        const Prob P = prob_of_point(T, c0);
+        const int64_t n = (int64_t)P.nx * P.ny * P.nz, sy = P.nx, sz = (int64_t)P.nx * P.ny;
+        // whole chunk in one problem, indices in 32 bits
+        const bool plain = c1 - P.pt_off <= n && n < (1ll << 31);
+#pragma unroll
+        for (int s = 0; s < kParSteps; ++s) {
+            const long long g = c0 + 4 * (s * kParThreads + (int)threadIdx.x);
+            if (g >= c1) continue;
+            const uint32_t i = (uint32_t)(g - P.pt_off), row = i / (uint32_t)P.nx;
+            const int x = (int)(i - row * (uint32_t)P.nx);
+            if (!plain || g + 4 > c1 || x + 4 > P.nx) {  // the four points are not of one row
+                for (long long k = g; k < g + 4 && k < c1; ++k) single(k);
+                continue;
+            }
+            const int z = (int)(row / (uint32_t)P.ny), y = (int)(row - (uint32_t)z * (uint32_t)P.ny);
+            const double* at = t + g;
+            double c[4], ym[4], yp[4], zm[4], zp[4];
+            __builtin_memcpy(c, at, 32);
+            const double xl = at[x > 0 ? -1 : 0], xr = at[x + 4 < P.nx ? 4 : 3];
+            __builtin_memcpy(ym, at + (y > 0 ? -sy : 0), 32);
+            __builtin_memcpy(yp, at + (y < P.ny - 1 ? sy : 0), 32);
+            __builtin_memcpy(zm, at + (z > 0 ? -sz : 0), 32);
+            __builtin_memcpy(zp, at + (z < P.nz - 1 ? sz : 0), 32);
+            uint32_t b = 0;
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                b |= parent_byte(c[k], k > 0 ? c[k - 1] : xl, k < 3 ? c[k + 1] : xr, ym[k], yp[k], zm[k], zp[k]) << (8 * k);
+            __builtin_memcpy(par + g, &b, 4);
         }
-        const int64_t x = i % P.nx, y = (i / P.nx) % P.ny, z = i / ((int64_t)P.nx * P.ny);
-        const int64_t sy = P.nx, sz = (int64_t)P.nx * P.ny;
-        uint8_t b = 0;
-        {
-            double l = x > 0 ? fabs(tp[i - 1]) : inf64();
-            double r = x < P.nx - 1 ? fabs(tp[i + 1]) : inf64();
-            if (fmin(l, r) < ti) b |= (l <= r) ? 1 : 2;
-        }
-        {
-            double l = y > 0 ? fabs(tp[i - sy]) : inf64();
-            double r = y < P.ny - 1 ? fabs(tp[i + sy]) : inf64();
-            if (fmin(l, r) < ti) b |= ((l <= r) ? 1 : 2) << 2;
-        }
-        if (P.nz > 1) {
-            double l = z > 0 ? fabs(tp[i - sz]) : inf64();
-            double r = z < P.nz - 1 ? fabs(tp[i + sz]) : inf64();
-            if (fmin(l, r) < ti) b |= ((l <= r) ? 1 : 2) << 4;
-        }
-        par[g] = b;
     }
 }
 
