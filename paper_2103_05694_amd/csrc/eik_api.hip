@@ -54,7 +54,15 @@ constexpr int kMaxLookahead = 16;
 static_assert(kMaxLookahead < kRings && kMaxLookahead < 64, "the claim window is read by one wave");
 constexpr int kScalWords = 192;
 constexpr int kTimelineCap = 1 << 16;
-constexpr int kSCur = 0, kSFlags = 128, kSPoisoned = 129, kSSrcCount = 130;
+constexpr int kSCur = 0, kSFlags = 128, kSPoisoned = 129;
+
+// The scalars and the statistics words as they lie on the device, one after the
+// other: one copy fetches a call's status.
+struct StatusWords {
+    int32_t scal[kScalWords];
+    unsigned long long counters[kCounters];
+};
+static_assert(sizeof(StatusWords) == kScalWords * sizeof(int32_t) + kCounters * sizeof(unsigned long long), "no padding");
 
 // One uploaded batch layout: the problem table (tile shape and offsets
 // included) and the source offsets, as on the host and on the device.
@@ -79,12 +87,12 @@ struct Workspace {
     uint64_t* tkey = nullptr;
     int64_t tiles_cap = 0;
     uint32_t ring_cap = 0;
-    // scalars, on separate 256-byte lines: cur, then flags / poisoned /
-    // source-list count (see the kS* offsets)
+    // scalars, on separate 256-byte lines: cur, then flags / poisoned
+    // (see the kS* offsets), and behind them the statistics words
     int32_t* scal = nullptr;
     unsigned long long* counters = nullptr;
-    int32_t* srclist = nullptr;
-    int64_t srclist_cap = 0;
+    StatusWords* status = nullptr;     // pinned host copy, filled by eik_status
+    std::mutex status_mu;
     // device problem tables of batched calls (problem list + source offsets),
     // one per distinct layout, kept until eik_release
     std::vector<Table> tables;
@@ -161,19 +169,19 @@ int get_ws(hipStream_t st, Workspace** out) {
     Workspace* w = new Workspace();
     w->device = dev;
     w->stream = st;
-    hipError_t e = hipMalloc((void**)&w->scal, kScalWords * sizeof(int32_t));
-    if (e == hipSuccess) e = hipMalloc((void**)&w->counters, kCounters * sizeof(unsigned long long));
+    hipError_t e = hipMalloc((void**)&w->scal, sizeof(StatusWords));
+    if (e == hipSuccess) e = hipHostMalloc((void**)&w->status, sizeof(StatusWords), hipHostMallocDefault);
     if (e == hipSuccess) e = hipMalloc((void**)&w->ctr, sizeof(uint32_t) * kCtrWords);
     if (e == hipSuccess) e = hipMalloc((void**)&w->timeline, sizeof(unsigned long long) * (2 + 2 * kTimelineCap));
     if (e != hipSuccess) {
         delete w;
         return fail(EIK_ENOMEM, std::string("hipMalloc failed: ") + hipGetErrorString(e));
     }
-    int32_t init[kScalWords] = {0};
-    init[kSPoisoned] = 1;  // the first reset initialises the rings
-    HIP_TRY(hipMemcpy(w->scal, init, sizeof(init), hipMemcpyHostToDevice));
+    w->counters = (unsigned long long*)(w->scal + kScalWords);
+    StatusWords init = {};
+    init.scal[kSPoisoned] = 1;  // the first reset initialises the rings
+    HIP_TRY(hipMemcpy(w->scal, &init, sizeof(init), hipMemcpyHostToDevice));
     HIP_TRY(hipMemset(w->ctr, 0, sizeof(uint32_t) * kCtrWords));
-    HIP_TRY(hipMemset(w->counters, 0, kCounters * sizeof(unsigned long long)));
     HIP_TRY(hipMemset(w->timeline, 0, sizeof(unsigned long long) * (2 + 2 * kTimelineCap)));
     g_ws[key] = w;
     *out = w;
@@ -369,7 +377,6 @@ struct Bufs {
     uint64_t* tile_aux = nullptr;   // per-tile min (warm start) or max (adjoint) time
     int32_t* scal = nullptr;
     unsigned long long* counters = nullptr;
-    int32_t* srclist = nullptr;
     unsigned long long* timeline = nullptr;
     uint32_t ring_cap = 0;
     int force_wipe = 0;             // re-initialise the rings in this call's reset
@@ -385,7 +392,6 @@ Bufs bufs_of(Workspace& w) {
     b.tile_aux = w.tile_tmax;
     b.scal = w.scal;
     b.counters = w.counters;
-    b.srclist = w.srclist;
     b.timeline = w.timeline;
     b.ring_cap = w.ring_cap;
     return b;
@@ -461,19 +467,14 @@ int forward_seq(const Bufs& b, const ProbTable& T, int64_t nsrc, int64_t ntiles,
     Sched s = make_sched(b, o);
     // the ablation operators need not settle: cap the runs unless the caller did
     if (OP != EIK_OP_DBAR && s.max_visits == 0) s.max_visits = 256 * (long long)ntiles;
-    int32_t* srccnt = b.scal + kSSrcCount;
 
-    hipLaunchKernelGGL(k_reset, dim3(blocks_for(std::max<int64_t>(ntiles, (int64_t)kRings * kShards * b.ring_cap), kThreads, 4096)),
-                       dim3(kThreads), 0, st, s, b.tkey, (int)ntiles, srccnt,
-                       (long long)kRings * kShards * b.ring_cap, b.force_wipe);
-    hipLaunchKernelGGL((k_src_mark<TX, TY, TZ>), dim3(blocks_for(nsrc, kThreads)), dim3(kThreads), 0, st,
-                       T, src_idx, src_t0, (long long)nsrc, s, b.srclist, srccnt);
+    const int64_t clear = std::max<int64_t>({ntiles, (int64_t)kRings * kShards * b.ring_cap, warm ? 0 : npts_total});
+    hipLaunchKernelGGL(k_reset, dim3(blocks_for(clear, kThreads, 8192)), dim3(kThreads), 0, st, s, b.tkey, (int)ntiles,
+                       (long long)kRings * kShards * b.ring_cap, b.force_wipe, warm ? nullptr : t,
+                       (long long)npts_total);
     if (warm)
         hipLaunchKernelGGL((k_warm_prep<TX, TY, TZ>), dim3((unsigned)std::min<int64_t>(ntiles, 65536)),
                            dim3(kThreads), 0, st, T, (int)ntiles, t, b.tile_aux, s);
-    else
-        hipLaunchKernelGGL(k_fill_inf, dim3(blocks_for(npts_total, kThreads, 8192)), dim3(kThreads), 0, st,
-                           (long long)npts_total, t);
     hipLaunchKernelGGL((k_src_place<TX, TY, TZ>), dim3(blocks_for(nsrc, kThreads)), dim3(kThreads), 0, st,
                        T, src_idx, src_t0, (long long)nsrc, t, s);
     if (warm)
@@ -517,10 +518,11 @@ int forward_seq(const Bufs& b, const ProbTable& T, int64_t nsrc, int64_t ntiles,
     if (tw && (rc = timing_end(*tw, o))) return rc;
 
     if (par)
-        hipLaunchKernelGGL(k_parents, dim3(blocks_for(npts_total, kParChunk, 1 << 16)), dim3(kParThreads), 0,
-                           st, T, (long long)npts_total, (const double*)t, par);
-    hipLaunchKernelGGL(k_src_unsign, dim3(blocks_for(nsrc, kThreads)), dim3(kThreads), 0, st, T, src_idx,
-                       src_t0, (long long)nsrc, t);
+        hipLaunchKernelGGL(k_parents<true>, dim3(blocks_for(npts_total, kParChunk, 1 << 16)), dim3(kParThreads), 0,
+                           st, T, (long long)npts_total, t, par);
+    else
+        hipLaunchKernelGGL(k_src_unsign, dim3(blocks_for(nsrc, kThreads)), dim3(kThreads), 0, st, T, src_idx,
+                           src_t0, (long long)nsrc, t);
     HIP_TRY(hipGetLastError());
     return EIK_OK;
 }
@@ -533,7 +535,6 @@ int forward(Workspace& w, const std::vector<Prob>& probs, const std::vector<int6
     int rc;
     const int64_t nsrc = src_off.back();
     if ((rc = ensure_tiles(w, ntiles))) return rc;
-    if ((rc = grow(&w.srclist, &w.srclist_cap, nsrc, w.stream))) return rc;
     ProbTable T;
     if ((rc = make_table(w, probs, &src_off, &T))) return rc;
     if ((rc = forward_seq<TX, TY, TZ, OP>(bufs_of(w), T, nsrc, ntiles, npts_total, field, src_idx, src_t0, t,
@@ -595,9 +596,9 @@ int adjoint(Workspace& w, const std::vector<Prob>& probs, int64_t ntiles, int64_
     Sched s = make_sched(bufs_of(w), o);
     s.max_visits = 0;
     unsigned long long* tref = w.counters + 4;
-    hipLaunchKernelGGL(k_reset, dim3(blocks_for(std::max<int64_t>(ntiles, (int64_t)kRings * kShards * w.ring_cap), kThreads, 4096)),
-                       dim3(kThreads), 0, st, s, w.tkey, (int)ntiles, w.scal + kSSrcCount,
-                       (long long)kRings * kShards * w.ring_cap, 0);
+    const int64_t ring_words = (int64_t)kRings * kShards * w.ring_cap;
+    hipLaunchKernelGGL(k_reset, dim3(blocks_for(std::max<int64_t>(ntiles, ring_words), kThreads, 4096)), dim3(kThreads), 0,
+                       st, s, w.tkey, (int)ntiles, (long long)ring_words, 0, (double*)nullptr, 0ll);
     hipLaunchKernelGGL((k_adj_prep<TX, TY, TZ>), dim3(blocks_for(ntiles, 4, 2048)), dim3(kThreads), 0, st, T,
                        (int)ntiles, t, mu, w.tile_tmax, tref);
     hipLaunchKernelGGL(k_adj_push_all, dim3(blocks_for(ntiles, kThreads, 4096)), dim3(kThreads), 0, st,
@@ -726,8 +727,8 @@ int build_problems(int32_t nprob, const eik_grid* grids, const int64_t* offsets,
 
 // Layout of the static scratch array, in bytes (each part 256-byte aligned):
 // the 32 bucket rings at full capacity for kNaMaxTiles tiles, their counters,
-// tile states, requeue keys, per-tile minima (warm start), the scalars, the
-// statistics words and the source-tile list.
+// tile states, requeue keys, per-tile minima (warm start), the scalars and,
+// right after them, the statistics words.
 constexpr int64_t kNaMaxTiles = 1 << 16;
 constexpr int64_t kNaMaxSrc = 1 << 16;
 constexpr size_t na_round(size_t x) { return (x + 255) / 256 * 256; }
@@ -737,9 +738,8 @@ constexpr size_t kNaTstate = kNaCtr + na_round(sizeof(uint32_t) * kCtrWords);
 constexpr size_t kNaTkey = kNaTstate + na_round(sizeof(uint32_t) * kNaMaxTiles);
 constexpr size_t kNaTmin = kNaTkey + na_round(sizeof(uint64_t) * kNaMaxTiles);
 constexpr size_t kNaScal = kNaTmin + na_round(sizeof(uint64_t) * kNaMaxTiles);
-constexpr size_t kNaCounters = kNaScal + na_round(sizeof(int32_t) * kScalWords);
-constexpr size_t kNaSrclist = kNaCounters + na_round(sizeof(unsigned long long) * kCounters);
-constexpr size_t kNaBytes = kNaSrclist + na_round(sizeof(int32_t) * kNaMaxSrc);
+constexpr size_t kNaCounters = kNaScal + sizeof(int32_t) * kScalWords;
+constexpr size_t kNaBytes = kNaCounters + na_round(sizeof(unsigned long long) * kCounters);
 
 }  // namespace
 
@@ -791,7 +791,6 @@ Bufs na_bufs(const NaDevice& d, hipStream_t st) {
     b.tile_aux = (uint64_t*)(d.ptr + kNaTmin);
     b.scal = (int32_t*)(d.ptr + kNaScal);
     b.counters = (unsigned long long*)(d.ptr + kNaCounters);
-    b.srclist = (int32_t*)(d.ptr + kNaSrclist);
     b.timeline = nullptr;
     b.ring_cap = (uint32_t)(kNaMaxTiles / kShards);
     // the first call on a device initialises the rings (their memory has
@@ -984,8 +983,8 @@ int eik_parents(const eik_grid* g, const double* t, int64_t nsrc, const int64_t*
     if ((rc = make_table(*w, probs, &soff, &T))) return rc;
     int64_t n = (int64_t)g->nx * g->ny * g->nz;
     hipStream_t st = (hipStream_t)stream;
-    hipLaunchKernelGGL(k_parents, dim3(blocks_for(n, kParChunk, 1 << 16)), dim3(kParThreads), 0, st, T,
-                       (long long)n, t, parents_out);
+    hipLaunchKernelGGL(k_parents<false>, dim3(blocks_for(n, kParChunk, 1 << 16)), dim3(kParThreads), 0, st, T,
+                       (long long)n, (double*)t, parents_out);
     if (nsrc > 0)
         hipLaunchKernelGGL(k_parents_mark_src, dim3(blocks_for(nsrc, kThreads)), dim3(kThreads), 0, st,
                            T, src_idx, (long long)nsrc, parents_out);
@@ -1090,32 +1089,33 @@ int eik_status(void* stream, eik_stats* out) {
     // The last call on this stream may have been eik_solve_noalloc, whose
     // status words live in this device's scratch array; then nothing is
     // allocated here either.
-    const int32_t* scal_src = nullptr;
-    const unsigned long long* ctr_src = nullptr;
+    const void* src = nullptr;
     int64_t last_ntiles = 0;
     {
         std::lock_guard<std::mutex> lk(g_na_mu);
         if (dev >= 0 && dev < kNaMaxDevices) {
             const NaDevice& d = g_na[dev];
             if (d.ptr && d.last_seq > 0 && d.last_stream == st && (!w || d.last_seq > w->last_seq)) {
-                scal_src = (const int32_t*)(d.ptr + kNaScal);
-                ctr_src = (const unsigned long long*)(d.ptr + kNaCounters);
+                src = d.ptr + kNaScal;
                 last_ntiles = d.last_ntiles;
             }
         }
     }
     int rc;
-    if (!scal_src) {
+    StatusWords words;
+    if (src) {
+        HIP_TRY(hipStreamSynchronize(st));
+        HIP_TRY(hipMemcpy(&words, src, sizeof(words), hipMemcpyDeviceToHost));
+    } else {
         if (!w && (rc = get_ws(st, &w))) return rc;
-        scal_src = w->scal;
-        ctr_src = w->counters;
         last_ntiles = w->last_ntiles;
+        std::lock_guard<std::mutex> lk(w->status_mu);
+        HIP_TRY(hipMemcpyAsync(w->status, w->scal, sizeof(words), hipMemcpyDeviceToHost, st));
+        HIP_TRY(hipStreamSynchronize(st));
+        words = *w->status;
     }
-    HIP_TRY(hipStreamSynchronize(st));
-    int32_t sc[kScalWords];
-    unsigned long long ctr[kCounters];
-    HIP_TRY(hipMemcpy(sc, scal_src, sizeof(sc), hipMemcpyDeviceToHost));
-    HIP_TRY(hipMemcpy(ctr, ctr_src, sizeof(ctr), hipMemcpyDeviceToHost));
+    const int32_t* sc = words.scal;
+    const unsigned long long* ctr = words.counters;
     uint32_t flags = (uint32_t)sc[kSFlags];
     int code = EIK_OK;
     if (flags & kFlagWatchdog) code = EIK_EHANG;
@@ -1191,8 +1191,7 @@ void eik_release(void) {
         (void)hipFree(w->tstate);
         (void)hipFree(w->tkey);
         (void)hipFree(w->scal);
-        (void)hipFree(w->counters);
-        (void)hipFree(w->srclist);
+        (void)hipHostFree(w->status);
         (void)hipFree(w->rw);
         for (Table& tb : w->tables) {
             (void)hipFree(tb.d_probs);

@@ -85,12 +85,14 @@ __device__ __forceinline__ double field_q(double f, double h, int kind, bool& ok
 // per-solve set-up
 // ---------------------------------------------------------------------------
 
-// Clears tile states and requeue keys, the window, counters and flags.  When the
-// previous solve on this workspace ended abnormally (`poisoned`), or the caller
-// asks for it (`force_wipe`: memory whose contents are not known yet), it also
-// re-initialises the rings so no stale slot can be taken for a new item.
-__global__ void k_reset(Sched s, uint64_t* tkey, int ntiles, int32_t* srclist_count,
-                        long long ring_words, int force_wipe) {
+// Clears tile states and requeue keys, the window, counters and flags, and (t not
+// NULL) sets t to +inf at every point: a solve starts from the upper bound +inf
+// everywhere.  When the previous solve on this workspace ended abnormally
+// (`poisoned`), or the caller asks for it (`force_wipe`: memory whose contents
+// are not known yet), it also re-initialises the rings so no stale slot can be
+// taken for a new item.
+__global__ void k_reset(Sched s, uint64_t* tkey, int ntiles, long long ring_words, int force_wipe, double* t,
+                        long long npts) {
     const bool wipe = force_wipe || __hip_atomic_load(s.poisoned, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
     const long long stride = (long long)gridDim.x * blockDim.x;
     const long long i0 = (long long)blockIdx.x * blockDim.x + threadIdx.x;
@@ -106,17 +108,18 @@ __global__ void k_reset(Sched s, uint64_t* tkey, int ntiles, int32_t* srclist_co
         for (long long i = i0; i < (long long)kPendWord; i += stride)
             s.ctr[i] = (i % kCtrStride) == kCrWord ? (uint32_t)kCountBias : 0u;
     }
+    if (i0 < kCounters) s.counters[i0] = 0ull;
+    if (i0 < kShards) *pend_word(s, (int)i0) = 0ull;
     if (i0 == 0) {
         if (s.timeline) {
             s.timeline[0] = wall_clock64();
             s.timeline[1] = 0ull;
         }
         *s.cur = 0;
-        for (int i = 0; i < kShards; ++i) *pend_word(s, i) = 0ull;
         *s.flags = 0u;
-        for (int i = 0; i < kCounters; ++i) s.counters[i] = 0ull;
-        *srclist_count = 0;
     }
+    if (t)
+        for (long long i = i0; i < npts; i += stride) t[i] = inf64();
 }
 
 template <int TX, int TY, int TZ>
@@ -130,10 +133,12 @@ __device__ __forceinline__ bool src_ok(const Prob& P, int64_t idx, double t0) {
     return idx >= 0 && idx < n && t0 >= 0.0 && t0 < inf64() && !signbit(t0);
 }
 
-// Marks source tiles (S) and lists each one once.
+// Writes each source as -t0 (the sign bit marks a fixed point during the solve;
+// min over duplicates through the signed image, where -0.0 is the smallest),
+// marks its tile (S) and queues it.
 template <int TX, int TY, int TZ>
-__global__ void k_src_mark(ProbTable T, const int64_t* src_idx, const double* src_t0, long long nsrc,
-                           Sched s, int32_t* srclist, int32_t* srclist_count) {
+__global__ void k_src_place(ProbTable T, const int64_t* src_idx, const double* src_t0, long long nsrc,
+                            double* t, Sched s) {
     long long g = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     if (g == 0) *s.poisoned = 0;  // the reset before this kernel has wiped the rings
     if (g >= nsrc) return;
@@ -144,38 +149,10 @@ __global__ void k_src_mark(ProbTable T, const int64_t* src_idx, const double* sr
         set_flag(s, kFlagBadSrc);
         return;
     }
-    uint32_t tile = tile_of_point<TX, TY, TZ>(P, idx);
-    uint32_t old = __hip_atomic_fetch_or(s.tstate + tile, kS, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (!(old & kS)) {
-        int k = __hip_atomic_fetch_add(srclist_count, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        srclist[k] = (int32_t)tile;
-    }
-}
-
-// t := +inf at every point of the launch (grid-stride), before the sources
-// are placed: a solve starts from the upper bound +inf everywhere.
-__global__ void k_fill_inf(long long npts_total, double* t) {
-    const long long stride = (long long)gridDim.x * blockDim.x;
-    for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < npts_total; i += stride)
-        t[i] = inf64();
-}
-
-// Writes each source as -t0 (the sign bit marks a fixed point during the solve;
-// min over duplicates through the signed image, where -0.0 is the smallest) and
-// queues its tile.
-template <int TX, int TY, int TZ>
-__global__ void k_src_place(ProbTable T, const int64_t* src_idx, const double* src_t0, long long nsrc,
-                            double* t, Sched s) {
-    long long g = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (g >= nsrc) return;
-    const Prob P = prob_of_source(T, g);
-    int64_t idx = src_idx[g];
-    double t0 = src_t0 ? src_t0[g] : 0.0;
-    if (!src_ok(P, idx, t0)) return;
     long long* ti = (long long*)(t + P.pt_off + idx);
     __hip_atomic_fetch_min(ti, (long long)as_u64(-t0), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     uint32_t tile = tile_of_point<TX, TY, TZ>(P, idx);
-    uint32_t old = __hip_atomic_fetch_or(s.tstate + tile, kQ, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    uint32_t old = __hip_atomic_fetch_or(s.tstate + tile, kQ | kS, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (!(old & kQ)) activate_push(s, tile, t0, 0);
 }
 
@@ -630,9 +607,11 @@ __device__ __forceinline__ uint32_t parent_byte(double t, double xm, double xp, 
 // index arithmetic stays small: a block takes kParChunk consecutive points and
 // finds their problem once, and a thread divides once for four points, whose
 // rows it reads as vectors (512x512x256: 498 us with a search and three 64-bit
-// divisions per point, 345 us point by point without them).
+// divisions per point, 345 us point by point without them).  With UNSIGN it also
+// restores +t0 at the sources; other threads read those values as |t|.
 constexpr int kParThreads = 256, kParSteps = 4, kParChunk = 4 * kParThreads * kParSteps;
-__global__ void __launch_bounds__(kParThreads) k_parents(ProbTable T, long long npts_total, const double* t,
+template <bool UNSIGN>
+__global__ void __launch_bounds__(kParThreads) k_parents(ProbTable T, long long npts_total, double* t,
                                                          uint8_t* par) {
     // one point by the general route
     auto single = [&](long long g) {
@@ -640,7 +619,9 @@ __global__ void __launch_bounds__(kParThreads) k_parents(ProbTable T, long long 
         const int64_t i = g - Q.pt_off, row = i / Q.nx, sy = Q.nx, sz = (int64_t)Q.nx * Q.ny;
         const int x = (int)(i - row * Q.nx), y = (int)(row % Q.ny), z = (int)(row / Q.ny);
         const double* at = t + g;
-        par[g] = (uint8_t)parent_byte(at[0], at[x > 0 ? -1 : 0], at[x < Q.nx - 1 ? 1 : 0], at[y > 0 ? -sy : 0],
+        const double c = at[0];
+        if (UNSIGN && signbit(c)) t[g] = fabs(c);
+        par[g] = (uint8_t)parent_byte(c, at[x > 0 ? -1 : 0], at[x < Q.nx - 1 ? 1 : 0], at[y > 0 ? -sy : 0],
                                       at[y < Q.ny - 1 ? sy : 0], at[z > 0 ? -sz : 0], at[z < Q.nz - 1 ? sz : 0]);
     };
     for (long long c0 = (long long)blockIdx.x * kParChunk; c0 < npts_total; c0 += (long long)gridDim.x * kParChunk) {
@@ -673,6 +654,11 @@ __global__ void __launch_bounds__(kParThreads) k_parents(ProbTable T, long long 
             for (int k = 0; k < 4; ++k)
                 b |= parent_byte(c[k], k > 0 ? c[k - 1] : xl, k < 3 ? c[k + 1] : xr, ym[k], yp[k], zm[k], zp[k]) << (8 * k);
             __builtin_memcpy(par + g, &b, 4);
+            if (UNSIGN && (b & 0x80808080u)) {
+#pragma unroll
+                for (int k = 0; k < 4; ++k)
+                    if (signbit(c[k])) t[g + k] = fabs(c[k]);
+            }
         }
     }
 }
