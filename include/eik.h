@@ -116,7 +116,8 @@ typedef struct {
                                 between).  EIK_FLAG_TIMELINE, EIK_FLAG_TRACK_CHANGE,
                                 EIK_FLAG_WARM_START, EIK_FLAG_PACKED: above */
     int32_t lookahead;       /* 0..16: work may be taken from the lowest non-drained bucket
-                                and this many buckets above it (0 = strict bucket order) */
+                                and this many buckets above it; a worker that finds none
+                                there in a few polls looks up to 16 buckets above it */
     int32_t horizon;         /* 0 => off; k in 1..4: a run of a tile claimed from bucket b
                                 settles only values r with floor(r / delta) < b + k and requeues
                                 the tile for the rest (no effect when delta == 0) */

@@ -90,7 +90,7 @@ __global__ void k_adj_push_all(int ntiles, const uint64_t* tile_tmax,
         const int tile = first + lane;
         const bool in = tile < ntiles;
         if (in) s.tstate[tile] = kQ;
-        const int64_t k = in ? push_bucket(s, tref - as_f64(tile_tmax[tile]), 0) : 0;
+        const int64_t k = in ? push_bucket(s, tref - as_f64(tile_tmax[tile]), 0, 0) : 0;
         const int r = ring_of(k, shard_of((uint32_t)tile));
         unsigned long long todo = __ballot(in);
         if (lane == 0) pend_add(s, (uint32_t)__popcll(todo), 0);

@@ -153,7 +153,7 @@ __global__ void k_src_place(ProbTable T, const int64_t* src_idx, const double* s
     __hip_atomic_fetch_min(ti, (long long)as_u64(-t0), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     uint32_t tile = tile_of_point<TX, TY, TZ>(P, idx);
     uint32_t old = __hip_atomic_fetch_or(s.tstate + tile, kQ | kS, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (!(old & kQ)) activate_push(s, tile, t0, 0);
+    if (!(old & kQ)) activate_push(s, tile, t0);
 }
 
 // Restores +t0 at the sources.
@@ -230,7 +230,7 @@ __global__ void k_warm_push(ProbTable T, int ntiles, const uint64_t* tile_min, S
         }
         if (key == kInfBits) continue;
         const uint32_t old = __hip_atomic_fetch_or(s.tstate + tile, kQ, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (!(old & kQ)) activate_push(s, (uint32_t)tile, as_f64(key), 0);
+        if (!(old & kQ)) activate_push(s, (uint32_t)tile, as_f64(key));
     }
 }
 

@@ -7,15 +7,15 @@
 // item is a grid tile and the scheduler is a window of NB bucket rings:
 //
 //  * a tile pushed with time t goes to bucket k = floor(t / delta), clamped to
-//    the window [cur, cur + NB); ring k mod NB holds it;
-//  * a claimer takes work only from the current bucket `cur`; `cur` moves on
-//    (to the next non-empty bucket) only once bucket `cur` is drained: nothing
-//    queued in it and no tile claimed from it still running.  This is the
-//    bucket discipline of delta-stepping: within a bucket any order and any
-//    degree of parallelism, across buckets increasing time, so the number of
-//    premature (later lowered again) tile runs stays small;
-//  * pushes happen only from tiles running in bucket `cur` (or before the
-//    solve starts), so `cur` cannot move while a push computes its ring;
+//    the window [cur, cur + NB); the rings k mod NB hold it;
+//  * a claimer takes work from the lowest bucket that has any, within a window
+//    above the current bucket `cur` (Sched::lookahead, or kWide for a workgroup
+//    that has been idle); `cur` moves on (to the next bucket that is not drained)
+//    only once nothing is queued in it and no tile claimed from it is still
+//    running.  This is the bucket discipline of delta-stepping with a window:
+//    the number of premature (later lowered again) tile runs stays small;
+//  * a push goes at most kRings - 1 buckets above the `cur` its run was claimed
+//    under, and `cur` never decreases, so no two buckets share a ring;
 //  * delta = 0 puts everything in one bucket (a plain FIFO worklist);
 //  * the operator is monotone and causal, so none of this changes results.
 //
@@ -85,6 +85,7 @@ constexpr uint32_t kQ = 1u, kR = 2u, kV = 4u, kS = 8u;
 constexpr int kCounters = 24;
 constexpr int kRings = 32;    // buckets of the window
 constexpr int kShards = 8;    // rings per bucket
+constexpr int kWide = 17, kPatience = 3;  // window of an idle workgroup, and after how many polls
 // Each ring counter (head, tail, count + running) lives in its own 256-byte
 // line, so polling one does not slow the atomics on the others.
 constexpr int kCtrPad = 64;                 // uint32 words per counter line
@@ -133,10 +134,17 @@ __device__ __forceinline__ int ring_of(int64_t bucket, int shard) {
 __device__ __forceinline__ int shard_of(uint32_t tile) {
     return (int)((tile ^ (((tile >> 3) * 0x9E3779B1u) >> 29)) & (kShards - 1));
 }
-// A run is counted as running in the ring it was claimed from, named by its
-// slot = bucket * kShards + shard; a run handed on keeps the slot.
-__device__ __forceinline__ int64_t slot_bucket(int64_t slot) { return slot / kShards; }
-__device__ __forceinline__ int slot_ring(int64_t slot) { return ring_of(slot / kShards, (int)(slot & (kShards - 1))); }
+// A run is counted as running in the ring it was claimed from.  Its slot names
+// that ring and how far above `cur` its bucket was then:
+// (bucket * kShards + shard) * kRings + (bucket - cur).  A run handed on keeps it.
+__device__ __forceinline__ int64_t make_slot(int64_t bucket, int shard, int above) {
+    return (bucket * kShards + shard) * kRings + above;
+}
+__device__ __forceinline__ int64_t slot_bucket(int64_t slot) { return slot / (kShards * kRings); }
+__device__ __forceinline__ int slot_above(int64_t slot) { return (int)(slot & (kRings - 1)); }
+__device__ __forceinline__ int slot_ring(int64_t slot) {
+    return ring_of(slot_bucket(slot), (int)(slot / kRings) & (kShards - 1));
+}
 __device__ __forceinline__ int my_shard() { return (int)(blockIdx.x & (kShards - 1)); }
 
 // Live work: per shard of the counting workgroup, the tiles ever queued (high
@@ -194,18 +202,22 @@ __device__ __forceinline__ int64_t bucket_of(const Sched& s, double t) {
     return (int64_t)k;
 }
 
-// Enqueue `tile` with time key `t`.  The caller has already counted it as live
-// work.  `base` is the bucket the pushing run was claimed from (0 before
-// the solve starts): `cur` cannot pass it while that run is live and is at least
-// base - lookahead, so buckets in [base, base + kRings - 1 - lookahead] never
-// alias a bucket behind `cur`.  With count = false the ring's queued count is
-// left to the caller, which must add it after its stores are done and before
-// it ends the run (publish folds it into the end-of-run RMW).  Single lane.
-__device__ __forceinline__ void push_tile(const Sched& s, uint32_t tile, double t, int64_t base,
-                                          bool count = true) {
+// Bucket a push with time key `t` goes to, from a run in bucket `base` that was
+// `above` buckets over `cur` when claimed (0, 0 before the solve starts): not
+// below the run's own, and not so far up that it would alias a bucket behind
+// `cur` (which never decreases).
+__device__ __forceinline__ int64_t push_bucket(const Sched& s, double t, int64_t base, int above) {
     int64_t k = bucket_of(s, t);
     if (k < base) k = base;
-    if (k > base + kRings - 1 - s.lookahead) k = base + kRings - 1 - s.lookahead;
+    if (k > base - above + kRings - 1) k = base - above + kRings - 1;
+    return k;
+}
+
+// Enqueue `tile` in bucket `k` (push_bucket).  The caller has already counted it
+// as live work.  With count = false the ring's queued count is left to the
+// caller, which must add it when or before it ends the run (publish folds it
+// into the end-of-run RMW).  Single lane.
+__device__ __forceinline__ void push_tile(const Sched& s, uint32_t tile, int64_t k, bool count = true) {
     const int r = ring_of(k, shard_of(tile));
     uint32_t pos = __hip_atomic_fetch_add(ring_tail(s, r), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     uint64_t* cell = s.items + (size_t)r * (s.cap_mask + 1) + (pos & s.cap_mask);
@@ -220,20 +232,12 @@ __device__ __forceinline__ void push_tile(const Sched& s, uint32_t tile, double 
         }
         __builtin_amdgcn_s_sleep(1);
     }
-    __hip_atomic_store(cell, ((uint64_t)(pos + 1u) << 32) | tile, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (!count) return;
     // everything this wave did before (the live-work count included) completes
-    // before the item becomes claimable
+    // before the item becomes claimable (it has: the cell was read after it);
+    // the cell itself may arrive after the count, a claimer waits for it
     stores_done();
-    cr_add(s, r, 1);
-}
-
-// Push bucket of a time key as push_tile computes it.
-__device__ __forceinline__ int64_t push_bucket(const Sched& s, double t, int64_t base) {
-    int64_t k = bucket_of(s, t);
-    if (k < base) k = base;
-    if (k > base + kRings - 1 - s.lookahead) k = base + kRings - 1 - s.lookahead;
-    return k;
+    __hip_atomic_store(cell, ((uint64_t)(pos + 1u) << 32) | tile, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (count) cr_add(s, r, 1);
 }
 
 // End of a run: its pushes were counted first (push_tile waits for that), so the
@@ -243,10 +247,10 @@ __device__ __forceinline__ void end_run(const Sched& s, int64_t slot) {
     cr_add(s, slot_ring(slot), 0ull - kRunOne);
 }
 
-// Count a newly activated tile and enqueue it.  Single lane.
-__device__ __forceinline__ void activate_push(const Sched& s, uint32_t tile, double t, int64_t base) {
+// Count a tile and enqueue it before the solve starts.  Single lane.
+__device__ __forceinline__ void activate_push(const Sched& s, uint32_t tile, double t) {
     pend_add(s, 1, 0);
-    push_tile(s, tile, t, base);
+    push_tile(s, tile, push_bucket(s, t, 0, 0));
 }
 
 // Try to take one item from ring r: one RMW counts the claimer as running and
@@ -339,6 +343,10 @@ __device__ __forceinline__ void idle_sleep(int units) {
 // line the work comes through, so where few items face many claimers only some
 // of them try: about as many as there are items.
 //
+// A workgroup that found nothing in kPatience polls looks kWide buckets far: it
+// has nothing to lose, while waiting for a bucket of few tiles to drain costs
+// every idle one a run's time (97x83x61, 616 tiles, no window: 3.4 -> 1.4 ms).
+//
 // The watchdog counts consecutive polls that saw no progress anywhere (no count
 // word, `cur` or live-work change); it fires after 2^kStallBits of them (about
 // 14 s with the back-off below), however long a valid solve takes.  kMaxSleep
@@ -348,7 +356,7 @@ __device__ __forceinline__ void idle_sleep(int units) {
 template <int kMaxSleep, int kStallBits, class Take>
 __device__ __forceinline__ int claim_with(const Sched& s, int64_t* slot, int32_t& cur_hint, Take take) {
     const int lane = threadIdx.x & 63;
-    const int win = s.lookahead + 1;
+    int win = s.lookahead + 1;
     const int own = my_shard();
     const int lj = lane / kShards, lsh = lane % kShards;
     constexpr int kCols = 64 / kShards;  // buckets read at once
@@ -444,11 +452,11 @@ __device__ __forceinline__ int claim_with(const Sched& s, int64_t* slot, int32_t
             // claimers this ring may have: this shard's workgroups, or all
             const uint32_t rivals = mine ? (gridDim.x + kShards - 1) / kShards : gridDim.x;
             rnd = (uint32_t)__builtin_amdgcn_readfirstlane((int)(rnd * 1664525u + 1013904223u));
-            if ((uint32_t)count * 2u >= rivals || (rnd >> 16) * (uint64_t)rivals < (uint64_t)count * 2u * 65536u) {
+            if ((uint32_t)count * 8u >= rivals || (rnd >> 16) * (uint64_t)rivals < (uint64_t)count * 8u * 65536u) {
                 const int64_t bucket = (int64_t)c + first + l / kShards;
                 const int got = take(ring_of(bucket, l % kShards), count);
                 if (got > 0) {
-                    *slot = bucket * kShards + l % kShards;
+                    *slot = make_slot(bucket, l % kShards, (int)(bucket - cur_hint));
                     return got;
                 }
                 if (got == -2) return -2;
@@ -461,6 +469,7 @@ __device__ __forceinline__ int claim_with(const Sched& s, int64_t* slot, int32_t
         if (__ballot(w[0] != seen)) stall = 0;  // something moved since the last poll
         seen = w[0];
         ++idle;
+        if (idle >= kPatience) win = max(win, kWide);
         if (++stall > (1ll << kStallBits)) {
             if (lane == 0) set_flag(s, kFlagWatchdog);
             return -2;
@@ -601,6 +610,7 @@ __device__ __forceinline__ int publish_wave(const Sched& s, uint64_t* tkey, uint
                                             unsigned long long self_key, bool order_v) {
     const int lane = threadIdx.x & 63;
     const int64_t bucket = slot_bucket(slot);
+    const int above = slot_above(slot);
     // lane 0 updates the tile's own word before the activations when readers
     // of the neighbours rely on V (order_v); otherwise lane 6 does it
     // alongside them
@@ -634,12 +644,13 @@ __device__ __forceinline__ int publish_wave(const Sched& s, uint64_t* tkey, uint
         }
     }
     if (!order_v) own = __shfl(own, ol);
+    const int64_t to = push_bucket(s, as_f64(fk), bucket, above);
     const bool requeue = (own & kQ) != 0;
     const unsigned long long wm = __ballot(want);
     const int k = __popcll(wm);
     int cl = -1;
     if (cont && wm) {
-        const bool cand = want && push_bucket(s, as_f64(fk), bucket) == bucket;
+        const bool cand = want && to == bucket;
         unsigned long long key = cand ? fk : ~0ull;
         // minimum over lanes 0..7 (the six face lanes)
 #pragma unroll
@@ -653,36 +664,31 @@ __device__ __forceinline__ int publish_wave(const Sched& s, uint64_t* tkey, uint
     }
     if (lane == 0) pend_add(s, (uint32_t)k + (requeue ? 1u : 0u), 1u);
     // Pushes into this run's own ring leave their queued count to the one
-    // RMW below, which also ends the run: their cells are stored first, and the
-    // run stays counted until that RMW, so the bucket never looks drained with
+    // RMW below, which also ends the run, so the bucket never looks drained with
     // work of it uncounted.  Pushes to other rings count themselves, and that
-    // completes before the RMW too.
+    // completes before the RMW.
     const int ring = slot_ring(slot);
     const bool pushme = want && lane != cl;
-    const bool same = pushme && ring_of(push_bucket(s, as_f64(fk), bucket), shard_of(n)) == ring;
-    if (pushme) push_tile(s, n, as_f64(fk), bucket, !same);
+    const bool same = pushme && ring_of(to, shard_of(n)) == ring;
+    if (pushme) push_tile(s, n, to, !same);
     bool rq_same = false;
     if (lane == 0 && requeue) {
         uint64_t kb = __hip_atomic_exchange((unsigned long long*)(tkey + tile), kInfBits, __ATOMIC_RELAXED,
                                             __HIP_MEMORY_SCOPE_AGENT);
         if (self_key < kb) kb = self_key;
-        const double key = kb == kInfBits ? 0.0 : as_f64(kb);
-        rq_same = ring_of(push_bucket(s, key, bucket), shard_of(tile)) == ring;
-        push_tile(s, tile, key, bucket, !rq_same);
+        const int64_t k = push_bucket(s, kb == kInfBits ? 0.0 : as_f64(kb), bucket, above);
+        rq_same = ring_of(k, shard_of(tile)) == ring;
+        push_tile(s, tile, k, !rq_same);
     }
     const uint64_t nsame = (uint64_t)__popcll(__ballot(same)) + (uint64_t)__popcll(__ballot(rq_same));
+    const bool away = __ballot(pushme && !same) != 0 || __ballot(lane == 0 && requeue && !rq_same) != 0;
     if (cl >= 0) {
-        if (lane == 0 && nsame) {
-            stores_done();
-            cr_add(s, ring, nsame);
-        }
+        if (lane == 0 && nsame) cr_add(s, ring, nsame);
         return (int)__shfl(n, cl);
     }
     // this run's own pushes are counted: the bucket it came from may now drain
-    if (lane == 0) {
-        stores_done();
-        cr_add(s, ring, nsame - kRunOne);
-    }
+    if (away) stores_done();
+    if (lane == 0) cr_add(s, ring, nsame - kRunOne);
     return -1;
 }
 
@@ -701,7 +707,7 @@ __device__ __forceinline__ int publish(const Sched& s, uint64_t* tkey, uint32_t 
 __device__ __forceinline__ void drop_run(const Sched& s, uint32_t tile, int64_t slot) {
     const uint32_t old = __hip_atomic_fetch_xor(s.tstate + tile, kR, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     pend_add(s, (old & kQ) ? 1u : 0u, 1u);
-    if (old & kQ) push_tile(s, tile, 0.0, slot_bucket(slot));
+    if (old & kQ) push_tile(s, tile, slot_bucket(slot));
     end_run(s, slot);
 }
 
