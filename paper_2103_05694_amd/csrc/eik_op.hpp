@@ -458,6 +458,76 @@ __device__ __forceinline__ double update_rect(const double* n, const double* w, 
     return search_slow_rect<D3>(X, Y, Z, c, A0, G, tcb);
 }
 
+// update_rect() out of line, for the lanes its short form below cannot decide.
+template <bool D3>
+__device__ __noinline__ double update_rect_rare(double xm, double xp, double ym, double yp, double zm, double zp,
+                                                double wxm, double wxp, double wym, double wyp, double wzm, double wzp,
+                                                double q, double tcur) {
+    const double n[6] = {xm, xp, ym, yp, zm, zp}, w[6] = {wxm, wxp, wym, wyp, wzm, wzp};
+    bool changed;
+    return update_rect<D3>(n, w, q * q, tcur, changed);
+}
+
+// update_rect() for the wave-per-tile solver, as update_short() for update(): no
+// clamps and no branches, the window's outcomes as lane masks.  The terms of
+// reaches_rect() as squares of a maximum with 0, which has the same bits.
+template <bool D3>
+__device__ __forceinline__ double update_rect_short(const double* n, const double* w, double q, double tc,
+                                                    unsigned long long act) {
+    const double c = q * q;
+    constexpr int NA = D3 ? 3 : 2;
+    double s0 = nmin(n[0], n[1]), v0 = n[0] <= n[1] ? w[0] : w[1];
+    double s1 = nmin(n[2], n[3]), v1 = n[2] <= n[3] ? w[2] : w[3];
+    double s2 = inf64(), v2 = 1.0;
+    pswap(s0, v0, s1, v1);
+    if constexpr (D3) {
+        s2 = nmin(n[4], n[5]);
+        v2 = n[4] <= n[5] ? w[4] : w[5];
+        pswap(s1, v1, s2, v2);
+        pswap(s0, v0, s1, v1);
+    }
+    // the axes whose minimum lies below the root (see update_rect); an axis left
+    // out gets a zero weight and a finite minimum
+    const double b1 = s1 - s0, w0 = v0 * v0;
+    const bool use1 = w0 * b1 * b1 < c;  // false for b1 = +inf
+    const double w1 = use1 ? v1 * v1 : 0.0, e1 = use1 ? b1 : 0.0;
+    double A = w0 + w1, B = w1 * e1;
+    double C = fma(B, e1, -c);
+    if constexpr (D3) {
+        const double b2 = s2 - s0, e = b2 - e1;
+        const bool use2 = use1 && fma(w0 * b2, b2, w1 * e * e) < c;
+        const double w2 = use2 ? v2 * v2 : 0.0, e2 = use2 ? b2 : 0.0, wb = w2 * e2;
+        A = A + w2;
+        B = B + wb;
+        C = fma(wb, e2, C);
+    }
+    const uint64_t G = as_u64(s0 + est_div(B + est_sqrt(fma(B, B, -A * C)), A));
+    double r[3], s[3];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        r[k] = as_f64(G - 1 + (uint64_t)k);
+        double t[3];
+#pragma unroll
+        for (int a = 0; a < NA; ++a) {
+            const double m = fmax(nmax((r[k] - n[2 * a]) * w[2 * a], (r[k] - n[2 * a + 1]) * w[2 * a + 1]), 0.0);
+            t[a] = m * m;
+        }
+        if constexpr (D3) {
+            const double lo01 = nmin(t[0], t[1]), hi01 = nmax(t[0], t[1]);
+            s[k] = (hi01 + nmax(lo01, t[2])) + nmin(lo01, t[2]);
+        } else {
+            s[k] = t[0] + t[1];
+        }
+    }
+    double res = s[1] >= c ? r[1] : r[2];
+    const unsigned long long sure = mask_lt(s0, r[0]) & mask_lt(s[0], c) & mask_ge(s[2], c);
+    if (act & ~sure) {
+        if (in_mask(act & ~sure))
+            res = update_rect_rare<D3>(n[0], n[1], n[2], n[3], n[4], n[5], w[0], w[1], w[2], w[3], w[4], w[5], q, tc);
+    }
+    return res;
+}
+
 // The paper's two explicit two-dimensional formulas (the d-tilde and d-hat
 // columns of Tables "tab:prec_1" and "tab:prec_2"), kept for the precision
 // ablation: they are not monotone in floating point, so an asynchronous solve

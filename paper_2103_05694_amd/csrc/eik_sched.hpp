@@ -552,7 +552,7 @@ __device__ __forceinline__ int claim_group(const Sched& s, GroupMail& g, int w, 
             who = (unsigned int)__builtin_amdgcn_readfirstlane(
                 (int)__hip_atomic_load(&g.idle, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP));
             // a share of what is queued, so that the blocks' waves fill evenly
-            const int want = max(1, min(__popc(who), count >> 6));
+            const int want = max(1, min(__popc(who), count >> 4));
             return try_claim_many(s, r, want, item);
         });
         int mine = got;

@@ -72,7 +72,7 @@ struct SweepCfg {
     // Points p = lane + 64 j and lanes: a step j moves every lane by the same
     // (DY, DZ) rows and planes (DX points where a row is longer than the wave).
     // Byte of point p in an array where the points of a lane (p = lane + 64 j) are adjacent.
-    __device__ static constexpr int mine(int p) { return (p % 64) * NPT + p / 64; }
+    __device__ static constexpr int mine(int p) { return (int)((((unsigned)p & 63u) * NPT) | ((unsigned)p >> 6)); }
     __device__ static constexpr int jx(int j) { return TX > 64 ? (64 * j) % TX : 0; }
     __device__ static constexpr int jy(int j) { return (64 * j / TX) % TY; }
     __device__ static constexpr int jz(int j) { return 64 * j / (TX * TY); }
@@ -478,14 +478,14 @@ __global__ void __launch_bounds__((64 * SweepCfg<TX, TY, TZ>::W))
                     if constexpr (OP == 0) {
                         r = update_short<C::D3>(nmin(xa, xb), nmin(ya, yb), nmin(za, zb), q, tc, act);
                     } else {
-                        const double nb6[6] = {mx ? xa : xb, mx ? xb : xa, my ? ya : yb, my ? yb : ya,
-                                               mz ? za : zb, mz ? zb : za};
-                        const double w6[6] = {sW[x], sW[TX + x], sW[2 * TX + cy], sW[2 * TX + TY + cy],
-                                              C::D3 ? sW[2 * (TX + TY) + cz] : 1.0,
-                                              C::D3 ? sW[2 * (TX + TY) + TZ + cz] : 1.0};
-                        bool ch;
-                        r = tc;
-                        if (in_mask(act)) r = update_rect<C::D3>(nb6, w6, q * q, tc, ch);
+                        // behind and ahead along each axis: the operator does not
+                        // tell an axis's two sides apart
+                        const double nb6[6] = {xb, xa, yb, ya, zb, za};
+                        const int ox = mx ? TX : 0, oy = 2 * TX + (my ? TY : 0), oz = 2 * (TX + TY) + (mz ? TZ : 0);
+                        const double w6[6] = {sW[ox + x], sW[(TX - ox) + x], sW[oy + cy], sW[(4 * TX + TY - oy) + cy],
+                                              C::D3 ? sW[oz + cz] : 1.0,
+                                              C::D3 ? sW[(4 * (TX + TY) + TZ - oz) + cz] : 1.0};
+                        r = update_rect_short<C::D3>(nb6, w6, q, tc, act);
                     }
                     unsigned long long chm = mask_lt(r, tc) & act;
                     if (held) {

@@ -87,6 +87,53 @@ def test_values_that_miss_the_window(gpu, O):
 
 
 @pytest.mark.parametrize("tile", TILES)
+def test_rectilinear_tile_edges(gpu, O, tile):
+    """Spacings over six decades: axes that drop out of the root, equal minima
+    with different weights on the two sides, and values that miss the window of
+    three doubles."""
+    rng = np.random.default_rng(200 + sum(tile))
+    tx, ty, tz = tile
+    axis = lambda n, lo, hi: np.cumsum(10.0 ** rng.uniform(lo, hi, n))
+    for d, lo, hi in ((-1, -0.5, 0.5), (0, -3.0, 3.0), (1, -0.1, 0.1)):
+        nz = 1 if tz == 1 else max(tz + d, 2)
+        shape = (nz, max(2 * ty - d, 2), max(tx + d, 2))
+        f = W.random_field(shape, rng, 0.5, 5.0, block=3)
+        if d == 1:
+            f[:] = 2.0  # symmetric fronts: both sides of an axis equal
+        xs, ys = axis(shape[2], lo, hi), axis(shape[1], lo, hi)
+        zs = axis(nz, lo, hi) if nz > 1 else None
+        for src in (np.array([f.size // 2], dtype=np.int64), np.array([0, f.size - 1], dtype=np.int64)):
+            t0 = np.linspace(0.0, 0.3, src.size) * float(np.ptp(xs))
+            ref = O.solve_rect(f, xs, ys, zs, src, t0=t0).reshape(shape)
+            fd = torch.from_numpy(f if nz > 1 else f[0]).cuda()
+            got = gpu.solve_rect(fd, xs, ys, zs, torch.from_numpy(src), t0=torch.from_numpy(t0),
+                                 delta=float(np.ptp(xs)) / 20, tile=tile if tz > 1 else tile[:2])
+            got = got.cpu().numpy().reshape(shape)
+            assert np.array_equal(got.view(np.uint64), ref.view(np.uint64)), (shape, d)
+
+
+@pytest.mark.parametrize("nx", [1, 2, 3, 4, 5, 7, 8, 63, 65, 257])
+def test_parent_rows(gpu, O, nx):
+    """The parent record takes four points of a row at a time: row lengths around
+    multiples of four, constant media (ties everywhere), and a batch whose chunks
+    of points start inside a row."""
+    rng = np.random.default_rng(nx)
+    fields, srcs = [], []
+    for i, shape in enumerate(((2, 9, nx), (5, 3, nx), (2, 1, nx), (4, 31, nx))):
+        f = W.random_field(shape, rng, 0.5, 2.0) if i % 2 else np.full(shape, 2.0)
+        fields.append(f)
+        srcs.append(np.unique(rng.integers(0, f.size, 2)).astype(np.int64))
+    dev = [torch.from_numpy(f).cuda() for f in fields]
+    ts, pars = gpu.solve_batched(dev, 1.0, [torch.from_numpy(s) for s in srcs], parents=True, delta=0.5, tile=(8, 8, 8))
+    for f, d, s, t, p in zip(fields, dev, srcs, ts, pars):
+        ref = O.fmm(f, 1.0, s)
+        par = O.parents(ref, s).reshape(-1)
+        assert np.array_equal(p.cpu().numpy().reshape(-1), par), f.shape
+        alone = gpu.parents_of(torch.from_numpy(ref.reshape(d.shape)).cuda(), torch.from_numpy(s))
+        assert np.array_equal(alone.cpu().numpy().reshape(-1), par), f.shape
+
+
+@pytest.mark.parametrize("tile", TILES)
 def test_adjoint_tile_edges(gpu, O, tile):
     rng = np.random.default_rng(100 + sum(tile))
     tx, ty, tz = tile
