@@ -47,7 +47,7 @@ sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0
 METRIC = "grid points solved/s & % HBM peak; batched fwd+adjoint shots/s vs plain"
-TRAFFIC_SUMMARY = os.path.join(ROOT, "profiles", "k_solve_layered_512x512x256_pmc.txt")
+TRAFFIC_SUMMARY = os.path.join(ROOT, "profiles", "k_sweep_layered_512x512x256_pmc.txt")
 
 
 def kernel_source_hash() -> str:
@@ -245,7 +245,7 @@ def bench_single(args, torch, eik, W) -> dict:
                          max(st.workgroups * kernel_ms * 1e3, 1e-9),
         "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": achieved / HBM_PEAK_GBS, "traffic": traffic,
-                     "kernel": "k_solve (persistent soft-priority tile solver)",
+                     "kernel": "k_sweep (persistent soft-priority tile solver)",
                      "algorithmic_bytes_per_launch": algo_bytes},
         "output": {"status": int(st.status), "times_sha256": digest,
                    "oracle_sha256": golden["times_sha256"] if golden else None, "validated": validated},

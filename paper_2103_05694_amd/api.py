@@ -179,7 +179,7 @@ def solve(field: torch.Tensor, h: float, sources, t0: Optional[torch.Tensor] = N
     """First-arrival times; returns t, or (t, parents) when parents=True.
     `delta` (the priority bucket width), `lookahead` (0..16: how many buckets
     past the lowest open one a claim may take work from), `horizon`, `tile`,
-    `grid_blocks` and `packed` (the compacted relaxation passes,
+    `grid_blocks` and `packed` (accepted, no effect on the solve,
     EIK_FLAG_PACKED) only schedule the work: the result is the same bits for
     every choice (the d-bar operator is monotone and causal).
 

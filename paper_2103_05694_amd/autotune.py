@@ -33,7 +33,7 @@ TILES = {3: [(16, 8, 8), (8, 8, 8), (32, 8, 4)],
 DELTA_FACTORS = (0.0, 0.25, 0.5, 1.0, 2.0, 4.0, 8.0)
 GRID_BLOCKS = (0,)       # 0 = as many workgroups as fit on the device
 HORIZONS = (0, 1, 2)     # 0 = off; k = settle values below (bucket + k) only
-PACKED = (False, True)   # relaxation passes: per-thread points, or compacted lists
+PACKED = (False, True)   # accepted and recorded; no effect on the wave-per-tile kernels
 LOOKAHEADS = (2, 4, 8, 16)  # second stage: buckets beyond the lowest a claim may take work from
 LOOKAHEAD_FACTORS = (0.0625, 0.125, 0.25, 0.5, 1.0)  # bucket widths tried with a lookahead window
 

@@ -171,7 +171,14 @@ constexpr int adj_waves() {
 // The reverse sweep, one wave per tile in the order of the forward solver
 // (eik_sweep.hpp) turned round: the octant is the one the parents lie in, so a
 // point is mostly visited after its children, and a point that finishes marks
-// its parents, which are then mostly the next points visited.
+// its parents, which are then mostly the next points visited.  Most levels only
+// look up readiness; the FP64 part runs when some lane's point is ready.
+//
+// Bound by the chain of tiles from the last points reached back to the source
+// (a level 0.45 us, a run 22 us, of which staging and publishing 10), and with
+// many problems by latency at 5 tiles of 16x8x8 in flight a compute unit.  A
+// workgroup per tile with a barrier per readiness pass took 53.5 ms for 32
+// problems of 256x256x128 (16x8x8 tiles), this takes 31.7 ms.
 template <int TX, int TY, int TZ>
 __global__ void __launch_bounds__((64 * adj_waves<TX, TY, TZ>()))
     __attribute__((amdgpu_waves_per_eu(((adj_waves<TX, TY, TZ>() + 3) / 4)))) k_adjoint(AdjArgs A) {
@@ -585,7 +592,7 @@ __global__ void __launch_bounds__((64 * adj_waves<TX, TY, TZ>()))
             }
         }
         stores_done();
-        next = uni(publish_wave(S, A.tkey, (uint32_t)tile, slot, !visited, nb, nid, face, true, kInfBits, false));
+        next = uni(publish_wave(S, A.tkey, (uint32_t)tile, slot, !visited, nb, nid, face, true, kInfBits));
         if (lane == 0) s_stat[5] += (unsigned long long)ndone;
         phase(3);
     }

@@ -289,26 +289,6 @@ __device__ __forceinline__ void flush_stats(const Sched& S, const unsigned long 
                                __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Dirty flags of the in-tile relaxation: one byte per point, stored so that
-// the NPT points of one thread (p = tid + j * NT) are adjacent and one LDS
-// access reads or clears all of them.
-template <int NT, int NPT>
-__device__ __forceinline__ int didx(int p) {
-    return (p % NT) * NPT + p / NT;
-}
-template <int NPT>
-__device__ __forceinline__ uint32_t ld_flags(const uint8_t* f) {
-    if constexpr (NPT == 4) return *(const uint32_t*)f;
-    else if constexpr (NPT == 2) return *(const uint16_t*)f;
-    else return *f;
-}
-template <int NPT>
-__device__ __forceinline__ void st_flags(uint8_t* f, uint32_t v) {
-    if constexpr (NPT == 4) *(uint32_t*)f = v;
-    else if constexpr (NPT == 2) *(uint16_t*)f = (uint16_t)v;
-    else *f = (uint8_t)v;
-}
-
 // The precision ablation (two-dimensional grids): the same schedule with the
 // explicit operators OP 1..3 of apply_op.  They assign their value, which may
 // rise, and are not causal, so every neighbour of a changed point is marked
@@ -504,10 +484,7 @@ __global__ void __launch_bounds__(TX * TY) k_ablate(SolveArgs A) {
         stores_done();
         __syncthreads();
         if (tid < 64) {
-            // runs read halos without looking at V (t starts at +inf), so V
-            // needs no ordering against the activations
-            const int nxt = publish(S, A.tkey, (uint32_t)tile, s_slot, !visited, s_nb, s_nid, s_face, true, kInfBits,
-                                    false);
+            const int nxt = publish(S, A.tkey, (uint32_t)tile, s_slot, !visited, s_nb, s_nid, s_face, true);
             if (tid == 0) s_next = nxt;
         }
         if (tid == 0) {

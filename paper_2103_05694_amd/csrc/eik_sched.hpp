@@ -27,7 +27,8 @@
 // whoever issues it (83 per us measured with 64 to 4096 waves, against 545 per
 // us over 8 lines), and while such requests queue, the loads behind them in the
 // compute unit wait too (staging a tile took 33 us instead of 3.2 us with 2816
-// waves on unsharded rings).
+// waves on unsharded rings).  The live work is one word per shard for the same
+// reason; all_done() reads them twice.
 //
 // Each ring is a bounded MPMC array of 64-bit cells (sequence << 32 | tile),
 // positions taken with fetch-add.  Its queued count and the number of runs
@@ -44,14 +45,14 @@
 // expiry.
 //
 // Tile state word (one uint32 per tile):
-//   bit0 Q  queued / needs another run       bit1 R  a workgroup is running it
+//   bit0 Q  queued / needs another run       bit1 R  a wave or workgroup is running it
 //   bit2 V  interior of t holds real values  bit3 S  contains a point source
 // Activation = fetch_or(Q) after the writer's stores completed; whoever turns an idle word
 // (no Q, no R) into Q pushes the tile.  A runner turns Q into R with an
 // acquiring RMW before it reads any t, and at the end either clears R (idle) or,
 // if Q was set meanwhile, keeps Q and pushes the tile again.  So every change
 // of a tile's halo or interior is followed by a run that starts after it, and
-// at most one workgroup runs a tile at any time.
+// at most one of them runs a tile at any time.
 //
 // Memory ordering across the 8 XCDs (each with its own L2).  Every access to
 // data another workgroup may touch concurrently -- arrival times, adjoint
@@ -60,7 +61,7 @@
 // (loads and stores coherent at device scope without any cache maintenance).
 // Ordering then only needs completion: a writer waits until its stores have
 // been acknowledged (`stores_done`, s_waitcnt vmcnt(0) in every wave, then a
-// barrier) before the RMW that hands the data over, and a reader issues its
+// barrier if several waves share the tile) before the RMW that hands the data over, and a reader issues its
 // loads only after the RMW that took the data over has returned.  This replaces
 // agent-scope release/acquire fences, whose L2 write-back / invalidate on every
 // tile visit cost far more than the visit itself.
@@ -179,9 +180,6 @@ __device__ __forceinline__ void cr_add(const Sched& s, int r, uint64_t v) {
     __hip_atomic_fetch_add(ring_cr(s, r), (unsigned long long)v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-__device__ __forceinline__ uint32_t ld_acq(uint32_t* p) {
-    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
 __device__ __forceinline__ uint32_t ld_rlx(uint32_t* p) {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
@@ -346,6 +344,8 @@ __device__ __forceinline__ void idle_sleep(int units) {
 // A workgroup that found nothing in kPatience polls looks kWide buckets far: it
 // has nothing to lose, while waiting for a bucket of few tiles to drain costs
 // every idle one a run's time (97x83x61, 616 tiles, no window: 3.4 -> 1.4 ms).
+// Further still costs more early runs than it saves waiting (13601x2801, tuned
+// window: 31 ms with 16 buckets, 65 ms with all 32).
 //
 // The watchdog counts consecutive polls that saw no progress anywhere (no count
 // word, `cur` or live-work change); it fires after 2^kStallBits of them (about
@@ -511,10 +511,6 @@ struct GroupMail {
 };
 constexpr int kNoMail = -3;
 
-__device__ __forceinline__ int lds_ld(const int* p) {
-    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-}
-
 // As claim(), for wave `w` of the block.
 __device__ __forceinline__ int claim_group(const Sched& s, GroupMail& g, int w, int64_t* slot, int32_t& cur_hint) {
     const int lane = threadIdx.x & 63;
@@ -594,7 +590,7 @@ __device__ __forceinline__ int claim_group(const Sched& s, GroupMail& g, int w, 
 //   first   the run wrote this tile's interior for the first time (sets V).
 // The tile's own state word drops R (and gains V); the RMW's return also says
 // whether the tile was activated during the run.  Lanes 0..5 activate the
-// neighbours in parallel, after that RMW when neighbours read V (order_v).
+// neighbours in parallel with it.
 // The live work counts the newly queued neighbours, a requeue and this run's end
 // at once, before any push makes new items claimable, so it never under-counts.
 // `self_key` (bits of a time, kInfBits for none) requeues the tile itself with
@@ -612,14 +608,14 @@ __device__ __forceinline__ int claim_group(const Sched& s, GroupMail& g, int w, 
 // then ended), uniform across the wave.
 __device__ __forceinline__ int publish_wave(const Sched& s, uint64_t* tkey, uint32_t tile, int64_t slot, bool first,
                                             uint32_t nb, uint32_t nid, unsigned long long face, bool cont,
-                                            unsigned long long self_key, bool order_v) {
+                                            unsigned long long self_key) {
     const int lane = threadIdx.x & 63;
     const int64_t bucket = slot_bucket(slot);
     const int above = slot_above(slot);
-    // lane 0 updates the tile's own word before the activations when readers
-    // of the neighbours rely on V (order_v); otherwise lane 6 does it
-    // alongside them
-    const int ol = order_v ? 0 : 6;
+    // lane 6 updates the tile's own word alongside the activations of lanes 0-5:
+    // runs read halos without looking at V (t starts at +inf, mu at NaN), so V
+    // needs no order against them
+    constexpr int ol = 6;
     uint32_t own = 0;
     if (lane == ol) {
         // work of this tile left for a later bucket: activate the tile itself
@@ -629,9 +625,6 @@ __device__ __forceinline__ int publish_wave(const Sched& s, uint64_t* tkey, uint
         own = __hip_atomic_fetch_xor(s.tstate + tile, kR | (first ? kV : 0u), __ATOMIC_RELAXED,
                                      __HIP_MEMORY_SCOPE_AGENT);
     }
-    // with order_v the RMW has returned here, so V is visible before any
-    // neighbour is activated
-    if (order_v) own = __shfl(own, 0);
     bool want = false;
     uint32_t n = 0;
     unsigned long long fk = kInfBits;
@@ -648,7 +641,7 @@ __device__ __forceinline__ int publish_wave(const Sched& s, uint64_t* tkey, uint
             }
         }
     }
-    if (!order_v) own = __shfl(own, ol);
+    own = __shfl(own, ol);
     const int64_t to = push_bucket(s, as_f64(fk), bucket, above);
     const bool requeue = (own & kQ) != 0;
     const unsigned long long wm = __ballot(want);
@@ -708,11 +701,11 @@ __device__ __forceinline__ int publish_wave(const Sched& s, uint64_t* tkey, uint
 __device__ __forceinline__ int publish(const Sched& s, uint64_t* tkey, uint32_t tile, int64_t slot, bool first,
                                        const uint32_t* nb, const uint32_t* nid,
                                        const unsigned long long* face, bool cont = false,
-                                       unsigned long long self_key = kInfBits, bool order_v = true) {
+                                       unsigned long long self_key = kInfBits) {
     const int lane = threadIdx.x & 63;
     const bool in = lane < 6;
     return publish_wave(s, tkey, tile, slot, first, in ? nb[lane] : 0u, in ? nid[lane] : 0u,
-                        in ? face[lane] : kInfBits, cont, self_key, order_v);
+                        in ? face[lane] : kInfBits, cont, self_key);
 }
 
 // Drop a claimed tile without running it (visit cap reached).  Lane 0.

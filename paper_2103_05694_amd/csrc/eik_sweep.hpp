@@ -1,6 +1,7 @@
-// The persistent forward solver: one wave per tile.
+// The persistent forward solver: one wave per tile, and as many waves (tiles in
+// flight) on a compute unit as its LDS holds tiles.
 //
-// A workgroup is a single wave.  It claims the approximately earliest active
+// A wave claims the approximately earliest active
 // tile (eik_sched.hpp), stages its times, the 1-cell halo and the per-point
 // constants in LDS, applies the update operator to dirty points until nothing
 // in the tile changes, writes the lowered points back and activates the face
@@ -17,6 +18,21 @@
 // (Jacobi order) re-evaluates a point each time one of its neighbours drops.
 // A level needs no barrier: the wave runs in lockstep and its LDS accesses are
 // performed in order.
+//
+// What bounds it.  The bytes it must move (16 per point) are a hundredth of its
+// time.  On a large grid with one source the front's chain of tiles does: a level
+// takes about 0.55 us, almost all of it the serial chain of the operator's FP64
+// instructions (10 cycles each), staging and publishing a tile about 10 us, and
+// most waves wait for the front (13601x2801: 300 us per run waiting, 42 us
+// running).  With many problems at once the waves are busy and the FP64 issue
+// and the LDS capacity (6 tiles of 16x8x8 a compute unit) bound it.  A workgroup
+// of 512 or 1024 threads per tile, Jacobi passes with a barrier each and rings
+// not split into shards, which this replaced, took, for the whole call: 512x512x256
+// layered, 16x8x8 tiles, 24.8 ms against 11.85 ms; 4096x4096, 16 sources, 32x32
+// tiles, 12.2 against 6.5 ms; 13601x2801, 36.7 against 29.5 ms; 32 problems of
+// 256x256x128 (forward and adjoint) 138 against 58 ms; 101x101 0.52 against
+// 0.34 ms.  More waves than tiles in LDS (waiting for a free one) made the
+// batch 4% faster and everything else 5% slower, and is not done.
 //
 // Only dirty points are evaluated.  A lane keeps the dirty bits of the points
 // it visits next in a register, bit i for the point i levels ahead.  In sweep
@@ -619,7 +635,7 @@ __global__ void __launch_bounds__((64 * SweepCfg<TX, TY, TZ>::W))
         }
         // the stores complete before the tile's faces are handed to the neighbours
         stores_done();
-        next = uni(publish_wave(S, A.tkey, (uint32_t)tile, slot, !visited, nb, nid, face, true, self_key, false));
+        next = uni(publish_wave(S, A.tkey, (uint32_t)tile, slot, !visited, nb, nid, face, true, self_key));
         if (lane == 0) {
             s_stat[5] += (unsigned long long)upd;
             s_stat[6] += (unsigned long long)passes;
