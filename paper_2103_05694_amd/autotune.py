@@ -1,6 +1,6 @@
 """Autotuner for the persistent solver's free parameters: the tile shape, the
 priority bucket width delta, the lookahead window of buckets a workgroup may
-take work from, the bucket horizon and the pass structure.
+take work from, the bucket horizon and the `packed` option (which no longer changes the kernels).
 
 The paper leaves the priority scale open and notes that the best trade-off
 between priority inversions and contention depends on hardware and input
