@@ -7,6 +7,7 @@
 #include <stdint.h>
 
 #include "eik_op.hpp"
+#include "eik_rules.hpp"
 #include "eik_sched.hpp"
 
 namespace eik {

@@ -264,8 +264,7 @@ __global__ void __launch_bounds__((64 * SweepCfg<TX, TY, TZ>::W))
         const int lx0 = lane % TX, ly0 = (lane / TX) % TY, lz0 = lane / (TX * TY);
         const int nx = P.nx - x0, ny = P.ny - y0, nz = P.nz - z0;  // points from the tile's first on
         const bool whole = nx >= TX && ny >= TY && nz >= TZ;
-        // whether a tile and its halo span less than 4 GiB of an array
-        const bool narrow = C::D3 ? plane < (1ll << 29) / (TZ + 2) : P.nx < (1 << 29) / (TY + 2);
+        const bool narrow = offsets_fit_32<TX, TY, TZ>(P.nx, plane);
         const int64_t lane_off = lz0 * plane + (int64_t)ly0 * P.nx + lx0;
         {
             double fv[NPT], tv[NPT], hv[HPT];

@@ -1,0 +1,22 @@
+// The kernels' arithmetic rules (eik_rules.hpp), compiled for the host.
+#include <stdint.h>
+
+#include "eik_rules.hpp"
+
+using namespace eik;
+
+extern "C" {
+
+#define EIK_SHAPES(X) \
+    X(32, 8, 4) X(16, 8, 8) X(8, 8, 8) X(64, 4, 4) X(16, 8, 4) X(8, 8, 4) X(8, 4, 4) \
+    X(32, 32, 1) X(64, 16, 1) X(128, 8, 1) X(16, 16, 1) X(16, 8, 1)
+
+int rule_offsets_fit_32(int tx, int ty, int tz, int64_t nx, int64_t plane) {
+#define EIK_ONE(a, b, c) \
+    if (tx == a && ty == b && tz == c) return offsets_fit_32<a, b, c>(nx, plane);
+    EIK_SHAPES(EIK_ONE)
+#undef EIK_ONE
+    return -1;
+}
+
+}  // extern "C"

@@ -1,0 +1,60 @@
+"""The rules the kernels decide by (csrc/eik_rules.hpp), compiled for the host
+and checked at their limits."""
+import ctypes
+import os
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2103_05694_amd", "csrc")
+TILES = [(32, 8, 4), (16, 8, 8), (8, 8, 8), (64, 4, 4), (16, 8, 4), (8, 8, 4), (8, 4, 4),
+         (32, 32, 1), (64, 16, 1), (128, 8, 1), (16, 16, 1), (16, 8, 1)]
+
+
+@pytest.fixture(scope="module")
+def R(tmp_path_factory):
+    out = str(tmp_path_factory.mktemp("rules") / "rules.so")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-shared", "-fPIC", "-I", CSRC, "-o", out,
+                    os.path.join(ROOT, "tests", "rules_host.cpp")], check=True)
+    lib = ctypes.CDLL(out)
+    lib.rule_offsets_fit_32.argtypes = [ctypes.c_int] * 3 + [ctypes.c_int64] * 2
+    return lib
+
+
+def furthest(tile, nx, ny):
+    """Largest byte offset from the halo's corner that a whole tile with all its
+    neighbours reads (the y+ halo exists only where rows go on behind the tile)."""
+    tx, ty, tz = tile
+    plane = nx * ny
+    cell = lambda x, y, z: (z + 1) * plane * (tz > 1) + (y + 1) * nx + x + 1
+    far = [cell(tx - 1, ty - 1, tz - 1)]
+    if nx > tx:
+        far.append(cell(tx, ty - 1, tz - 1))
+    if ny > ty:
+        far.append(cell(tx - 1, ty, tz - 1))
+    if tz > 1:
+        far.append(cell(tx - 1, ty - 1, tz))
+    return 8 * max(far)
+
+
+@pytest.mark.parametrize("tile", TILES)
+def test_offsets_that_fit_do_not_wrap(R, tile):
+    tx, ty, tz = tile
+    fits = lambda nx, ny: R.rule_offsets_fit_32(*tile, nx, nx * ny)
+    for ny in sorted({ty, ty + 1, 2 * ty, 1000}):
+        edge = (1 << 29) // (ny * (tz + 2) if tz > 1 else ty + 2)
+        for nx in range(max(edge - 200, tx), edge + 200):
+            if fits(nx, ny):
+                assert furthest(tile, nx, ny) < 1 << 32, (tile, nx, ny)
+        # not so strict that large ordinary grids are refused
+        assert fits(edge * 3 // 4, ny), (tile, ny)
+    assert fits(4096, 4096 if tz > 1 else 1 << 20)
+
+
+def test_planes_that_used_to_wrap(R):
+    """Rows as many as the tile has: the far corner of the z+ halo at or past 4 GiB."""
+    for tile, nx, ny in (((64, 4, 4), 22369621, 4), ((32, 8, 4), 11184810, 8), ((8, 4, 4), 22369621, 4)):
+        assert furthest(tile, nx, ny) >= 1 << 32
+        assert nx * ny < (1 << 29) // (tile[2] + 2)   # what the bound once was
+        assert not R.rule_offsets_fit_32(*tile, nx, nx * ny)
