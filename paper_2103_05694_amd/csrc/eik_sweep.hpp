@@ -164,8 +164,8 @@ struct SweepTile {
     // rectilinear grids: reciprocal spacings [x- | x+ | y- | y+ | z- | z+] over the tile's coordinates
     double wx[OP == 4 ? 2 * (TX + TY + TZ) : 1];
     unsigned long long stat[9];       // as in k_ablate
-    uint8_t dirty[C::NP];             // marks carried into the next sweep
-    uint8_t low[C::NP];               // 1: lowered by this run, at C::mine(); 2: a source on its first run
+    alignas(8) uint8_t dirty[C::NP];  // marks carried into the next sweep (these two are cleared eight at a time)
+    alignas(8) uint8_t low[C::NP];    // 1: lowered by this run, at C::mine(); 2: a source on its first run
 };
 
 template <int TX, int TY, int TZ, int OP = 0, bool COUNT = false>

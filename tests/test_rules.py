@@ -58,3 +58,17 @@ def test_planes_that_used_to_wrap(R):
         assert furthest(tile, nx, ny) >= 1 << 32
         assert nx * ny < (1 << 29) // (tile[2] + 2)   # what the bound once was
         assert not R.rule_offsets_fit_32(*tile, nx, nx * ny)
+
+
+def test_flag_bytes_cleared_as_words_are_aligned(tmp_path):
+    """The byte flags of a tile in LDS are cleared eight at a time."""
+    src = tmp_path / "layout.hip"
+    src.write_text('#include <stddef.h>\n#include "eik_adjoint.hpp"\nusing namespace eik;\n' + "".join(
+        f"using A{i} = AdjTile<{x}, {y}, {z}>;\nusing S{i} = SweepTile<{x}, {y}, {z}, 0>;\n"
+        f"using R{i} = SweepTile<{x}, {y}, {z}, 4>;\n"
+        f"static_assert(offsetof(A{i}, dirty) % 8 == 0 && sizeof(A{i}) % 8 == 0);\n"
+        f"static_assert(offsetof(S{i}, dirty) % 8 == 0 && offsetof(S{i}, low) % 8 == 0);\n"
+        f"static_assert(offsetof(R{i}, dirty) % 8 == 0 && offsetof(R{i}, low) % 8 == 0);\n"
+        for i, (x, y, z) in enumerate(TILES)))
+    hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+    subprocess.run([hipcc, "--cuda-host-only", "-fsyntax-only", "-std=c++17", "-I", CSRC, str(src)], check=True)
