@@ -23,4 +23,28 @@ EIK_RULE bool offsets_fit_32(int64_t nx, int64_t plane) {
     return last < (1ll << 29);
 }
 
+// When a worker that waits for work gives up (an internal error: the launch can
+// make no progress any more).  It looks now and then at a word that every end of
+// a run changes, handed on or not, and gives up once that has stood still for
+// kStallTicks, or as soon as another worker has, so that one expiry ends the
+// launch.  Time alone would also pass while the whole process is off the device,
+// so it takes kStallLooks looks as well (a tenth of a second of polling or more).
+constexpr uint64_t kStallTicks = 1400000000ull;  // 14 s of the 100 MHz clock
+constexpr uint32_t kStallLooks = 4096;
+struct StallWatch {
+    uint64_t seen = 0, since = 0;
+    uint32_t looks = 0;  // since `seen` was first seen (0: not looked yet)
+    EIK_RULE bool gives_up(uint64_t progress, bool another_did, uint64_t now) {
+        if (another_did) return true;
+        if (looks == 0 || progress != seen) {
+            seen = progress;
+            since = now;
+            looks = 1;
+            return false;
+        }
+        if (looks < kStallLooks) ++looks;
+        return looks == kStallLooks && now - since > kStallTicks;
+    }
+};
+
 }  // namespace eik

@@ -70,6 +70,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "eik_rules.hpp"
+
 namespace eik {
 
 // Wait until every memory operation this wave issued has completed (device
@@ -87,6 +89,7 @@ constexpr int kCounters = 24;
 constexpr int kRings = 32;    // buckets of the window
 constexpr int kShards = 8;    // rings per bucket
 constexpr int kWide = 17, kPatience = 3;  // window of an idle workgroup, and after how many polls
+constexpr int kLookEvery = 16;            // idle polls between looks at the launch's progress
 // Each ring counter (head, tail, count + running) lives in its own 256-byte
 // line, so polling one does not slow the atomics on the others.
 constexpr int kCtrPad = 64;                 // uint32 words per counter line
@@ -159,22 +162,22 @@ __device__ __forceinline__ void pend_add(const Sched& s, uint32_t queued, uint32
     __hip_atomic_fetch_add(pend_word(s, my_shard()), ((unsigned long long)queued << 32) + ended, __ATOMIC_RELAXED,
                            __HIP_MEMORY_SCOPE_AGENT);
 }
+// Tiles ever queued, or runs ever ended, over all shards.  All 64 lanes.
+__device__ __forceinline__ uint32_t pend_sum(const Sched& s, bool queued) {
+    const int lane = threadIdx.x & 63;
+    unsigned long long w = 0;
+    if (lane < kShards)
+        w = __hip_atomic_load(pend_word(s, lane), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    stores_done();  // these loads return before any later one goes out
+    uint32_t v = queued ? (uint32_t)(w >> 32) : (uint32_t)w;
+#pragma unroll
+    for (int off = 1; off < kShards; off <<= 1) v += __shfl_xor(v, off);
+    return (uint32_t)__builtin_amdgcn_readfirstlane((int)v);
+}
 // True when no work is left anywhere.  All 64 lanes.
 __device__ __forceinline__ bool all_done(const Sched& s) {
-    const int lane = threadIdx.x & 63;
-    uint32_t sum[2];
-#pragma unroll
-    for (int pass = 0; pass < 2; ++pass) {
-        unsigned long long w = 0;
-        if (lane < kShards)
-            w = __hip_atomic_load(pend_word(s, lane), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        stores_done();  // the first pass's loads return before the second's go out
-        uint32_t v = pass == 0 ? (uint32_t)w : (uint32_t)(w >> 32);
-#pragma unroll
-        for (int off = 1; off < kShards; off <<= 1) v += __shfl_xor(v, off);
-        sum[pass] = (uint32_t)__builtin_amdgcn_readfirstlane((int)v);
-    }
-    return sum[0] == sum[1];
+    const uint32_t ended = pend_sum(s, false);
+    return ended == pend_sum(s, true);
 }
 __device__ __forceinline__ void cr_add(const Sched& s, int r, uint64_t v) {
     __hip_atomic_fetch_add(ring_cr(s, r), (unsigned long long)v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -347,13 +350,15 @@ __device__ __forceinline__ void idle_sleep(int units) {
 // Further still costs more early runs than it saves waiting (13601x2801, tuned
 // window: 31 ms with 16 buckets, 65 ms with all 32).
 //
-// The watchdog counts consecutive polls that saw no progress anywhere (no count
-// word, `cur` or live-work change); it fires after 2^kStallBits of them (about
-// 14 s with the back-off below), however long a valid solve takes.  kMaxSleep
-// caps the back-off (units of s_sleep(127), about 3.4 us); with few workgroups
-// polling (64 or fewer) the cap is a quarter of one, as they cannot flood the
-// counters and the front's next tile waits for the poll.
-template <int kMaxSleep, int kStallBits, class Take>
+// Every kLookEvery idle polls it looks whether the launch still makes progress
+// (StallWatch: the runs ended so far and `cur`).  The count words would not do: a
+// run that is handed on again and again, a front along a channel one tile wide,
+// leaves all of them as they are.
+//
+// kMaxSleep caps the back-off (units of s_sleep(127), about 3.4 us); with few
+// workgroups polling (64 or fewer) the cap is a quarter of one, as they cannot
+// flood the counters and the front's next tile waits for the poll.
+template <int kMaxSleep, class Take>
 __device__ __forceinline__ int claim_with(const Sched& s, int64_t* slot, int32_t& cur_hint, Take take) {
     const int lane = threadIdx.x & 63;
     int win = s.lookahead + 1;
@@ -363,9 +368,8 @@ __device__ __forceinline__ int claim_with(const Sched& s, int64_t* slot, int32_t
     const unsigned long long own_lanes = 0x0101010101010101ull << own;
     static_assert(kShards == 8, "the lane masks below");
     constexpr int kParts = kRings / kCols;
-    long long idle = 0;   // polls so far (sets the back-off)
-    long long stall = 0;  // polls since anything last moved (the watchdog)
-    unsigned long long seen = ~0ull;
+    long long idle = 0;  // polls so far (sets the back-off)
+    StallWatch watch;
     uint32_t rnd = (uint32_t)wall_clock64() * 0x9E3779B1u + blockIdx.x * 0x85EBCA6Bu;
     for (;;) {
         const int32_t c = cur_hint;
@@ -462,17 +466,17 @@ __device__ __forceinline__ int claim_with(const Sched& s, int64_t* slot, int32_t
                 if (got == -2) return -2;
             }
             __builtin_amdgcn_s_sleep(8);
-            stall = 0;
             continue;
         }
         if (moved) continue;
-        if (__ballot(w[0] != seen)) stall = 0;  // something moved since the last poll
-        seen = w[0];
         ++idle;
         if (idle >= kPatience) win = max(win, kWide);
-        if (++stall > (1ll << kStallBits)) {
-            if (lane == 0) set_flag(s, kFlagWatchdog);
-            return -2;
+        if (idle % kLookEvery == 0) {
+            const uint64_t progress = ((uint64_t)(uint32_t)c << 32) | pend_sum(s, false);
+            if (watch.gives_up(progress, ld_rlx(s.poisoned) != 0, wall_clock64())) {
+                if (lane == 0) set_flag(s, kFlagWatchdog);
+                return -2;
+            }
         }
         // exponential back-off from about 0.1 us keeps idle workgroups from
         // flooding the counters the busy ones need
@@ -487,7 +491,7 @@ __device__ __forceinline__ int claim_with(const Sched& s, int64_t* slot, int32_t
 // One tile for a block of its own (the block-per-tile kernels).
 __device__ __forceinline__ int claim(const Sched& s, int64_t* slot, int32_t& cur_hint) {
     int tile = -1;
-    const int rc = claim_with<8, 19>(s, slot, cur_hint, [&](int r, int32_t) {
+    const int rc = claim_with<8>(s, slot, cur_hint, [&](int r, int32_t) {
         int got = -1;
         if ((threadIdx.x & 63) == 0) got = try_claim(s, r);
         got = __shfl(got, 0);
@@ -544,7 +548,7 @@ __device__ __forceinline__ int claim_group(const Sched& s, GroupMail& g, int w, 
         int item = -1;
         int64_t b = 0;
         unsigned int who = 0;
-        const int got = claim_with<1, 22>(s, &b, cur_hint, [&](int r, int32_t count) {
+        const int got = claim_with<1>(s, &b, cur_hint, [&](int r, int32_t count) {
             who = (unsigned int)__builtin_amdgcn_readfirstlane(
                 (int)__hip_atomic_load(&g.idle, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP));
             // a share of what is queued, so that the blocks' waves fill evenly

@@ -19,4 +19,11 @@ int rule_offsets_fit_32(int tx, int ty, int tz, int64_t nx, int64_t plane) {
     return -1;
 }
 
+uint64_t rule_stall_ticks() { return kStallTicks; }
+StallWatch* stall_new() { return new StallWatch(); }
+void stall_delete(StallWatch* w) { delete w; }
+int stall_gives_up(StallWatch* w, uint64_t progress, int another, uint64_t now) {
+    return w->gives_up(progress, another != 0, now);
+}
+
 }  // extern "C"

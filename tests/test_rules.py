@@ -19,6 +19,10 @@ def R(tmp_path_factory):
                     os.path.join(ROOT, "tests", "rules_host.cpp")], check=True)
     lib = ctypes.CDLL(out)
     lib.rule_offsets_fit_32.argtypes = [ctypes.c_int] * 3 + [ctypes.c_int64] * 2
+    lib.rule_stall_ticks.restype = ctypes.c_uint64
+    lib.stall_new.restype = ctypes.c_void_p
+    lib.stall_delete.argtypes = [ctypes.c_void_p]
+    lib.stall_gives_up.argtypes = [ctypes.c_void_p, ctypes.c_uint64, ctypes.c_int, ctypes.c_uint64]
     return lib
 
 
@@ -72,3 +76,41 @@ def test_flag_bytes_cleared_as_words_are_aligned(tmp_path):
         for i, (x, y, z) in enumerate(TILES)))
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     subprocess.run([hipcc, "--cuda-host-only", "-fsyntax-only", "-std=c++17", "-I", CSRC, str(src)], check=True)
+
+
+SECOND = 100_000_000  # ticks of the 100 MHz clock
+
+
+def looks(R, n, step, progress=lambda i: 7, another=lambda i: 0, start=10 ** 12):
+    """Index of the look (one every `step` ticks) at which a worker gives up, or None."""
+    w = R.stall_new()
+    try:
+        for i in range(n):
+            if R.stall_gives_up(w, progress(i), another(i), start + int(i * step)):
+                return i
+    finally:
+        R.stall_delete(w)
+
+
+def test_stall_ends_after_the_stated_time_whatever_the_back_off(R):
+    assert R.rule_stall_ticks() == 14 * SECOND
+    for step in (3000, 30000, 300000):  # 30 us to 3 ms between looks
+        i = looks(R, 15 * SECOND // step, step)
+        assert 14 * SECOND <= i * step <= 14 * SECOND + 2 * step, step
+
+
+def test_progress_between_looks_never_ends_a_launch(R):
+    """Hand-ons along a channel leave the count words alone; the runs ended go on."""
+    assert looks(R, 200_000, 30000, progress=lambda i: i) is None             # 60 s
+    assert looks(R, 200_000, 30000, progress=lambda i: i // 40_000) is None   # a run of 12 s each
+    assert looks(R, 200_000, 30000, progress=lambda i: (i // 20_000) % 2 ** 32 - 1 & 2 ** 64 - 1) is None
+
+
+def test_time_off_the_device_is_not_a_stall(R):
+    for step in (20 * SECOND, 3600 * SECOND):
+        assert looks(R, 4000, step) is None
+
+
+def test_one_expiry_ends_every_wait(R):
+    assert looks(R, 10, 3000, progress=lambda i: i, another=lambda i: i >= 3) == 3
+    assert looks(R, 1, 3000, another=lambda i: 1) == 0
