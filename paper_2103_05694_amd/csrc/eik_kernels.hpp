@@ -385,6 +385,7 @@ __global__ void __launch_bounds__(TX * TY) k_ablate(SolveArgs A) {
         }
         if (tid == 0) {
             s_upd = 0u;
+            s_more[0] = 0;
             s_more[1] = 0;
             s_more[2] = 0;
         }

@@ -142,3 +142,69 @@ def test_work_classification_needs_dbar(gpu):
         gpu.solve(f, 1.0, torch.tensor([0]), op="dhat", work_ref=ref)
     with pytest.raises(gpu.EikError):
         gpu.solve(f, 1.0, torch.tensor([0]), track_change=True)   # d-bar needs no tracking
+
+
+def _passes_of_two_tiles(f, src, tile):
+    """Relaxation passes of the d-hat solver on one workgroup for a grid of two
+    tiles side by side whose rows lie in one wave: a pass evaluates its marked
+    points at once, a lowered point marks its neighbours, and the last pass of
+    a run is the first that marks nothing."""
+    ny, nx = f.shape
+    q = 1.0 / f
+    t = np.full((ny + 2, nx + 2), np.inf)
+    t[1 + src // nx, 1 + src % nx] = 0.0
+    free = np.ones((ny, nx), dtype=bool)
+    free[src // nx, src % nx] = False
+    total, visited, now = 0, [False, False], [int(src % nx >= tile)]
+    while now:
+        k = now.pop(0)
+        x0, x1 = k * tile, min((k + 1) * tile, nx)
+        before = t[1:-1, 1:-1].copy()
+        holds_source = not free[:, x0:x1].all()
+        mark = np.zeros((ny, nx), dtype=bool)
+        mark[:, x0:x1] = not visited[k] or holds_source
+        if visited[k] and not holds_source:
+            edge, halo = (x1 - 1, x1) if k == 0 else (x0, x0 - 1)
+            mark[:, edge] = t[1:-1, 1 + halo] < t[1:-1, 1 + edge]
+        while True:
+            total += 1
+            a = np.minimum(t[1:-1, :-2], t[1:-1, 2:])
+            b = np.minimum(t[:-2, 1:-1], t[2:, 1:-1])
+            with np.errstate(invalid="ignore"):
+                two = 0.5 * ((a + b) + np.sqrt(2.0 * (q * q) - (a - b) * (a - b)))
+                r = np.where(np.abs(a - b) >= q, np.minimum(a, b) + q, two)
+            r = np.where(np.isinf(a) & np.isinf(b), np.inf, r)
+            cur = t[1:-1, 1:-1]
+            ch = mark & free & (r != cur)
+            low = ch & (r < cur)
+            t[1:-1, 1:-1] = np.where(ch, r, cur)
+            mark = np.zeros((ny, nx), dtype=bool)
+            mark[1:] |= low[:-1]
+            mark[:-1] |= low[1:]
+            mark[:, 1:] |= low[:, :-1]
+            mark[:, :-1] |= low[:, 1:]
+            mark[:, :x0] = False
+            mark[:, x1:] = False
+            if not (low[:, x0:x1].any()):
+                break
+        fell = t[1:-1, 1:-1] < before
+        if not visited[k]:
+            fell |= ~free
+        face = tile - 1 if k == 0 else tile
+        if nx > tile and fell[:, face].any():
+            now.append(1 - k)
+        visited[k] = True
+    return total
+
+
+@pytest.mark.parametrize("ny", [1, 2, 3, 4])
+def test_passes_do_not_depend_on_the_tile_before(gpu, ny):
+    """The pass flags of a tile start clear: a run that finds nothing to do ends
+    after one pass, whatever the workgroup ran before."""
+    rng = np.random.default_rng(ny)
+    for nx in [1] + list(range(17, 33)):
+        f = rng.uniform(1.0, 1.2, (ny, nx))
+        src = int(rng.integers(0, min(nx, 16)))
+        gpu.solve(torch.from_numpy(f).cuda(), 1.0, torch.tensor([src]), op="dhat", tile=(16, 8), grid_blocks=1,
+                  check_status=False)
+        assert gpu.status().relax_passes == _passes_of_two_tiles(f, np.int64(src), 16), (nx, src)
