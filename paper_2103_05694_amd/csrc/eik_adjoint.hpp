@@ -556,12 +556,12 @@ __global__ void __launch_bounds__((64 * adj_waves<TX, TY, TZ>()))
         // A face point whose parent lies across that face unblocks the neighbour,
         // keyed by the parent's own time, the earliest bucket in which that
         // parent can be taken (its other children, later in time, are then mostly
-        // done as well).  The keys only order the work: floats rounded down.
+        // done as well).
         unsigned long long face = kInfBits;
 #pragma unroll
         for (int f = 0; f < C::NF; ++f) {
             if (!((has >> f) & 1)) continue;
-            float fk = __uint_as_float(0x7F800000u);
+            double fk = inf64();
             unsigned long long any = 0;
 #pragma unroll
             for (int b = 0; b < HB[f]; ++b) {
@@ -572,12 +572,12 @@ __global__ void __launch_bounds__((64 * adj_waves<TX, TY, TZ>()))
                 const uint32_t want = (f & 1) ? 2u : 1u;
                 const bool on = in && sF[e.point()] != 0 && ((sP[L] >> (2 * (f >> 1))) & 3u) == want;
                 const double key = fmax(tref - sT[L + F::out(f)], 0.0);
-                fk = on ? fminf(fk, __double2float_rd(key)) : fk;
+                fk = on ? nmin(fk, key) : fk;
                 any |= __ballot(on);
             }
             if (any) {
-                const float m = __uint_as_float(wave_min_u32(__float_as_uint(fk)));
-                if (lane == f) face = as_u64((double)m);
+                const uint64_t m = wave_min_u64(as_u64(fk));
+                if (lane == f) face = m;
             }
         }
         // face neighbours x-, x+, y-, y+, z-, z+ (bit 30: the tile exists)

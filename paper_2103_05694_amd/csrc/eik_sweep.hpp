@@ -155,6 +155,19 @@ __device__ __forceinline__ uint32_t wave_min_u32(uint32_t v) {
     return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
 }
 
+// The same for 64 bits: the smallest high half, then the smallest low half of the
+// lanes that have it, which is mostly one lane.
+__device__ __forceinline__ uint64_t wave_min_u64(uint64_t v) {
+    const uint32_t hi = wave_min_u32((uint32_t)(v >> 32));
+    const unsigned long long who = __ballot((uint32_t)(v >> 32) == hi);
+    uint32_t lo;
+    if ((who & (who - 1)) == 0)
+        lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, __ffsll((long long)who) - 1);
+    else
+        lo = wave_min_u32((uint32_t)(v >> 32) == hi ? (uint32_t)v : ~0u);
+    return ((uint64_t)hi << 32) | lo;
+}
+
 // One wave's tile in LDS.
 template <int TX, int TY, int TZ, int OP>
 struct SweepTile {
@@ -595,14 +608,13 @@ __global__ void __launch_bounds__((64 * SweepCfg<TX, TY, TZ>::W))
             }
         }
         // A lowered face value matters to the neighbour only where it is below
-        // the neighbour's own value there (its halo cell here, as staged).  The
-        // keys only order the work, so they are kept as floats rounded down.
-        // Lane f gets face f's key.
+        // the neighbour's own value there (its halo cell here, as staged).  Lane f
+        // gets face f's key.
         unsigned long long face = kInfBits;
 #pragma unroll
         for (int f = 0; f < C::NF; ++f) {
             if (!((has >> f) & 1)) continue;
-            float fk = __uint_as_float(0x7F800000u);
+            double fk = inf64();
             unsigned long long any = 0;
 #pragma unroll
             for (int b = 0; b < HB[f]; ++b) {
@@ -612,12 +624,12 @@ __global__ void __launch_bounds__((64 * SweepCfg<TX, TY, TZ>::W))
                 const int L = e.lds();
                 const double v = sT[L];
                 const bool low = in && sC[C::mine(e.point())] != 0 && v < sT[L + F::out(f)];
-                fk = low ? fminf(fk, __double2float_rd(v)) : fk;
+                fk = low ? nmin(fk, v) : fk;
                 any |= __ballot(low);
             }
             if (any) {
-                const float m = __uint_as_float(wave_min_u32(__float_as_uint(fk)));
-                if (lane == f) face = as_u64((double)m);
+                const uint64_t m = wave_min_u64(as_u64(fk));
+                if (lane == f) face = m;
             }
         }
         unsigned long long self_key = kInfBits;

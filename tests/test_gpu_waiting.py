@@ -21,3 +21,24 @@ def test_channel_longer_than_the_watchdog(gpu, oracle_lib):
     assert st.handoffs > 0.9 * st.tile_visits
     ref = oracle_lib.fmm(f, 1.0, src)
     assert np.array_equal(t.cpu().numpy().ravel().view(np.uint64), ref.ravel().view(np.uint64))
+
+
+@pytest.mark.parametrize("power", [300, -300])
+def test_buckets_at_any_scale_of_time(gpu, oracle_lib, power):
+    """Speeds, bucket width and start time scaled by a power of two: the keys
+    that order the work keep the range of the times, so the buckets are walked
+    as they are unscaled, and the times are the unscaled ones scaled."""
+    f = np.random.default_rng(9).uniform(1.0, 3.0, (33, 70, 90))
+    src = torch.tensor([0])
+    kw = dict(tile=(8, 8, 8), lookahead=0, check_status=False)
+    adv = []
+    for p in (0, power):
+        t = gpu.solve(torch.from_numpy(np.ldexp(f, -p)).cuda(), 1.0, src, delta=float(np.ldexp(0.5, p)), **kw)
+        adv.append(gpu.status().bucket_advances)
+        if p == 0:
+            ref = t.cpu().numpy()
+            assert np.array_equal(ref.view(np.uint64), oracle_lib.fmm(f, 1.0, src.numpy()).reshape(f.shape).view(np.uint64))
+        else:
+            assert np.array_equal(t.cpu().numpy().view(np.uint64), np.ldexp(ref, p).view(np.uint64))
+    print(adv)
+    assert adv[0] > 40 and adv[1] > adv[0] / 2
