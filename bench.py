@@ -421,10 +421,11 @@ def bench_ablation(args, torch, eik, W) -> dict:
 def bench_schedules(args, torch, eik, W) -> dict:
     """Schedule comparison in one kernel (the paper's work-efficiency view):
     one bucket (a plain FIFO worklist, the topology-driven extreme), narrow
-    buckets (close to fast marching's order) and the tuned width, on the
-    headline model.  Every operator evaluation is classified against the final
-    times: empty (no change), good (sets the final value), bad (lowers the
-    value to something that is lowered again later)."""
+    buckets in strict order (close to fast marching's order) and with idle
+    workers looking past it, and the tuned width, on the headline model.
+    Every operator evaluation is classified against the final times: empty (no
+    change), good (sets the final value), bad (lowers the value to something
+    that is lowered again later)."""
     p = W.layered_3d(512, 512, 256, h=10.0, seed=2)
     f = torch.from_numpy(p.field).cuda()
     src = torch.as_tensor(p.src).cuda()
@@ -432,18 +433,22 @@ def bench_schedules(args, torch, eik, W) -> dict:
     ref = eik.solve(f, p.h, src, delta=args.delta, horizon=args.horizon, lookahead=args.lookahead, **kw)
     eik.status()
     out = {"workload": "3D 512x512x256 layered model (the headline solve)", "tile": list(args.tile), "rows": []}
-    for name, delta, hz, la in (("one bucket (FIFO)", 0.0, 0, 0), ("narrow buckets", args.delta / 8.0, 0, 0),
-                                ("tuned", args.delta, args.horizon, args.lookahead)):
+    for name, delta, hz, la, strict in (("one bucket (FIFO)", 0.0, 0, 0, False),
+                                        ("narrow buckets, strict order", args.delta / 8.0, 0, 0, True),
+                                        ("narrow buckets", args.delta / 8.0, 0, 0, False),
+                                        ("tuned", args.delta, args.horizon, args.lookahead, False)):
         t = torch.empty_like(f)
-        eik.solve(f, p.h, src, delta=delta, horizon=hz, lookahead=la, out=t, **kw)
+        sch = dict(kw, delta=delta, horizon=hz, lookahead=la, strict_window=strict)
+        eik.solve(f, p.h, src, out=t, **sch)
         eik.status()
         torch.cuda.synchronize()
-        eik.solve(f, p.h, src, delta=delta, horizon=hz, lookahead=la, out=t, time_kernels=True, **kw)
+        eik.solve(f, p.h, src, out=t, time_kernels=True, **sch)
         ms = eik.status().kernel_ms
-        eik.solve(f, p.h, src, delta=delta, horizon=hz, lookahead=la, out=t, work_ref=ref, **kw)
+        eik.solve(f, p.h, src, out=t, work_ref=ref, **sch)
         st = eik.status()
         ev, imp, good = st.evaluations, st.improving, st.final_updates
-        out["rows"].append({"schedule": name, "delta": delta, "horizon": hz, "lookahead": la, "kernel_ms": ms,
+        out["rows"].append({"schedule": name, "delta": delta, "horizon": hz, "lookahead": la,
+                            "strict_window": strict, "kernel_ms": ms,
                             "visits_per_tile": st.tile_visits / max(st.ntiles, 1),
                             "evaluations_per_point": ev / p.npts, "empty": (ev - imp) / max(ev, 1),
                             "good": good / max(ev, 1), "bad": (imp - good) / max(ev, 1),

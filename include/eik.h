@@ -82,6 +82,12 @@ extern "C" {
                                      NaN or negative (sign bit set) input value is replaced by
                                      +inf and reported by eik_status as EIK_EINVAL. */
 
+#define EIK_FLAG_STRICT_WINDOW 128u  /* eik_opts.flags: keep every claim within `lookahead`.  Without
+                                     it a worker that finds no work there in a few polls looks
+                                     up to 16 buckets above the lowest non-drained one, so that
+                                     lookahead == 0 is the strict bucket order only with this
+                                     flag.  Changes the schedule, never the result. */
+
 #define EIK_OP_DBAR 0     /* eik_opts.op: smallest double with S(r) >= c (section "Achieving
                              Exact Monotonicity with Finite Precision Arithmetic") */
 #define EIK_OP_DHAT 1     /* the reordered explicit formula of Table "tab:prec_2" */
@@ -114,10 +120,12 @@ typedef struct {
                                 eik_status then reports the mean duration of the kernels timed
                                 since the previous eik_status (at most 4096 launches in
                                 between).  EIK_FLAG_TIMELINE, EIK_FLAG_TRACK_CHANGE,
-                                EIK_FLAG_WARM_START, EIK_FLAG_PACKED: above */
+                                EIK_FLAG_WARM_START, EIK_FLAG_PACKED,
+                                EIK_FLAG_STRICT_WINDOW: above */
     int32_t lookahead;       /* 0..16: work may be taken from the lowest non-drained bucket
                                 and this many buckets above it; a worker that finds none
-                                there in a few polls looks up to 16 buckets above it */
+                                there in a few polls looks up to 16 buckets above it, unless
+                                EIK_FLAG_STRICT_WINDOW is set (with 0: strict bucket order) */
     int32_t horizon;         /* 0 => off; k in 1..4: a run of a tile claimed from bucket b
                                 settles only values r with floor(r / delta) < b + k and requeues
                                 the tile for the rest (no effect when delta == 0) */

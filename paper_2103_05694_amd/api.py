@@ -41,7 +41,7 @@ def make_opts(delta: float = 0.0, tile: Optional[Sequence[int]] = None, grid_blo
               max_tile_visits: int = 0, time_kernels: bool = False, lookahead: int = 0,
               timeline: bool = False, op: str = "dbar", horizon: int = 0,
               work_ref: Optional[torch.Tensor] = None, track_change: bool = False,
-              warm_start: bool = False, packed: bool = False) -> eik_opts:
+              warm_start: bool = False, packed: bool = False, strict_window: bool = False) -> eik_opts:
     o = eik_opts()
     o.delta = float(delta)
     t = tuple(tile) if tile else (0, 0, 0)
@@ -53,7 +53,8 @@ def make_opts(delta: float = 0.0, tile: Optional[Sequence[int]] = None, grid_blo
     o.max_tile_visits = int(max_tile_visits)
     o.flags = (_lib.EIK_FLAG_TIME_KERNELS if time_kernels else 0) | \
         (_lib.EIK_FLAG_TIMELINE if timeline else 0) | (_lib.EIK_FLAG_TRACK_CHANGE if track_change else 0) | \
-        (_lib.EIK_FLAG_WARM_START if warm_start else 0) | (_lib.EIK_FLAG_PACKED if packed else 0)
+        (_lib.EIK_FLAG_WARM_START if warm_start else 0) | (_lib.EIK_FLAG_PACKED if packed else 0) | \
+        (_lib.EIK_FLAG_STRICT_WINDOW if strict_window else 0)
     o.lookahead = int(lookahead)
     o.horizon = int(horizon)
     o.op = _op_code(op)
@@ -175,10 +176,12 @@ def solve(field: torch.Tensor, h: float, sources, t0: Optional[torch.Tensor] = N
           check_status: bool = True, stream=None, time_kernels: bool = False, lookahead: int = 0,
           timeline: bool = False, op: str = "dbar", horizon: int = 0,
           work_ref: Optional[torch.Tensor] = None, track_change: bool = False, warm_start: bool = False,
-          packed: bool = False):
+          packed: bool = False, strict_window: bool = False):
     """First-arrival times; returns t, or (t, parents) when parents=True.
     `delta` (the priority bucket width), `lookahead` (0..16: how many buckets
-    past the lowest open one a claim may take work from), `horizon`, `tile`,
+    past the lowest open one a claim may take work from; a worker that finds
+    none there in a few polls looks 16 past it, unless `strict_window` is set:
+    then lookahead=0 is the strict bucket order), `horizon`, `tile`,
     `grid_blocks` and `packed` (accepted, no effect on the solve,
     EIK_FLAG_PACKED) only schedule the work: the result is the same bits for
     every choice (the d-bar operator is monotone and causal).
@@ -211,7 +214,7 @@ def solve(field: torch.Tensor, h: float, sources, t0: Optional[torch.Tensor] = N
         if work_ref.shape != field.shape:
             raise ValueError("work_ref must have the field's shape")
     o = make_opts(delta, tile, grid_blocks, max_tile_visits, time_kernels, lookahead, timeline, op,
-                  horizon, work_ref, track_change, warm_start, packed)
+                  horizon, work_ref, track_change, warm_start, packed, strict_window)
     rc = L.eik_solve(ctypes.byref(g), field.data_ptr(), src.numel(), src.data_ptr(),
                      t0d.data_ptr() if t0d is not None else None, t.data_ptr(),
                      par.data_ptr() if par is not None else None, ctypes.byref(o),
@@ -226,7 +229,7 @@ def solve_rect(field: torch.Tensor, xs, ys, zs=None, sources=None, t0=None, kind
                delta: float = 0.0, tile: Optional[Sequence[int]] = None, grid_blocks: int = 0,
                max_tile_visits: int = 0, out: Optional[torch.Tensor] = None, check_status: bool = True,
                stream=None, time_kernels: bool = False, lookahead: int = 0, horizon: int = 0,
-               warm_start: bool = False) -> torch.Tensor:
+               warm_start: bool = False, strict_window: bool = False) -> torch.Tensor:
     """First-arrival times on a rectilinear grid: xs, ys[, zs] are the
     coordinates of the points along each axis (host sequences or CPU tensors,
     strictly increasing), so the spacing may vary per axis and index."""
@@ -256,7 +259,7 @@ def solve_rect(field: torch.Tensor, xs, ys, zs=None, sources=None, t0=None, kind
         _check_buf(out, "out", torch.float64, field.numel(), field.device)
     t = out if out is not None else torch.empty_like(field)
     o = make_opts(delta, tile, grid_blocks, max_tile_visits, time_kernels, lookahead, horizon=horizon,
-                  warm_start=warm_start)
+                  warm_start=warm_start, strict_window=strict_window)
     rc = L.eik_solve_rect(ctypes.byref(g), coords[0].ctypes.data, coords[1].ctypes.data,
                           coords[2].ctypes.data if len(coords) == 3 else None, field.data_ptr(), src.numel(),
                           src.data_ptr(), t0d.data_ptr() if t0d is not None else None, t.data_ptr(),
@@ -283,7 +286,7 @@ def adjoint(field: torch.Tensor, h: float, t: torch.Tensor, parents: torch.Tenso
             tile: Optional[Sequence[int]] = None, grid_blocks: int = 0,
             out: Optional[torch.Tensor] = None, mu_out: Optional[torch.Tensor] = None,
             check_status: bool = True, stream=None, time_kernels: bool = False,
-            lookahead: int = 0, packed: bool = False) -> torch.Tensor:
+            lookahead: int = 0, packed: bool = False, strict_window: bool = False) -> torch.Tensor:
     """d loss / d slowness from d loss / d t through the recorded upwind parents."""
     for a in (field, t, dL_dt):
         _check_field(a)
@@ -303,7 +306,7 @@ def adjoint(field: torch.Tensor, h: float, t: torch.Tensor, parents: torch.Tenso
     L = _lib.load()
     g = _grid_of(field.shape, h, kind)
     grad = out if out is not None else torch.empty_like(field)
-    o = make_opts(delta, tile, grid_blocks, 0, time_kernels, lookahead, packed=packed)
+    o = make_opts(delta, tile, grid_blocks, 0, time_kernels, lookahead, packed=packed, strict_window=strict_window)
     rc = L.eik_adjoint(ctypes.byref(g), field.data_ptr(), t.data_ptr(), parents.data_ptr(),
                        dL_dt.data_ptr(), grad.data_ptr(),
                        mu_out.data_ptr() if mu_out is not None else None, ctypes.byref(o),
@@ -407,14 +410,15 @@ def pack(fields: Sequence[torch.Tensor], hs: Union[float, Sequence[float]], sour
 def solve_packed(b: Batch, t_packed: torch.Tensor, par_packed: Optional[torch.Tensor] = None,
                  delta: float = 0.0, tile=None, grid_blocks: int = 0, stream=None,
                  time_kernels: bool = False, lookahead: int = 0, horizon: int = 0,
-                 packed: bool = False) -> None:
+                 packed: bool = False, strict_window: bool = False) -> None:
     """Enqueue one batched forward launch (no host synchronisation)."""
     dev = b.field.device
     _check_buf(t_packed, "t_packed", torch.float64, b.npts, dev)
     if par_packed is not None:
         _check_buf(par_packed, "par_packed", torch.uint8, b.npts, dev)
     L = _lib.load()
-    o = make_opts(delta, tile, grid_blocks, 0, time_kernels, lookahead, horizon=horizon, packed=packed)
+    o = make_opts(delta, tile, grid_blocks, 0, time_kernels, lookahead, horizon=horizon, packed=packed,
+                  strict_window=strict_window)
     check(L.eik_solve_batched(b.nprob, b.grids, b.offsets, b.field.data_ptr(), b.src_off,
                               b.src.data_ptr(), b.t0.data_ptr() if b.t0 is not None else None,
                               t_packed.data_ptr(), par_packed.data_ptr() if par_packed is not None else None,
@@ -424,7 +428,7 @@ def solve_packed(b: Batch, t_packed: torch.Tensor, par_packed: Optional[torch.Te
 def adjoint_packed(b: Batch, t_packed: torch.Tensor, par_packed: torch.Tensor, g_packed: torch.Tensor,
                    grad_packed: torch.Tensor, mu_packed: Optional[torch.Tensor] = None, delta: float = 0.0,
                    tile=None, grid_blocks: int = 0, stream=None, time_kernels: bool = False,
-                   lookahead: int = 0, packed: bool = False) -> None:
+                   lookahead: int = 0, packed: bool = False, strict_window: bool = False) -> None:
     """Enqueue one batched adjoint launch (no host synchronisation)."""
     dev = b.field.device
     _check_buf(t_packed, "t_packed", torch.float64, b.npts, dev)
@@ -434,7 +438,7 @@ def adjoint_packed(b: Batch, t_packed: torch.Tensor, par_packed: torch.Tensor, g
     if mu_packed is not None:
         _check_buf(mu_packed, "mu_packed", torch.float64, b.npts, dev)
     L = _lib.load()
-    o = make_opts(delta, tile, grid_blocks, 0, time_kernels, lookahead, packed=packed)
+    o = make_opts(delta, tile, grid_blocks, 0, time_kernels, lookahead, packed=packed, strict_window=strict_window)
     check(L.eik_adjoint_batched(b.nprob, b.grids, b.offsets, b.field.data_ptr(), t_packed.data_ptr(),
                                 par_packed.data_ptr(), g_packed.data_ptr(), grad_packed.data_ptr(),
                                 mu_packed.data_ptr() if mu_packed is not None else None,

@@ -38,7 +38,7 @@ constexpr int kThreads = 256;
 // A push from a run claimed from bucket b lands at most kRings - 1 - lookahead
 // buckets above b; 16 leaves a push range of 15 buckets.
 constexpr int kMaxLookahead = 16;
-static_assert(kMaxLookahead < kRings && kMaxLookahead < 64, "the claim window is read by one wave");
+static_assert(kMaxLookahead < kWide && kWide < kRings, "a push must not reach a bucket behind `cur`");
 constexpr int kScalWords = 192;
 constexpr int kTimelineCap = 1 << 16;
 constexpr int kSCur = 0, kSFlags = 128, kSPoisoned = 129;
@@ -319,7 +319,7 @@ int check_opts(const eik_opts* o) {
     if (o->grid_blocks < 0) return fail(EIK_EINVAL, "grid_blocks must be >= 0");
     if (o->max_tile_visits < 0) return fail(EIK_EINVAL, "max_tile_visits must be >= 0");
     if (o->flags & ~(EIK_FLAG_TIME_KERNELS | EIK_FLAG_TIMELINE | EIK_FLAG_TRACK_CHANGE | EIK_FLAG_WARM_START |
-                     EIK_FLAG_PACKED))
+                     EIK_FLAG_PACKED | EIK_FLAG_STRICT_WINDOW))
         return fail(EIK_EINVAL, "unknown flags");
     if ((o->flags & EIK_FLAG_PACKED) && o->op != EIK_OP_DBAR)
         return fail(EIK_ENOTSUP, "compacted passes run with d-bar only");
@@ -398,6 +398,7 @@ Sched make_sched(const Bufs& w, const eik_opts* o) {
     s.inv_delta = (d > 0.0 && std::isfinite(d)) ? 1.0 / d : 0.0;
     s.max_visits = o ? (long long)o->max_tile_visits : 0;
     s.lookahead = o ? o->lookahead : 0;
+    s.strict = (o && (o->flags & EIK_FLAG_STRICT_WINDOW)) ? 1 : 0;
     s.horizon = o ? o->horizon : 0;
     s.track = (o && (o->flags & EIK_FLAG_TRACK_CHANGE)) ? 1 : 0;
     const bool tl = o && (o->flags & EIK_FLAG_TIMELINE) && w.timeline;

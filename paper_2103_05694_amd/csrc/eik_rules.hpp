@@ -23,6 +23,15 @@ EIK_RULE bool offsets_fit_32(int64_t nx, int64_t plane) {
     return last < (1ll << 29);
 }
 
+// Buckets from the current one on that a claim may take work from: `lookahead`
+// beyond the current one, and for a worker that has found nothing in kPatience
+// polls kWide of them, unless the caller wants the window kept (`strict`).
+constexpr int kWide = 17, kPatience = 3;
+EIK_RULE int claim_window(int lookahead, bool strict, long long idle_polls) {
+    const int own = lookahead + 1;
+    return strict || idle_polls < kPatience || own > kWide ? own : kWide;
+}
+
 // When a worker that waits for work gives up (an internal error: the launch can
 // make no progress any more).  It looks now and then at a word that every end of
 // a run changes, handed on or not, and gives up once that has stood still for

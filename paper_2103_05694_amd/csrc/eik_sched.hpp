@@ -10,7 +10,7 @@
 //    the window [cur, cur + NB); the rings k mod NB hold it;
 //  * a claimer takes work from the lowest bucket that has any, within a window
 //    above the current bucket `cur` (Sched::lookahead, or kWide for a workgroup
-//    that has been idle); `cur` moves on (to the next bucket that is not drained)
+//    that has been idle, unless the caller keeps it from that); `cur` moves on (to the next bucket that is not drained)
 //    only once nothing is queued in it and no tile claimed from it is still
 //    running.  This is the bucket discipline of delta-stepping with a window:
 //    the number of premature (later lowered again) tile runs stays small;
@@ -88,7 +88,6 @@ constexpr uint32_t kQ = 1u, kR = 2u, kV = 4u, kS = 8u;
 constexpr int kCounters = 24;
 constexpr int kRings = 32;    // buckets of the window
 constexpr int kShards = 8;    // rings per bucket
-constexpr int kWide = 17, kPatience = 3;  // window of an idle workgroup, and after how many polls
 constexpr int kLookEvery = 16;            // idle polls between looks at the launch's progress
 // Each ring counter (head, tail, count + running) lives in its own 256-byte
 // line, so polling one does not slow the atomics on the others.
@@ -116,6 +115,7 @@ struct Sched {
     double inv_delta;    // 1/delta, 0 => single bucket
     long long max_visits;  // 0 => unlimited
     int lookahead;       // claims may come from buckets cur .. cur + lookahead
+    int strict;          // also those of an idle worker (claim_window)
     int horizon;         // 0, or k: a run settles only values below bucket (its bucket + k)
     int track;           // ablation operators: re-activate on any change (else on decrease)
     unsigned long long* timeline;  // NULL, or [0] start, [1] end, then (time, bucket) per advance
@@ -344,7 +344,8 @@ __device__ __forceinline__ void idle_sleep(int units) {
 // line the work comes through, so where few items face many claimers only some
 // of them try: about as many as there are items.
 //
-// A workgroup that found nothing in kPatience polls looks kWide buckets far: it
+// A workgroup that found nothing in kPatience polls looks kWide buckets far
+// (claim_window; not with Sched::strict): it
 // has nothing to lose, while waiting for a bucket of few tiles to drain costs
 // every idle one a run's time (97x83x61, 616 tiles, no window: 3.4 -> 1.4 ms).
 // Further still costs more early runs than it saves waiting (13601x2801, tuned
@@ -361,7 +362,7 @@ __device__ __forceinline__ void idle_sleep(int units) {
 template <int kMaxSleep, class Take>
 __device__ __forceinline__ int claim_with(const Sched& s, int64_t* slot, int32_t& cur_hint, Take take) {
     const int lane = threadIdx.x & 63;
-    int win = s.lookahead + 1;
+    int win = claim_window(s.lookahead, s.strict, 0);
     const int own = my_shard();
     const int lj = lane / kShards, lsh = lane % kShards;
     constexpr int kCols = 64 / kShards;  // buckets read at once
@@ -470,7 +471,7 @@ __device__ __forceinline__ int claim_with(const Sched& s, int64_t* slot, int32_t
         }
         if (moved) continue;
         ++idle;
-        if (idle >= kPatience) win = max(win, kWide);
+        win = claim_window(s.lookahead, s.strict, idle);
         if (idle % kLookEvery == 0) {
             const uint64_t progress = ((uint64_t)(uint32_t)c << 32) | pend_sum(s, false);
             if (watch.gives_up(progress, ld_rlx(s.poisoned) != 0, wall_clock64())) {

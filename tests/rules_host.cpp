@@ -19,6 +19,8 @@ int rule_offsets_fit_32(int tx, int ty, int tz, int64_t nx, int64_t plane) {
     return -1;
 }
 
+int rule_claim_window(int lookahead, int strict, int64_t idle) { return claim_window(lookahead, strict != 0, idle); }
+
 uint64_t rule_stall_ticks() { return kStallTicks; }
 StallWatch* stall_new() { return new StallWatch(); }
 void stall_delete(StallWatch* w) { delete w; }

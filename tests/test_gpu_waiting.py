@@ -42,3 +42,24 @@ def test_buckets_at_any_scale_of_time(gpu, oracle_lib, power):
             assert np.array_equal(t.cpu().numpy().view(np.uint64), np.ldexp(ref, p).view(np.uint64))
     print(adv)
     assert adv[0] > 40 and adv[1] > adv[0] / 2
+
+
+def test_strict_window_keeps_the_bucket_order(gpu):
+    """With narrow buckets idle workers find work only above the window.  Kept
+    from it they take the buckets one by one: more advances, fewer early runs,
+    the same times and gradients."""
+    import workloads as W
+    p = W.layered_3d(160, 150, 100, h=10.0, seed=3)
+    f, src = torch.from_numpy(p.field).cuda(), torch.as_tensor(p.src).cuda()
+    g = torch.ones_like(f)
+    runs, advances, times, grads = [], [], [], []
+    for strict in (False, True):
+        t, par = gpu.solve(f, p.h, src, parents=True, tile=(8, 8, 8), delta=0.002, lookahead=0, strict_window=strict)
+        st = gpu.status()
+        runs.append(st.tile_visits)
+        advances.append(st.bucket_advances)
+        times.append(t)
+        grads.append(gpu.adjoint(f, p.h, t, par, g, tile=(8, 8, 8), delta=0.002, strict_window=strict))
+    print(runs, advances)
+    assert runs[1] < 0.85 * runs[0] and advances[1] > 1.2 * advances[0]
+    assert torch.equal(times[0], times[1]) and torch.equal(grads[0], grads[1])

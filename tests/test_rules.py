@@ -19,6 +19,7 @@ def R(tmp_path_factory):
                     os.path.join(ROOT, "tests", "rules_host.cpp")], check=True)
     lib = ctypes.CDLL(out)
     lib.rule_offsets_fit_32.argtypes = [ctypes.c_int] * 3 + [ctypes.c_int64] * 2
+    lib.rule_claim_window.argtypes = [ctypes.c_int, ctypes.c_int, ctypes.c_int64]
     lib.rule_stall_ticks.restype = ctypes.c_uint64
     lib.stall_new.restype = ctypes.c_void_p
     lib.stall_delete.argtypes = [ctypes.c_void_p]
@@ -114,3 +115,32 @@ def test_time_off_the_device_is_not_a_stall(R):
 def test_one_expiry_ends_every_wait(R):
     assert looks(R, 10, 3000, progress=lambda i: i, another=lambda i: i >= 3) == 3
     assert looks(R, 1, 3000, another=lambda i: 1) == 0
+
+
+def test_claim_window(R):
+    for la in range(17):
+        for idle in list(range(6)) + [1 << 40]:
+            assert R.rule_claim_window(la, 1, idle) == la + 1          # strict: the caller's, however long idle
+            assert R.rule_claim_window(la, 0, idle) == (la + 1 if idle < 3 else 17)
+
+
+def test_strict_window_is_an_option_of_every_solve():
+    """Accepted by the option check (which goes on to the next fault) and set by
+    every Python entry point that has a lookahead."""
+    import inspect
+
+    import paper_2103_05694_amd as eik
+    from paper_2103_05694_amd import _lib, build
+    if build.stale():
+        build.build()
+    L = _lib.load()
+    o = eik.make_opts(lookahead=17, strict_window=True)
+    assert o.flags == _lib.EIK_FLAG_STRICT_WINDOW and eik.make_opts().flags == 0
+    g = _lib.eik_grid(3, 8, 8, 8, 1.0, 0)
+    p = ctypes.c_void_p(16)
+    for rc in (L.eik_solve(ctypes.byref(g), p, 1, p, None, p, None, ctypes.byref(o), None),
+               L.eik_adjoint(ctypes.byref(g), p, p, p, p, p, None, ctypes.byref(o), None),
+               L.eik_solve_noalloc(ctypes.byref(g), p, 1, p, None, p, None, ctypes.byref(o), None)):
+        assert rc == -1 and b"lookahead" in L.eik_last_error()
+    for f in (eik.solve, eik.solve_rect, eik.adjoint, eik.solve_packed, eik.adjoint_packed):
+        assert inspect.signature(f).parameters["strict_window"].default is False, f
