@@ -23,6 +23,22 @@ EIK_RULE bool offsets_fit_32(int64_t nx, int64_t plane) {
     return last < (1ll << 29);
 }
 
+// Index of the last of n ascending values that are not above a bound (the first
+// one is not), by 64 probes at once: count(first, step, n) tells how many of the
+// values first + i * step (i < 64, i * step < n) are not above it.  One round up
+// to 64 values, two up to 4096, three up to 262144.
+template <class Count>
+EIK_RULE int last_not_above(int n, Count count) {
+    int first = 0;
+    while (n > 64) {
+        const int step = (n + 63) / 64;
+        const int at = (count(first, step, n) - 1) * step;
+        first += at;
+        n = n - at < step ? n - at : step;
+    }
+    return first + count(first, 1, n) - 1;
+}
+
 // Buckets from the current one on that a claim may take work from: `lookahead`
 // beyond the current one, and for a worker that has found nothing in kPatience
 // polls kWide of them, unless the caller wants the window kept (`strict`).

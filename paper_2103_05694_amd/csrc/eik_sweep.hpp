@@ -101,16 +101,15 @@ __device__ __forceinline__ void wave_order() { __builtin_amdgcn_fence(__ATOMIC_A
 __device__ __forceinline__ int uni(int v) { return __builtin_amdgcn_readfirstlane(v); }
 
 // The problem a tile belongs to, found by the wave together: one load of up to
-// 64 first tile ids per step instead of a binary search of dependent loads.
+// 64 first tile ids per round instead of a binary search of dependent loads.
 __device__ __forceinline__ Prob wave_prob_of_tile(const ProbTable& T, int tile) {
     if (T.nprob == 1) return T.p0;
     const int lane = threadIdx.x & 63;
-    int k = 0;
-    for (int b = 0; b < T.nprob; b += 64) {
-        const bool le = b + lane < T.nprob && T.probs[b + lane].tile_off <= tile;
-        k += __popcll(__ballot(le));
-    }
-    return T.probs[uni(k - 1)];
+    const int k = last_not_above(T.nprob, [&](int first, int step, int n) {
+        const long long i = (long long)lane * step;
+        return (int)__popcll(__ballot(i < n && T.probs[first + i].tile_off <= tile));
+    });
+    return T.probs[uni(k)];
 }
 
 // Cell c of face f (x-, x+, y-, y+, z-, z+) of a tile: the tile point on the

@@ -21,6 +21,16 @@ int rule_offsets_fit_32(int tx, int ty, int tz, int64_t nx, int64_t plane) {
 
 int rule_claim_window(int lookahead, int strict, int64_t idle) { return claim_window(lookahead, strict != 0, idle); }
 
+int rule_last_not_above(int n, const int* values, int bound, int* rounds) {
+    *rounds = 0;
+    return last_not_above(n, [&](int first, int step, int m) {
+        ++*rounds;
+        int k = 0;
+        for (long long i = 0; i < 64 && i * step < m; ++i) k += values[first + i * step] <= bound;
+        return k;
+    });
+}
+
 uint64_t rule_stall_ticks() { return kStallTicks; }
 StallWatch* stall_new() { return new StallWatch(); }
 void stall_delete(StallWatch* w) { delete w; }

@@ -4,6 +4,7 @@ import ctypes
 import os
 import subprocess
 
+import numpy as np
 import pytest
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
@@ -144,3 +145,18 @@ def test_strict_window_is_an_option_of_every_solve():
         assert rc == -1 and b"lookahead" in L.eik_last_error()
     for f in (eik.solve, eik.solve_rect, eik.adjoint, eik.solve_packed, eik.adjoint_packed):
         assert inspect.signature(f).parameters["strict_window"].default is False, f
+
+
+@pytest.mark.parametrize("n", [1, 2, 63, 64, 65, 127, 128, 129, 4095, 4096, 4097, 4160, 262144, 262145, 1000003])
+def test_last_not_above(R, n):
+    """The problem of a tile: right for every problem, in rounds that grow with
+    the logarithm of the problems to base 64."""
+    rng = np.random.default_rng(n)
+    first = np.concatenate([[0], np.cumsum(rng.integers(1, 5, n))]).astype(np.int32)  # first tile ids, end
+    rounds = ctypes.c_int(0)
+    most = 1 + (n > 64) + (n > 4096) + (n > 262144)
+    vp = first.ctypes.data_as(ctypes.POINTER(ctypes.c_int))
+    for i in range(n) if n <= 129 else np.unique(np.concatenate([rng.integers(0, n, 300), [0, 1, n - 2, n - 1]])):
+        for tile in (int(first[i]), int(first[i + 1]) - 1):
+            assert R.rule_last_not_above(n, vp, tile, ctypes.byref(rounds)) == i, (n, i)
+            assert rounds.value <= most, (n, i)
