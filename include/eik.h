@@ -160,8 +160,9 @@ typedef struct {
                                 wall clock): [0] claiming / waiting for work, [1] staging a
                                 tile and its halo in LDS, [2] relaxing (adjoint: readiness
                                 passes), [3] write-back + publish */
-    int64_t workgroups;      /* persistent workers of the last launch: waves, each running a
-                                tile at a time (ablation operators: workgroups) */
+    int64_t workgroups;      /* persistent workers of the last launch, each running a tile at a
+                                time: waves, or (ablation operators, launches of few tiles)
+                                workgroups */
     int64_t bucket_advances; /* times the lowest open priority bucket moved on */
     int64_t handoffs;        /* runs that started on a neighbour handed on by the previous run */
     int64_t evaluations;     /* with eik_opts.work_ref: operator evaluations in the solve */

@@ -154,7 +154,7 @@ struct AdjTile {
     using C = SweepCfg<TX, TY, TZ>;
     double t[C::NLDS];
     double m[C::NLDS];            // mu of a finished point, dL/dt of one that is not (halo: mu)
-    unsigned long long stat[9];   // as in k_ablate
+    unsigned long long stat[9];   // as in Block
     alignas(8) uint8_t dirty[C::NP];  // marks carried into the next sweep (cleared eight at a time)
     uint8_t par[C::NLDS];         // parent codes (bits 0-5), kDone, 0x80 a source or outside the grid
 };

@@ -14,7 +14,7 @@
 
 #include "eik.h"
 
-#include "eik_adjoint.hpp"
+#include "eik_block.hpp"
 
 using namespace eik;
 
@@ -209,6 +209,8 @@ int ensure_tiles(Workspace& w, int64_t ntiles) {
     return EIK_OK;
 }
 
+int64_t tiles_of(const Prob& p) { return (int64_t)p.ntx * p.nty * p.ntz; }
+
 bool same_probs(const std::vector<Prob>& a, const std::vector<Prob>& b) {
     return a.size() == b.size() && std::memcmp(a.data(), b.data(), sizeof(Prob) * a.size()) == 0;
 }
@@ -261,6 +263,8 @@ int make_table(Workspace& w, const std::vector<Prob>& probs, const std::vector<i
     T->src_off = nullptr;
     T->nprob = (int)probs.size();
     T->p0 = probs[0];
+    T->most_tiles = 0;
+    for (const Prob& p : probs) T->most_tiles = std::max(T->most_tiles, (int)tiles_of(p));
     T->nsrc0 = src_off ? (*src_off)[1] - (*src_off)[0] : 0;
     if (probs.size() == 1) return EIK_OK;
     const Table* tb = nullptr;
@@ -350,8 +354,6 @@ Prob make_prob(const eik_grid& g, TileShape ts, int64_t pt_off, int64_t tile_off
     p.h = g.h;
     return p;
 }
-
-int64_t tiles_of(const Prob& p) { return (int64_t)p.ntx * p.nty * p.ntz; }
 
 // The device buffers one forward or adjoint launch sequence works in: the
 // stream's workspace, or (eik_solve_noalloc) the library's static scratch.
@@ -479,19 +481,22 @@ int forward_seq(const Bufs& b, const ProbTable& T, int64_t nsrc, int64_t ntiles,
     a.rw = rw;
     a.warm = warm ? 1 : 0;
     a.s = s;
-    // the monotone operators run one wave per tile; the ablation operators, which
-    // are not causal, evaluate every marked point once per pass
+    // one wave per tile, or one workgroup: the ablation operators, which evaluate
+    // every marked point once per pass, and launches of few tiles (unless the
+    // caller bounds the workgroups)
+    using Few = FewTiles<TX, TY, TZ>;
+    constexpr bool exact = OP == EIK_OP_DBAR || OP == 4;
+    const bool any_grid = !o || o->grid_blocks == 0;
+    const bool block = !exact || (any_grid && !a.work_ref &&
+                                  (OP == 4 ? Few::rect(ntiles) : Few::solve(T.most_tiles, ntiles)));
     const void* kern = nullptr;
-    int threads = 64 * SweepCfg<TX, TY, TZ>::W;
-    if constexpr (OP == EIK_OP_DBAR) {
-        kern = a.work_ref ? (const void*)k_sweep<TX, TY, TZ, OP, true> : (const void*)k_sweep<TX, TY, TZ, OP>;
-    } else if constexpr (OP == 4) {
-        kern = (const void*)k_sweep<TX, TY, TZ, OP>;
-    } else {
-        static_assert(TZ == 1, "the ablation operators are two-dimensional");
-        threads = TX * TY;
-        kern = (const void*)k_ablate<TX, TY, OP>;
-    }
+    int threads = block ? TX * TY * TZ : 64 * SweepCfg<TX, TY, TZ>::W;
+    if constexpr (!exact || Few::kSolve)
+        if (block) kern = (const void*)k_block<TX, TY, TZ, OP>;
+    if constexpr (exact)
+        if (!block) kern = (const void*)k_sweep<TX, TY, TZ, OP>;
+    if constexpr (OP == EIK_OP_DBAR)
+        if (a.work_ref) kern = (const void*)k_sweep<TX, TY, TZ, OP, true>;
     int grid = 0;
     if ((rc = occupancy_grid(kern, threads, &grid, cached))) return rc;
     if (o && o->grid_blocks > 0) grid = std::min(grid, o->grid_blocks);
@@ -501,7 +506,7 @@ int forward_seq(const Bufs& b, const ProbTable& T, int64_t nsrc, int64_t ntiles,
     // compute units and idle waves do not poll (97x83x61, 616 tiles: 1.54 ms with
     // 3 waves a block, 1.66 with the 6 that fit; 45 tiles 0.85 / 0.92; no
     // difference once every wave has a tile, 9216 tiles: 3.0 / 3.0).
-    if (OP == EIK_OP_DBAR || OP == 4)
+    if (!block)
         threads = (int)std::min<int64_t>(threads, 64 * ((ntiles + grid - 1) / grid));
     if (tw && (rc = timing_begin(*tw, o))) return rc;
     void* kargs[] = {(void*)&a};
@@ -604,14 +609,18 @@ int adjoint(Workspace& w, const std::vector<Prob>& probs, int64_t ntiles, int64_
     a.tkey = w.tkey;
     a.tref_bits = tref;
     a.s = s;
+    using Few = FewTiles<TX, TY, TZ>;
+    const bool block = (!o || o->grid_blocks == 0) && Few::adjoint(T.most_tiles, ntiles);
     const void* kern = (const void*)k_adjoint<TX, TY, TZ>;
-    int threads = 64 * adj_waves<TX, TY, TZ>();
+    if constexpr (Few::kAdjoint)
+        if (block) kern = (const void*)k_adjoint_block<TX, TY, TZ>;
+    int threads = block ? TX * TY * TZ : 64 * adj_waves<TX, TY, TZ>();
     int grid = 0;
     if ((rc = occupancy_grid(kern, threads, &grid))) return rc;
     if (o && o->grid_blocks > 0) grid = std::min(grid, o->grid_blocks);
     if ((int64_t)grid > ntiles) grid = (int)ntiles;
     if (grid < 1) grid = 1;
-    threads = (int)std::min<int64_t>(threads, 64 * ((ntiles + grid - 1) / grid));
+    if (!block) threads = (int)std::min<int64_t>(threads, 64 * ((ntiles + grid - 1) / grid));
     if ((rc = timing_begin(w, o))) return rc;
     void* kargs[] = {(void*)&a};
     HIP_TRY(hipLaunchKernel(kern, dim3(grid), dim3(threads), kargs, 0, st));
@@ -915,6 +924,7 @@ int eik_solve_noalloc(const eik_grid* g, const double* field, int64_t nsrc, cons
     T.p0 = make_prob(*g, ts, 0, 0);
     T.nsrc0 = nsrc;
     const int64_t ntiles = tiles_of(T.p0);
+    T.most_tiles = (int)std::min(ntiles, kNaMaxTiles);
     if (ntiles > kNaMaxTiles)
         return fail(EIK_ENOTSUP, "eik_solve_noalloc: more than 65536 tiles (use eik_solve)");
     int dev = 0;

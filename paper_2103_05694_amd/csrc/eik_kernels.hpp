@@ -1,6 +1,6 @@
 // Forward kernels: per-solve reset, source placement, finalisation, the
-// upwind-parent record, the residual and the ablation solver; the solver itself
-// is in eik_sweep.hpp.
+// upwind-parent record and the residual; the solvers themselves are in
+// eik_sweep.hpp and eik_block.hpp.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -28,6 +28,7 @@ struct ProbTable {
     const Prob* probs;       // device table, used when nprob > 1
     const int64_t* src_off;  // device source offsets, used when nprob > 1
     int nprob;
+    int most_tiles;          // of one problem
     Prob p0;                 // the problem when nprob == 1
     int64_t nsrc0;           // its source count
 };
@@ -236,25 +237,8 @@ __global__ void k_warm_push(ProbTable T, int ntiles, const uint64_t* tile_min, S
 }
 
 // ---------------------------------------------------------------------------
-// tiles in LDS, and the ablation solver
+// shared by the tile kernels
 // ---------------------------------------------------------------------------
-
-template <int TX, int TY, int TZ, int NT>
-struct TileCfg {
-    static constexpr bool D3 = TZ > 1;
-    static constexpr int SY = TX + 2;
-    static constexpr int SZ = (TX + 2) * (TY + 2);
-    static constexpr int HZ = D3 ? TZ + 2 : 1;
-    static constexpr int ZOFF = D3 ? 1 : 0;
-    static constexpr int NLDS = SZ * HZ;
-    static constexpr int NP = TX * TY * TZ;
-    static constexpr int NPT = NP / NT;
-    static_assert(NP % NT == 0, "tile points must be a multiple of the block size");
-    static_assert(NT % 64 == 0, "block must be whole waves");
-    __device__ static constexpr int lds(int lx, int ly, int lz) {
-        return (lz + ZOFF) * SZ + (ly + 1) * SY + (lx + 1);
-    }
-};
 
 __device__ __forceinline__ double hload(const double* p) {
     // Halo cells belong to tiles other workgroups may be writing right now.
@@ -288,218 +272,6 @@ __device__ __forceinline__ void flush_stats(const Sched& S, const unsigned long 
     if (S.timeline)
         __hip_atomic_fetch_max(S.timeline + 1, (unsigned long long)wall_clock64(), __ATOMIC_RELAXED,
                                __HIP_MEMORY_SCOPE_AGENT);
-}
-
-// The precision ablation (two-dimensional grids): the same schedule with the
-// explicit operators OP 1..3 of apply_op.  They assign their value, which may
-// rise, and are not causal, so every neighbour of a changed point is marked
-// (with A.s.track on any change, else on a drop) and evaluated once per pass,
-// all of them at once: one thread per point, one workgroup per tile.  The
-// marks of a pass go to the other of two flag buffers, so one barrier per pass
-// orders them before the next pass's reads.
-template <int TX, int TY, int OP>
-__global__ void __launch_bounds__(TX * TY) k_ablate(SolveArgs A) {
-    constexpr int NT = TX * TY;
-    using C = TileCfg<TX, TY, 1, NT>;
-    __shared__ double sT[C::NLDS];
-    __shared__ uint8_t sDirty[2][NT + 4];
-    __shared__ int s_more[3];  // per pass (mod 3): some wave marked a point
-    __shared__ int s_tile, s_next;
-    __shared__ int64_t s_slot;
-    __shared__ uint32_t s_state, s_nb[6], s_nid[6];
-    __shared__ unsigned long long s_face[6];
-    __shared__ unsigned int s_upd;
-    // per-workgroup statistics: [0..3] phase times on the 100 MHz wall clock
-    // (claim, stage, relax, write + publish), [4] visits, [5] point updates,
-    // [6] passes, [7] hand-offs, [8] the last phase mark
-    __shared__ unsigned long long s_stat[9];
-
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int lx = tid % TX, ly = tid / TX, L = C::lds(lx, ly, 0);
-    const Sched& S = A.s;
-    if (tid == 0) {
-        s_next = -1;
-        s_slot = 0;
-        for (int i = 0; i < 8; ++i) s_stat[i] = 0;
-        s_stat[8] = wall_clock64();
-    }
-    auto phase = [&](int i) {
-        const unsigned long long now = wall_clock64();
-        s_stat[i] += now - s_stat[8];
-        s_stat[8] = now;
-    };
-    int32_t cur_hint = 0;  // wave 0: the window's lowest bucket as last seen
-    for (;;) {
-        if (tid < 64) {
-            int64_t slot = s_slot;
-            int tile = s_next;
-            if (tile < 0) tile = claim(S, &slot, cur_hint);
-            else if (tid == 0) ++s_stat[7];
-            if (tid == 0) {
-                s_next = -1;
-                s_tile = tile;
-                s_slot = slot;
-                if (tile >= 0) {
-                    // Q -> R; every load of this run is issued after it returned
-                    uint32_t st = __hip_atomic_fetch_xor(S.tstate + tile, kQ | kR, __ATOMIC_RELAXED,
-                                                         __HIP_MEMORY_SCOPE_AGENT);
-                    if ((st & (kQ | kR)) != kQ) set_flag(S, kFlagWatchdog);
-                    if (S.max_visits > 0) {
-                        unsigned long long v = __hip_atomic_fetch_add(S.counters + 3, 1ull, __ATOMIC_RELAXED,
-                                                                      __HIP_MEMORY_SCOPE_AGENT);
-                        if ((long long)v >= S.max_visits) {
-                            set_flag(S, kFlagLimit);
-                            st |= 0x80000000u;  // skip marker
-                        }
-                    }
-                    s_state = st;
-                }
-            }
-        }
-        __syncthreads();
-        const int tile = s_tile;
-        if (tile < 0) break;
-        const uint32_t st = s_state;
-        const Prob P = prob_of_tile(A.pt, tile);
-        const int tl = tile - P.tile_off;
-        const int tx = tl % P.ntx, ty = tl / P.ntx;
-        const int x0 = tx * TX, y0 = ty * TY;
-        if (tid == 0) {
-            ++s_stat[4];
-            phase(0);
-        }
-        if (st & 0x80000000u) {  // visit cap reached: drop the tile
-            if (tid == 0) drop_run(S, (uint32_t)tile, s_slot);
-            __syncthreads();
-            continue;
-        }
-        const bool visited = (st & kV) != 0;
-        // face neighbours x-, x+, y-, y+ (bit 30: the tile exists)
-        if (tid < 6) {
-            const int d = tid >> 1, step = (tid & 1) ? 1 : -1;
-            const int nx = tx + (d == 0 ? step : 0), ny = ty + (d == 1 ? step : 0);
-            const bool has = d < 2 && nx >= 0 && nx < P.ntx && ny >= 0 && ny < P.nty;
-            s_nb[tid] = has ? 0x40000000u : 0u;
-            s_nid[tid] = has ? (uint32_t)(P.tile_off + ny * P.ntx + nx) : 0u;
-            s_face[tid] = kInfBits;
-        }
-        if (tid == 0) {
-            s_upd = 0u;
-            s_more[0] = 0;
-            s_more[1] = 0;
-            s_more[2] = 0;
-        }
-        // ---- stage the tile and its halo -----------------------------------
-        const int x = x0 + lx, y = y0 + ly;
-        const bool in = x < P.nx && y < P.ny;
-        const int64_t gi = P.pt_off + (int64_t)y * P.nx + x;
-        double q = 0.0, t_in = inf64();
-        bool src = false;
-        if (in) {
-            bool ok;
-            q = field_q(A.field[gi], P.h, P.kind, ok);
-            t_in = as_f64(__hip_atomic_load((const uint64_t*)(A.t + gi), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-            if (!ok) set_flag(S, kFlagDomain);
-            src = signbit(t_in);
-            if (!ok || src) q = 0.0;  // a source is fixed
-            t_in = fabs(t_in);
-        }
-        sT[L] = t_in;
-        for (int i = tid; i < 2 * (TX + TY); i += NT) {
-            int hx, hy;
-            if (i < 2 * TY) {
-                hx = i / TY ? TX : -1;
-                hy = i % TY;
-            } else {
-                hx = (i - 2 * TY) % TX;
-                hy = (i - 2 * TY) / TX ? TY : -1;
-            }
-            const int X = x0 + hx, Y = y0 + hy;
-            const bool hin = X >= 0 && X < P.nx && Y >= 0 && Y < P.ny;
-            sT[C::lds(hx, hy, 0)] = hin ? hload(A.t + P.pt_off + (int64_t)Y * P.nx + X) : inf64();
-        }
-        sDirty[0][tid] = 0;
-        sDirty[1][tid] = 0;
-        __syncthreads();
-        // first pass: every point on a first run and in a tile holding a source;
-        // otherwise boundary points next to a halo value below their own
-        bool dirty = !visited || (st & kS) || S.horizon > 0;
-        if (!dirty)
-            dirty = (lx == 0 && sT[L - 1] < t_in) || (lx == TX - 1 && sT[L + 1] < t_in) ||
-                    (ly == 0 && sT[L - C::SY] < t_in) || (ly == TY - 1 && sT[L + C::SY] < t_in);
-        if (tid == 0) phase(1);
-        // ---- relax until the tile is quiet ---------------------------------
-        int cb = 0, passes = 0;
-        double v = t_in;
-        for (;;) {
-            if (tid == 0) s_more[(passes + 1) % 3] = 0;  // written next pass; last read two barriers ago
-            bool marked = false;
-            if (dirty && q > 0.0) {
-                const double ax = nmin(sT[L - 1], sT[L + 1]), ay = nmin(sT[L - C::SY], sT[L + C::SY]);
-                const double r = apply_op<OP>(ax, ay, inf64(), q);
-                const bool ch = r != v && r == r;
-                marked = S.track ? ch : (ch && r < v);
-                if (ch) {
-                    v = r;
-                    sT[L] = r;
-                }
-                if (marked) {
-                    uint8_t* nd = sDirty[cb ^ 1];
-                    if (lx > 0) nd[tid - 1] = 1;
-                    if (lx < TX - 1) nd[tid + 1] = 1;
-                    if (ly > 0) nd[tid - TX] = 1;
-                    if (ly < TY - 1) nd[tid + TX] = 1;
-                }
-            }
-            if (__ballot(marked) && lane == 0) s_more[passes % 3] = 1;
-            __syncthreads();
-            const int more = s_more[passes % 3];
-            ++passes;
-            if (!more) break;
-            cb ^= 1;
-            dirty = sDirty[cb][tid] != 0;
-            sDirty[cb][tid] = 0;
-            if (passes >= (1 << 16)) {  // these operators need not settle
-                if (tid == 0) set_flag(S, kFlagLimit);
-                break;
-            }
-        }
-        if (tid == 0) phase(2);
-        // ---- write back changed points, gather the faces' minima -----------
-        // every lowered face value counts (not causal), a raised one with tracking
-        // and on the first run a source, which no operator lowers
-        const bool chg = in && v != t_in;
-        const bool act = (chg && (v < t_in || S.track)) || (src && !visited);
-        if (chg) tstore(A.t + gi, v);
-        const bool on[4] = {lx == 0, lx == TX - 1, ly == 0, ly == TY - 1};
-#pragma unroll
-        for (int f = 0; f < 4; ++f) {
-            if (__ballot(act && on[f])) {
-                const double m = wave_min(act && on[f] ? v : inf64());
-                if (lane == 0) atomicMin(&s_face[f], (unsigned long long)as_u64(m));
-            }
-        }
-        const int cnt = __popcll(__ballot(chg));
-        if (cnt && lane == 0) atomicAdd(&s_upd, (unsigned int)cnt);
-        // every wave's stores complete before the block hands the tile's faces
-        // to the neighbours
-        stores_done();
-        __syncthreads();
-        if (tid < 64) {
-            const int nxt = publish(S, A.tkey, (uint32_t)tile, s_slot, !visited, s_nb, s_nid, s_face, true);
-            if (tid == 0) s_next = nxt;
-        }
-        if (tid == 0) {
-            s_stat[5] += s_upd;
-            s_stat[6] += (unsigned long long)passes;
-            phase(3);
-        }
-        __syncthreads();
-    }
-    if (tid == 0) {
-        phase(0);
-        flush_stats(S, s_stat);
-    }
 }
 
 // ---------------------------------------------------------------------------

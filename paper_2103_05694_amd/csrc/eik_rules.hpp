@@ -12,6 +12,39 @@
 
 namespace eik {
 
+// Launches of so few tiles that a run's own time decides take a workgroup per tile
+// (eik_block.hpp) instead of a wave per tile: `total` tiles, `most` of them in one
+// problem.  A run takes about half as long with all of a tile's points at once; a
+// wave evaluates fewer points and a compute unit holds five to ten of them.
+// Measured, wave / workgroup per tile, whole calls in ms, 16x8x8 and 32x32 tiles:
+//  * solves in 3D: 1 tile 0.18 / 0.12, 12 tiles 0.87 / 0.56, 384 tiles 3.05 / 1.90
+//    (random speeds, source inside) and 1.45 / 1.17 (layered, on the surface), 1000
+//    tiles 3.65 / 3.20 and 1.87 / 1.65, 1584 tiles 4.07 / 4.21 and 2.21 / 2.43;
+//    100 problems of 4 tiles 1.07 / 0.53.  Tiles of 256 points or fewer gain little
+//    beyond one (8x8x4: 1 tile 0.104 / 0.088, 256 tiles 0.82 / 0.77).
+//  * solves in 2D, where a front crosses a tile in twice the passes: 1 tile 0.158 /
+//    0.124, 100 problems of one 0.175 / 0.094, 1000 of one 0.27 / 0.26; 12 tiles
+//    0.52 / 0.49 (random) but 0.31 / 0.39 (layered), 256 tiles 1.6 / 2.0.
+//  * rectilinear solves, whose operator is the longest: 1 tile 0.46 / 0.32 (2D) and
+//    0.79 / 0.46 (3D), 32 tiles of 8x8x8 3.3 / 3.4.
+//  * adjoints, which evaluate a point once: 1 tile 0.125 / 0.080, 32 tiles of 16x8x8
+//    0.35 / 0.36 (layered) and 0.75 / 0.59 (random), 32 of 8x8x8 0.22 / 0.25, 4 of
+//    64x4x4 0.19 / 0.27; 100 problems of 4 tiles 0.47 / 0.37, 400 of 4 0.61 / 0.73.
+template <int TX, int TY, int TZ>
+struct FewTiles {
+    static constexpr int NP = TX * TY * TZ;
+    // whether the kernels are there for this shape at all
+    static constexpr bool kSolve = NP >= 256, kAdjoint = NP >= 512;
+    static EIK_RULE bool solve(int64_t most, int64_t total) {
+        if (TZ > 1 && NP >= 512) return total <= 1024;
+        return kSolve && most == 1 && total <= 512;
+    }
+    static EIK_RULE bool rect(int64_t total) { return kSolve && total == 1; }
+    static EIK_RULE bool adjoint(int64_t most, int64_t total) {
+        return kAdjoint && most <= (TZ >= 8 ? NP / 32 : 1) && total <= 512;
+    }
+};
+
 // Whether the cells of a tile that lies wholly in the grid, and of its face halos,
 // can be addressed by 32-bit byte offsets from the corner of the halo (one point
 // before the tile along each axis) in an array of doubles.  The furthest along

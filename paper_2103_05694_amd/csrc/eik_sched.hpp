@@ -490,9 +490,10 @@ __device__ __forceinline__ int claim_with(const Sched& s, int64_t* slot, int32_t
 }
 
 // One tile for a block of its own (the block-per-tile kernels).
+template <int kMaxSleep>
 __device__ __forceinline__ int claim(const Sched& s, int64_t* slot, int32_t& cur_hint) {
     int tile = -1;
-    const int rc = claim_with<8>(s, slot, cur_hint, [&](int r, int32_t) {
+    const int rc = claim_with<kMaxSleep>(s, slot, cur_hint, [&](int r, int32_t) {
         int got = -1;
         if ((threadIdx.x & 63) == 0) got = try_claim(s, r);
         got = __shfl(got, 0);

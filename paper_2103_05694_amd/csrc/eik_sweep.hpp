@@ -175,7 +175,7 @@ struct SweepTile {
     double q[C::NP];
     // rectilinear grids: reciprocal spacings [x- | x+ | y- | y+ | z- | z+] over the tile's coordinates
     double wx[OP == 4 ? 2 * (TX + TY + TZ) : 1];
-    unsigned long long stat[9];       // as in k_ablate
+    unsigned long long stat[9];       // as in Block
     alignas(8) uint8_t dirty[C::NP];  // marks carried into the next sweep (these two are cleared eight at a time)
     alignas(8) uint8_t low[C::NP];    // 1: lowered by this run, at C::mine(); 2: a source on its first run
 };

@@ -19,6 +19,17 @@ int rule_offsets_fit_32(int tx, int ty, int tz, int64_t nx, int64_t plane) {
     return -1;
 }
 
+int rule_few_tiles(int tx, int ty, int tz, int what, int64_t most, int64_t total) {
+#define EIK_ONE(a, b, c)                                    \
+    if (tx == a && ty == b && tz == c) {                    \
+        using F = FewTiles<a, b, c>;                        \
+        return what == 0 ? F::solve(most, total) : (what == 1 ? F::rect(total) : F::adjoint(most, total)); \
+    }
+    EIK_SHAPES(EIK_ONE)
+#undef EIK_ONE
+    return -1;
+}
+
 int rule_claim_window(int lookahead, int strict, int64_t idle) { return claim_window(lookahead, strict != 0, idle); }
 
 int rule_last_not_above(int n, const int* values, int bound, int* rounds) {

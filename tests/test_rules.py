@@ -20,6 +20,7 @@ def R(tmp_path_factory):
                     os.path.join(ROOT, "tests", "rules_host.cpp")], check=True)
     lib = ctypes.CDLL(out)
     lib.rule_offsets_fit_32.argtypes = [ctypes.c_int] * 3 + [ctypes.c_int64] * 2
+    lib.rule_few_tiles.argtypes = [ctypes.c_int] * 4 + [ctypes.c_int64] * 2
     lib.rule_claim_window.argtypes = [ctypes.c_int, ctypes.c_int, ctypes.c_int64]
     lib.rule_stall_ticks.restype = ctypes.c_uint64
     lib.stall_new.restype = ctypes.c_void_p
@@ -160,3 +161,20 @@ def test_last_not_above(R, n):
         for tile in (int(first[i]), int(first[i + 1]) - 1):
             assert R.rule_last_not_above(n, vp, tile, ctypes.byref(rounds)) == i, (n, i)
             assert rounds.value <= most, (n, i)
+
+
+@pytest.mark.parametrize("tile", TILES)
+def test_few_tiles(R, tile):
+    """Which launches take a workgroup per tile: everything of one tile of a shape
+    that has the kernels, nothing above the line."""
+    few = lambda what, most, total: R.rule_few_tiles(*tile, what, most, total)
+    points = tile[0] * tile[1] * tile[2]
+    deep = tile[2] > 1 and points >= 512
+    for total in (1, 2, 31, 32, 33, 512, 513, 1024, 1025, 1 << 30):
+        for most in sorted({1, 2, 16, 17, 32, 33, total}):
+            if most > total:
+                continue
+            assert few(0, most, total) == (total <= 1024 if deep else points >= 256 and most == 1 and total <= 512)
+            assert few(1, total, total) == (points >= 256 and total == 1)
+            lim = points // 32 if tile[2] >= 8 else 1
+            assert few(2, most, total) == (points >= 512 and most <= lim and total <= 512)
