@@ -936,7 +936,12 @@ int eik_solve_noalloc(const eik_grid* g, const double* field, int64_t nsrc, cons
     const int64_t npts = (int64_t)g->nx * g->ny * g->nz;
     if ((rc = na_dispatch(ts, b, T, nsrc, ntiles, npts, field, src_idx, src_t0, t_out, parents_out, opts)))
         return rc;
-    d->wiped = true;
+    // a call that was only captured has not run: the rings count as initialised
+    // from the first call that is enqueued for good
+    if (!d->wiped) {
+        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+        d->wiped = hipStreamIsCapturing(st, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone;
+    }
     d->last_stream = st;
     d->last_ntiles = ntiles;
     d->last_seq = next_seq();

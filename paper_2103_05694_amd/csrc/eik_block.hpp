@@ -10,8 +10,8 @@
 // operator (its serial FP64 chain), the LDS reads before it and one barrier,
 // about 1.05 us with 1024 threads in 3D and 0.77 us in 2D, however few points are
 // marked (a wave's level takes 0.49 and 0.37 us, but a run has three to five times
-// as many).  One thread per point, so that no wave has a second evaluation in a pass; a tile's waves then
-// fill a compute unit (119 registers, 4 waves per SIMD).
+// as many).  One thread per point, so that no wave has a second evaluation in a
+// pass; a tile's waves then fill a compute unit (119 registers, 4 waves per SIMD).
 #pragma once
 
 #include "eik_adjoint.hpp"

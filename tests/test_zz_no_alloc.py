@@ -107,3 +107,44 @@ def test_noalloc_limits_rejected_before_launch(gpu):
     assert rc == -6 and b"65536 sources" in L.eik_last_error()
     rc, _ = _call(L, "eik_solve_noalloc", f, 1.0, src, t, None, gpu.make_opts(time_kernels=True))
     assert rc == -6
+
+
+_CAPTURED_FIRST = """
+import ctypes, sys
+sys.path.insert(0, sys.argv[1])
+sys.path.insert(0, sys.argv[1] + "/tests")
+import torch
+import paper_2103_05694_amd as eik
+from paper_2103_05694_amd import _lib
+from test_zz_no_alloc import _call
+L = _lib.load()
+f = 1.0 + torch.rand((20, 33, 47), dtype=torch.float64, device="cuda")
+src = torch.tensor([1234], device="cuda")
+ref = eik.solve(f, 1.0, src)
+t = torch.zeros_like(f)
+graph = torch.cuda.CUDAGraph()
+with torch.cuda.graph(graph):
+    rc, _ = _call(L, "eik_solve_noalloc", f, 1.0, src, t)
+assert rc == 0
+for turn in range(3):   # eager first, then replays with eager calls in between
+    u = torch.zeros_like(f)
+    rc, st = _call(L, "eik_solve_noalloc", f, 1.0, src, u)
+    assert rc == 0 and L.eik_status(st, None) == 0, turn
+    assert torch.equal(u, ref), turn
+    t.zero_()
+    graph.replay()
+    torch.cuda.synchronize()
+    assert torch.equal(t, ref), turn
+print("captured first: ok", flush=True)
+"""
+
+
+def test_noalloc_first_call_captured(gpu):
+    """The first call of a process is captured and not replayed before an eager
+    call: that one must not take the static rings for initialised."""
+    import os
+    import subprocess
+    import sys
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    r = subprocess.run([sys.executable, "-c", _CAPTURED_FIRST, root], capture_output=True, text=True, timeout=100)
+    assert r.returncode == 0 and "captured first: ok" in r.stdout, r.stdout + r.stderr
