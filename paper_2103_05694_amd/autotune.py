@@ -1,6 +1,6 @@
 """Autotuner for the persistent solver's free parameters: the tile shape, the
 priority bucket width delta, the lookahead window of buckets a workgroup may
-take work from, the bucket horizon and the `packed` option (which no longer changes the kernels).
+take work from, and the bucket horizon (`packed` is recorded and changes nothing).
 
 The paper leaves the priority scale open and notes that the best trade-off
 between priority inversions and contention depends on hardware and input
@@ -33,7 +33,7 @@ TILES = {3: [(16, 8, 8), (8, 8, 8), (32, 8, 4)],
 DELTA_FACTORS = (0.0, 0.25, 0.5, 1.0, 2.0, 4.0, 8.0)
 GRID_BLOCKS = (0,)       # 0 = as many workgroups as fit on the device
 HORIZONS = (0, 1, 2)     # 0 = off; k = settle values below (bucket + k) only
-PACKED = (False, True)   # accepted and recorded; no effect on the wave-per-tile kernels
+PACKED = (False,)        # `packed` has no effect on the kernels: nothing to choose
 LOOKAHEADS = (2, 4, 8, 16)  # second stage: buckets beyond the lowest a claim may take work from
 LOOKAHEAD_FACTORS = (0.0625, 0.125, 0.25, 0.5, 1.0)  # bucket widths tried with a lookahead window
 
@@ -69,7 +69,7 @@ def tune(field: torch.Tensor, h: float, sources, kind: str = "speed",
          grid_blocks: Sequence[int] = GRID_BLOCKS, horizons: Sequence[int] = HORIZONS,
          packed: Sequence[bool] = PACKED, lookaheads: Sequence[int] = LOOKAHEADS,
          lookahead_factors: Sequence[float] = LOOKAHEAD_FACTORS, save: bool = True, log=print) -> dict:
-    """Time every (tile, delta, grid size, horizon, pass structure) candidate on
+    """Time every (tile, delta, grid size, horizon) candidate on
     this problem without a lookahead, then, with the best of them, every
     (lookahead, narrower delta) pair; all candidates must agree bitwise."""
     nd = field.dim()
@@ -108,7 +108,7 @@ def tune(field: torch.Tensor, h: float, sources, kind: str = "speed",
                     for pk in packed:
                         run(tile, fac, gb, hz, pk)
     # a lookahead window with narrower buckets, on the first stage's best for
-    # each tile and pass structure (what wins without a window often does not
+    # each tile (what wins without a window often does not
     # win with it)
     for tile in tiles:
         for pk in packed:
