@@ -117,7 +117,7 @@ __global__ void k_adj_push_all(int ntiles, const uint64_t* tile_tmax,
 
 // dL/ds from the final multipliers: fl(fl(mu * q) * h) at non-sources, 0 at
 // sources (mu is 0 there); a field value outside the domain raises the flag.
-// One block per tile, as k_adj_prep.
+// One block per tile, so that a tile's rows are read and written together.
 template <int TX, int TY, int TZ>
 __global__ void k_adj_grad(ProbTable T, int ntiles, const double* field, const uint8_t* par, const double* mu,
                            double* grad, uint32_t* flags) {
@@ -418,7 +418,7 @@ __global__ void __launch_bounds__((64 * adj_waves<TX, TY, TZ>()))
                     for (int i = lane; i < C::NP / 8; i += 64) ((uint64_t*)sF)[i] = 0;
                 }
                 bool quiet = false;
-                for (int k = 0; k < C::SWEEP; ++k) {
+                for (int k = 0; k < C::SPAN; ++k) {
                     unsigned long long act = __ballot(D & 1u);
                     if (!act) {
                         quiet = !__ballot(D != 0u);

@@ -35,8 +35,9 @@ int fail(int code, const std::string& msg) {
     } while (0)
 
 constexpr int kThreads = 256;
-// A push from a run claimed from bucket b lands at most kRings - 1 - lookahead
-// buckets above b; 16 leaves a push range of 15 buckets.
+// A push lands at most kRings - 1 buckets above the `cur` its run was claimed
+// under, and the run's own bucket lies less than kWide above that: the smallest
+// push range is kRings - kWide = 15 buckets.
 constexpr int kMaxLookahead = 16;
 static_assert(kMaxLookahead < kWide && kWide < kRings, "a push must not reach a bucket behind `cur`");
 constexpr int kScalWords = 192;

@@ -15,7 +15,9 @@
 //    running.  This is the bucket discipline of delta-stepping with a window:
 //    the number of premature (later lowered again) tile runs stays small;
 //  * a push goes at most kRings - 1 buckets above the `cur` its run was claimed
-//    under, and `cur` never decreases, so no two buckets share a ring;
+//    under, and `cur` never decreases, so no later bucket is put into the ring of
+//    an open one (an item that `cur` has passed by, see claim_with, counts as
+//    kRings buckets later, which only delays it);
 //  * delta = 0 puts everything in one bucket (a plain FIFO worklist);
 //  * the operator is monotone and causal, so none of this changes results.
 //
@@ -183,9 +185,6 @@ __device__ __forceinline__ void cr_add(const Sched& s, int r, uint64_t v) {
     __hip_atomic_fetch_add(ring_cr(s, r), (unsigned long long)v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-__device__ __forceinline__ uint32_t ld_rlx(uint32_t* p) {
-    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
 __device__ __forceinline__ int32_t ld_rlx(int32_t* p) {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
@@ -342,14 +341,18 @@ __device__ __forceinline__ void idle_sleep(int units) {
 // takes from the lowest bucket of its own shard, else from the lowest of the
 // others.  A claim that comes too late costs two read-modify-writes on the very
 // line the work comes through, so where few items face many claimers only some
-// of them try: about as many as there are items.
+// of them try: eight times as many as there are items, since most that could
+// are busy (twice as many: 512x512x256 11.5 -> 11.7 ms, 32 shots 58.3 -> 59.1;
+// 32 times: one shot of 256x256x128 11.0 -> 11.7, 8 uneven shots 17.9 -> 18.6).
 //
 // A workgroup that found nothing in kPatience polls looks kWide buckets far
-// (claim_window; not with Sched::strict): it
-// has nothing to lose, while waiting for a bucket of few tiles to drain costs
-// every idle one a run's time (97x83x61, 616 tiles, no window: 3.4 -> 1.4 ms).
-// Further still costs more early runs than it saves waiting (13601x2801, tuned
-// window: 31 ms with 16 buckets, 65 ms with all 32).
+// (claim_window; not with Sched::strict): it has nothing to lose, while waiting
+// for a bucket of few tiles to drain costs every idle one a run's time
+// (160x150x100, narrow buckets, no window: 13.2 ms kept to it, 2.7 ms looking
+// past it; 512x512x256 110.8 and 18.3).  Further still costs more early runs than
+// it saves waiting (13601x2801, tuned window: 31 ms with 16 buckets, 65 ms with
+// all 32).  Three polls: after eight, the 160x150x100 case takes 3.2 instead of
+// 2.9 ms and a shot 11.6 instead of 11.0, after one a shot 11.1.
 //
 // Every kLookEvery idle polls it looks whether the launch still makes progress
 // (StallWatch: the runs ended so far and `cur`).  The count words would not do: a
@@ -358,11 +361,13 @@ __device__ __forceinline__ void idle_sleep(int units) {
 //
 // kMaxSleep caps the back-off (units of s_sleep(127), about 3.4 us); with few
 // workgroups polling (64 or fewer) the cap is a quarter of one, as they cannot
-// flood the counters and the front's next tile waits for the poll.
+// flood the counters and the front's next tile waits for the poll (16x16x16, 4
+// tiles: 0.23 ms, 0.27 without; hundreds of workgroups: no difference either way).
 template <int kMaxSleep, class Take>
 __device__ __forceinline__ int claim_with(const Sched& s, int64_t* slot, int32_t& cur_hint, Take take) {
     const int lane = threadIdx.x & 63;
     int win = claim_window(s.lookahead, s.strict, 0);
+    const int wide = claim_window(s.lookahead, s.strict, kPatience);
     const int own = my_shard();
     const int lj = lane / kShards, lsh = lane % kShards;
     constexpr int kCols = 64 / kShards;  // buckets read at once
@@ -471,7 +476,7 @@ __device__ __forceinline__ int claim_with(const Sched& s, int64_t* slot, int32_t
         }
         if (moved) continue;
         ++idle;
-        win = claim_window(s.lookahead, s.strict, idle);
+        if (idle >= kPatience) win = wide;
         if (idle % kLookEvery == 0) {
             const uint64_t progress = ((uint64_t)(uint32_t)c << 32) | pend_sum(s, false);
             if (watch.gives_up(progress, ld_rlx(s.poisoned) != 0, wall_clock64())) {
@@ -553,7 +558,9 @@ __device__ __forceinline__ int claim_group(const Sched& s, GroupMail& g, int w, 
         const int got = claim_with<1>(s, &b, cur_hint, [&](int r, int32_t count) {
             who = (unsigned int)__builtin_amdgcn_readfirstlane(
                 (int)__hip_atomic_load(&g.idle, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP));
-            // a share of what is queued, so that the blocks' waves fill evenly
+            // a share of what is queued, so that the blocks' waves fill evenly (a
+            // quarter or a 64th instead of a 16th: 8 uneven shots 17.9 -> 17.8 and
+            // 18.4 ms, all else within 1%)
             const int want = max(1, min(__popc(who), count >> 4));
             return try_claim_many(s, r, want, item);
         });

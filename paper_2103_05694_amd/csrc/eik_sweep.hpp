@@ -61,9 +61,9 @@ struct SweepCfg {
     static constexpr int NP = TX * TY * TZ;
     static constexpr int NPT = NP / 64;           // points per lane, and levels per cycle
     static constexpr int NCOL = TY * TZ;          // columns along x
-    static constexpr int SPAN = TX + TY + TZ - 2; // levels of one sweep corner to corner
+    static constexpr int SPAN = TX + TY + TZ - 2; // levels of one sweep corner to corner; the octant is
+                                                  // chosen again after each
     static constexpr int NF = D3 ? 6 : 4;
-    static constexpr int SWEEP = SPAN;            // levels between choices of the octant
     // waves (tiles in flight) per workgroup: what the 160 KB of LDS of a
     // compute unit hold, one workgroup each, at most 16
     static constexpr int BYTES = 8 * NLDS + 8 * NP + 2 * NP;
@@ -479,7 +479,7 @@ __global__ void __launch_bounds__((64 * SweepCfg<TX, TY, TZ>::W))
                     for (int i = lane; i < C::NP / 8; i += 64) ((uint64_t*)sF)[i] = 0;
                 }
                 bool quiet = false;
-                for (int k = 0; k < C::SWEEP; ++k) {
+                for (int k = 0; k < C::SPAN; ++k) {
                     unsigned long long act = __ballot(D & 1u);
                     if (!act) {
                         quiet = !__ballot(D != 0u);
