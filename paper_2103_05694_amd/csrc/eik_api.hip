@@ -504,9 +504,9 @@ int forward_seq(const Bufs& b, const ProbTable& T, int64_t nsrc, int64_t ntiles,
     if ((int64_t)grid > ntiles) grid = (int)ntiles;
     if (grid < 1) grid = 1;
     // Fewer tiles than waves: fewer waves a block, so that tiles spread over the
-    // compute units and idle waves do not poll (97x83x61, 616 tiles: 1.54 ms with
-    // 3 waves a block, 1.66 with the 6 that fit; 45 tiles 0.85 / 0.92; no
-    // difference once every wave has a tile, 9216 tiles: 3.0 / 3.0).
+    // compute units and idle waves do not poll (waves on 97x83x61, 616 tiles: 1.54 ms
+    // with 3 a block, 1.66 with the 6 that fit; 45 tiles 0.85 / 0.92; no difference
+    // once every wave has a tile, 9216 tiles: 3.0 / 3.0).
     if (!block)
         threads = (int)std::min<int64_t>(threads, 64 * ((ntiles + grid - 1) / grid));
     if (tw && (rc = timing_begin(*tw, o))) return rc;

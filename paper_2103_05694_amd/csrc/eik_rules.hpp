@@ -15,33 +15,48 @@ namespace eik {
 // Launches of so few tiles that a run's own time decides take a workgroup per tile
 // (eik_block.hpp) instead of a wave per tile: `total` tiles, `most` of them in one
 // problem.  A run takes about half as long with all of a tile's points at once; a
-// wave evaluates fewer points and a compute unit holds five to ten of them.
-// Measured, wave / workgroup per tile, whole calls in ms, 16x8x8 and 32x32 tiles:
-//  * solves in 3D: 1 tile 0.18 / 0.12, 12 tiles 0.87 / 0.56, 384 tiles 3.05 / 1.90
-//    (random speeds, source inside) and 1.45 / 1.17 (layered, on the surface), 1000
-//    tiles 3.65 / 3.20 and 1.87 / 1.65, 1584 tiles 4.07 / 4.21 and 2.21 / 2.43;
-//    100 problems of 4 tiles 1.07 / 0.53.  Tiles of 256 points or fewer gain little
-//    beyond one (8x8x4: 1 tile 0.104 / 0.088, 256 tiles 0.82 / 0.77).
-//  * solves in 2D, where a front crosses a tile in twice the passes: 1 tile 0.158 /
-//    0.124, 100 problems of one 0.175 / 0.094, 1000 of one 0.27 / 0.26; 12 tiles
-//    0.52 / 0.49 (random) but 0.31 / 0.39 (layered), 256 tiles 1.6 / 2.0.
+// wave evaluates fewer points and a compute unit holds five to ten of them.  How
+// much fewer depends on the medium: least in random speeds with a source inside
+// (below "random"), most for a front through layers ("layered"), so the lines lie
+// where neither loses more than the other gains.  Measured, wave / workgroup per
+// tile, whole calls in ms:
+//  * solves in 3D, 16x8x8, random and layered: 1 tile 0.18 / 0.12, 384 tiles 3.05 /
+//    1.90 and 1.45 / 1.17, 1000 tiles 3.65 / 3.20 and 1.87 / 1.65, 1584 tiles 4.07 /
+//    4.21 and 2.21 / 2.43; 400 problems of 4 tiles 1.20 / 0.79 and 0.47 / 0.45, 200 of
+//    12 1.57 / 1.73 and 0.66 / 1.02, 30 of 64 2.08 / 2.49 and 1.00 / 1.06.  Tiles of 256
+//    points or fewer gain little beyond one (8x8x4: 1 tile 0.104 / 0.088, 256 tiles
+//    0.82 / 0.77).
+//  * solves in 2D, where a front crosses a tile in twice the passes, 32x32: 1 tile
+//    0.158 / 0.124, 1000 problems of one 0.27 / 0.26; 12 tiles of one problem 0.52 / 0.49
+//    and 0.31 / 0.39; 100 problems of 4 tiles 0.64 / 0.49 and 0.31 / 0.31, 400 of 4 0.83 /
+//    0.72 and 0.45 / 0.54.
 //  * rectilinear solves, whose operator is the longest: 1 tile 0.46 / 0.32 (2D) and
-//    0.79 / 0.46 (3D), 32 tiles of 8x8x8 3.3 / 3.4.
-//  * adjoints, which evaluate a point once: 1 tile 0.125 / 0.080, 32 tiles of 16x8x8
-//    0.35 / 0.36 (layered) and 0.75 / 0.59 (random), 32 of 8x8x8 0.22 / 0.25, 4 of
-//    64x4x4 0.19 / 0.27; 100 problems of 4 tiles 0.47 / 0.37, 400 of 4 0.61 / 0.73.
+//    0.79 / 0.46 (3D), 4 tiles of 8x8x8 1.18 / 1.06, 12 tiles of 16x8x8 7.2 / 6.1 (random)
+//    and 0.64 / 0.63 (layered), 24 tiles 1.10 / 1.33 (layered).
+//  * adjoints, which evaluate a point once: 16x8x8 1 tile 0.125 / 0.080, 32 tiles 1.22 /
+//    0.89 and 0.35 / 0.36, 512 tiles 3.13 / 2.37 and 1.43 / 1.25, 200 problems of 4 0.56 /
+//    0.51 and 0.34 / 0.31, 400 of 4 0.62 / 0.74 and 0.40 / 0.49; 8x8x8 12 tiles 0.31 / 0.29
+//    and 0.175 / 0.170, 32 tiles 0.36 / 0.33 and 0.22 / 0.25; 64x4x4 4 tiles 1.13 / 0.92 and
+//    0.19 / 0.27; 32x32 4 tiles 0.24 / 0.21 and 0.18 / 0.22, 100 problems of 4 0.38 / 0.36
+//    and 0.31 / 0.30, 200 of 4 0.44 / 0.48 and 0.38 / 0.42.
 template <int TX, int TY, int TZ>
 struct FewTiles {
     static constexpr int NP = TX * TY * TZ;
+    static constexpr bool kSquare = TX == 32 && TY == 32;
     // whether the kernels are there for this shape at all
     static constexpr bool kSolve = NP >= 256, kAdjoint = NP >= 512;
     static EIK_RULE bool solve(int64_t most, int64_t total) {
-        if (TZ > 1 && NP >= 512) return total <= 1024;
+        if (TZ > 1 && NP >= 512) return total <= (most <= 16 ? 1600 : 1024);
+        if (kSquare) return total <= 900 && (most == 1 || (most <= 9 && total >= 100));
         return kSolve && most == 1 && total <= 512;
     }
-    static EIK_RULE bool rect(int64_t total) { return kSolve && total == 1; }
+    static EIK_RULE bool rect(int64_t total) {
+        return kSolve && total <= (TZ > 1 && NP >= 512 ? (NP >= 1024 ? 12 : 8) : 1);
+    }
     static EIK_RULE bool adjoint(int64_t most, int64_t total) {
-        return kAdjoint && most <= (TZ >= 8 ? NP / 32 : 1) && total <= 512;
+        if (TZ >= 8) return total <= 800 && (NP >= 1024 || most <= 16);
+        if (kSquare && most > 1) return most <= 9 && total >= 100 && total <= 400;
+        return kAdjoint && most == 1 && total <= 512;
     }
 };
 

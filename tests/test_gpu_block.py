@@ -69,7 +69,7 @@ def test_adjoint_waves_on_small_grids(gpu, O, tile):
 @pytest.mark.parametrize("tile,shape", [((16, 8, 8), (64, 64, 256)), ((16, 8, 8), (64, 64, 257)), ((8, 8, 8), (64, 128, 64)),
                                         ((8, 8, 8), (65, 128, 64)), ((32, 32, 1), (1, 32, 32)), ((32, 32, 1), (1, 32, 33))])
 def test_solves_about_the_line(gpu, O, tile, shape):
-    """1024 tiles and more in 3D, one tile and two in 2D."""
+    """1024 tiles of one problem and more in 3D, one tile and two in 2D."""
     rng = np.random.default_rng(sum(shape))
     f = W.random_field(shape, rng, 0.5, 3.0, block=4)
     src = rng.integers(0, f.size, 2).astype(np.int64)
@@ -77,21 +77,23 @@ def test_solves_about_the_line(gpu, O, tile, shape):
         check(gpu, O, f, src, tile=tile if tile[2] > 1 else tile[:2], **kw)
 
 
-@pytest.mark.parametrize("n", [511, 512, 513])
-def test_batches_about_the_line(gpu, O, n):
-    """512 problems of one tile and one more; forward, parents and adjoint."""
+@pytest.mark.parametrize("tile,n", [((16, 8, 8), 800), ((16, 8, 8), 801), ((16, 8, 8), 1600), ((16, 8, 8), 1601),
+                                    ((8, 8, 8), 400), ((32, 32), 24), ((32, 32), 25), ((32, 32), 101), ((32, 32), 226)])
+def test_batches_about_the_line(gpu, O, tile, n):
+    """800 and 1600 problems of one tile, 25 and more of four tiles in 2D, each with
+    and without one more; forward, parents and adjoint."""
     rng = np.random.default_rng(n)
-    shapes = [(5, 7, 9), (8, 8, 16), (3, 8, 11)]
+    shapes = [(5, 7, 9), (8, 8, 16), (3, 8, 11)] if len(tile) == 3 else [(1, 33, 40), (1, 64, 64), (1, 50, 34)]
     fields = [W.random_field(shapes[i % 3], rng, 0.5, 4.0) for i in range(n)]
     srcs = [np.array([rng.integers(0, f.size)], dtype=np.int64) for f in fields]
-    b = gpu.pack([torch.from_numpy(f).cuda() for f in fields], 1.0, [torch.from_numpy(s) for s in srcs])
+    b = gpu.pack([torch.from_numpy(f if f.shape[0] > 1 else f[0]).cuda() for f in fields], 1.0, [torch.from_numpy(s) for s in srcs])
     t = torch.empty(b.npts, dtype=torch.float64, device="cuda")
     par = torch.empty(b.npts, dtype=torch.uint8, device="cuda")
     g = torch.from_numpy(rng.standard_normal(b.npts)).cuda()
     grad = torch.empty_like(t)
-    gpu.solve_packed(b, t, par, tile=(16, 8, 8))
+    gpu.solve_packed(b, t, par, tile=tile)
     gpu.status()
-    gpu.adjoint_packed(b, t, par, g, grad, tile=(16, 8, 8))
+    gpu.adjoint_packed(b, t, par, g, grad, tile=tile)
     gpu.status()
     ts, ps, gs, rs = b.views(t), b.views(par), b.views(g), b.views(grad)
     for i in range(0, n, 17):
@@ -103,11 +105,11 @@ def test_batches_about_the_line(gpu, O, n):
         assert np.max(np.abs(rs[i].cpu().numpy().ravel() - ra)) <= 1e-12 * np.max(np.abs(ra)), i
 
 
-@pytest.mark.parametrize("shape", [(32, 32, 64), (33, 32, 64), (24, 24, 24)])
+@pytest.mark.parametrize("shape", [(64, 80, 160), (65, 80, 160), (24, 24, 24)])
 def test_adjoints_about_the_line(gpu, O, shape):
-    """64 tiles and fewer of 16x8x8: either side of 32."""
+    """800 tiles of 16x8x8 and more."""
     rng = np.random.default_rng(sum(shape))
-    for sh in (shape, (shape[0], shape[1] // 2, shape[2])):
+    for sh in (shape,):
         f = W.random_field(sh, rng, 0.5, 5.0, block=2)
         src = np.unique(rng.integers(0, f.size, 2)).astype(np.int64)
         t = O.fmm(f, 1.0, src)

@@ -167,14 +167,25 @@ def test_last_not_above(R, n):
 def test_few_tiles(R, tile):
     """Which launches take a workgroup per tile: everything of one tile of a shape
     that has the kernels, nothing above the line."""
-    few = lambda what, most, total: R.rule_few_tiles(*tile, what, most, total)
+    few = lambda what, most, total: bool(R.rule_few_tiles(*tile, what, most, total))
     points = tile[0] * tile[1] * tile[2]
     deep = tile[2] > 1 and points >= 512
-    for total in (1, 2, 31, 32, 33, 512, 513, 1024, 1025, 1 << 30):
-        for most in sorted({1, 2, 16, 17, 32, 33, total}):
+    square = tile == (32, 32, 1)
+    for total in (1, 2, 8, 9, 12, 13, 16, 17, 99, 100, 400, 401, 512, 513, 800, 801, 900, 901, 1024, 1025, 1600, 1601, 1 << 30):
+        assert few(1, total, total) == (points >= 256 and total <= (1 if not deep else 12 if points >= 1024 else 8))
+        for most in sorted({1, 2, 9, 10, 16, 17, total}):
             if most > total:
                 continue
-            assert few(0, most, total) == (total <= 1024 if deep else points >= 256 and most == 1 and total <= 512)
-            assert few(1, total, total) == (points >= 256 and total == 1)
-            lim = points // 32 if tile[2] >= 8 else 1
-            assert few(2, most, total) == (points >= 512 and most <= lim and total <= 512)
+            small_batch = square and 1 < most <= 9 and total >= 100
+            if deep:
+                solve = total <= (1600 if most <= 16 else 1024)
+            elif square:
+                solve = total <= 900 and (most == 1 or small_batch)
+            else:
+                solve = points >= 256 and most == 1 and total <= 512
+            assert few(0, most, total) == solve, (most, total)
+            if tile[2] >= 8:
+                adj = total <= 800 and (points >= 1024 or most <= 16)
+            else:
+                adj = points >= 512 and (most == 1 and total <= 512 or small_batch and total <= 400)
+            assert few(2, most, total) == adj, (most, total)
