@@ -1,9 +1,8 @@
-// The persistent forward solver: one wave per tile, and as many waves (tiles in
-// flight) on a compute unit as its LDS holds tiles.
+// The persistent forward solver of all but small launches: one wave per tile, and
+// as many waves (tiles in flight) on a compute unit as its LDS holds tiles.
 //
-// A wave claims the approximately earliest active
-// tile (eik_sched.hpp), stages its times, the 1-cell halo and the per-point
-// constants in LDS, applies the update operator to dirty points until nothing
+// A wave claims the approximately earliest active tile (eik_sched.hpp), stages its
+// times, the 1-cell halo and the per-point constants in LDS, applies the update operator to dirty points until nothing
 // in the tile changes, writes the lowered points back and activates the face
 // neighbours whose halo changed (the paper's asynchronous marching method with
 // a tile as the unit of work; Theorem 1 makes every order reach the same bits).
@@ -27,12 +26,13 @@
 // running).  With many problems at once the waves are busy and the FP64 issue
 // and the LDS capacity (6 tiles of 16x8x8 a compute unit) bound it.  A workgroup
 // of 512 or 1024 threads per tile, Jacobi passes with a barrier each and rings
-// not split into shards, which this replaced, took, for the whole call: 512x512x256
-// layered, 16x8x8 tiles, 24.8 ms against 11.85 ms; 4096x4096, 16 sources, 32x32
-// tiles, 12.2 against 6.5 ms; 13601x2801, 36.7 against 29.5 ms; 32 problems of
-// 256x256x128 (forward and adjoint) 138 against 58 ms; 101x101 0.52 against
-// 0.34 ms.  More waves than tiles in LDS (waiting for a free one) made the
-// batch 4% faster and everything else 5% slower, and is not done.
+// not split into shards took, for the whole call: 512x512x256 layered, 16x8x8
+// tiles, 24.7 ms against 11.7; 4096x4096, 16 sources, 32x32 tiles, 12.4 against
+// 6.4 ms; 13601x2801, 37.0 against 30.0 ms; 32 problems of 256x256x128 (forward
+// and adjoint) 139 against 58 ms.  (On launches of few tiles that form, with the
+// shards, is the better one: eik_block.hpp.)  More waves than tiles in LDS
+// (waiting for a free one) made the batch 4% faster and everything else 5%
+// slower, and is not done.
 //
 // Only dirty points are evaluated.  A lane keeps the dirty bits of the points
 // it visits next in a register, bit i for the point i levels ahead.  In sweep
